@@ -68,7 +68,7 @@ int ic_op_sort_desc(ic_ctx* ctx, const void* values, int64_t n, int32_t* order);
  * that forbid allocation): the same stable descending order (order[j] =
  * index of the j-th largest of the n values; ties keep index order, -0
  * equals +0), computed by the same kernels, with the sort's keys, indices
- * and histograms in a file-scope device array of 48 MiB that every device
+ * and histograms in a file-scope device array of 50 MiB that every device
  * running the call holds until the process ends.  precision: IC_F32 or
  * IC_F64 (values: device, of that type); order: device int32[n]; stream: a
  * hipStream_t (NULL = default stream), synchronised once (the NaN check).

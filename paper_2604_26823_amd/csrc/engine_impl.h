@@ -83,7 +83,6 @@ class Engine final : public EngineBase {
     // sort length of rank-order matching: the field, or the 2 n^2 (n/2+1)
     // real and imaginary parts of the half spectrum (IC_ROM_FOURIER_REIM)
     rom_len_ = std::max(P_, 2 * Hq_);
-    sort_blocks_ = (rom_len_ + sk::kTile - 1) / sk::kTile;
 
     Carver c(ws);
     twp_ = c.take<cx<T>>(np_);
@@ -116,15 +115,14 @@ class Engine final : public EngineBase {
     dir_ = c.take<T>(P_);
     strial_ = c.take<T>(P_);
     gtrial_ = c.take<T>(P_);
-    keys_ = c.take<uint64_t>(rom_len_);
-    keys2_ = c.take<uint64_t>(rom_len_);
+    keys_ = c.take<sk::key_t<T>>(rom_len_);
+    keys2_ = c.take<sk::key_t<T>>(rom_len_);
     vals_ = c.take<uint32_t>(rom_len_);
     vals2_ = c.take<uint32_t>(rom_len_);
-    small_ = c.take<uint32_t>(rom_len_);
-    shist_ = c.take<uint32_t>(sk::kDigits * sort_blocks_);
+    shist_ = c.take<uint32_t>(sk::table_len(rom_len_));
     vbuf_ = c.take<T>(rom_len_);
-    tbuf_ = c.take<T>(rom_len_);
-    binc_ = c.take<uint32_t>(256);
+    binc_ = c.take<uint32_t>(2 * sk::kDigits);
+    bintab_ = c.take<uint8_t>(wtab_len_);
     // Block orders of the particles: one per mesh state d_0..d_S, one on the
     // data grid; ids and dest per order (see blocks.h).
     idtape_ = c.take<uint32_t>((size_t)(S_ + 1) * P_);
@@ -422,11 +420,8 @@ class Engine final : public EngineBase {
     if (n == 0) return;
     if (count_nonfinite(static_cast<const T*>(values), n) > 0)
       throw ApiError(IC_ERR_NONFINITE, "NaN in sort input");
-    sk::k_desc_keys<T><<<grid_for(n, kThreads), kThreads, 0, st_>>>(
-        static_cast<const T*>(values), keys_, vals_, n);
-    IC_LAUNCHED();
-    radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, n, 8 * sizeof(T), st_);
-    IC_HIP(hipMemcpyAsync(order, vals_, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st_));
+    radix_sort(sk::FromValues<T>{static_cast<const T*>(values)}, sort_bufs(), 0,
+               sk::ToOrder<sk::key_t<T>>{reinterpret_cast<uint32_t*>(order)}, n, st_);
   }
 
   void op_philox(int kind, uint64_t sub, uint64_t stream, uint64_t event, int64_t n,
@@ -584,6 +579,11 @@ class Engine final : public EngineBase {
   void axpy(const T* a, const T* b, double alpha, T* y, long long n) {
     fk::k_axpy<T><<<grid_for(n, kThreads), kThreads, 0, st_>>>(a, b, static_cast<T>(alpha), y, n);
     IC_LAUNCHED();
+  }
+
+  // Key and payload buffers and the prefix table of the radix passes.
+  SortBufs<sk::key_t<T>> sort_bufs() const {
+    return SortBufs<sk::key_t<T>>{{keys_, keys2_}, {vals_, vals2_}, shist_};
   }
 
   // ------------------------------------------------------ block orders
@@ -1335,7 +1335,6 @@ class Engine final : public EngineBase {
   bool tape_forces_;
   int wtab_len_;
   long long rom_len_;
-  long long sort_blocks_;
   size_t need_ = 0;
   long long pool_len_ = 0;
   cx<T>* twp_;
@@ -1349,8 +1348,9 @@ class Engine final : public EngineBase {
   T *dbar_, *pbar_, *gbar_, *rhobar_;
   double *part_, *scal_, *lbs_;
   T *hist_S_, *hist_Y_, *dir_, *strial_, *gtrial_;
-  uint64_t *keys_, *keys2_;
-  uint32_t *vals_, *vals2_, *small_, *shist_, *binc_;
+  sk::key_t<T> *keys_, *keys2_;
+  uint32_t *vals_, *vals2_, *shist_, *binc_;
+  uint8_t* bintab_;  // k bins of the Fourier-space matching by |k|^2
   bk::Layout Lm_{}, Ld_{};  // 8^3-cell blocks of the mesh and of the data grid
   unsigned nbm_ = 0, nbd_ = 0, mim_ = 0, mid_ = 0;
   uint32_t *idtape_, *desttape_, *ostart_, *oistart_, *dstart_, *distart_, *dids_;
@@ -1367,15 +1367,14 @@ class Engine final : public EngineBase {
   double* detvmax_ = nullptr;              // its cotangent paint's max |p_bar|
   static_assert(bk::kB == kZHalo, "the z halo spacing is the block side");
   T *tmpd_, *tmpp_, *dsd_, *psd_, *dbar2_, *pbar2_;
-  T *vbuf_, *tbuf_;
+  T* vbuf_;
   uint32_t* dbg_idx_[2];
   T* dbg_key_[2];
   uint32_t* dbg_bin_;
   long long dbg_n_[2] = {-1, -1};
-  // Host staging of the Fourier-space bin counts and starts; members so that
-  // asynchronous copies never outlive their source.
+  // Host staging of the Fourier-space bin counts; a member so that an
+  // asynchronous copy never outlives its target.
   std::vector<uint32_t> bin_count_ = std::vector<uint32_t>(256, 0);
-  std::vector<uint32_t> bin_start_ = std::vector<uint32_t>(128, 0);
   const int32_t* counts_ = nullptr;
   const T* resp_ = nullptr;
   KernelTimer timer_;

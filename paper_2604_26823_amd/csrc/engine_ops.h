@@ -6,66 +6,27 @@
 
 namespace ic {
 
-namespace ek {
-// Count of entries of v below thr -> part[block] (FP64 counts).
-static __global__ __launch_bounds__(fk::kRedThreads) void k_count_below(const uint32_t* __restrict__ v,
-                                                                 uint32_t thr,
-                                                                 double* __restrict__ part,
-                                                                 long long n) {
-  __shared__ double sh[fk::kRedThreads / 64];
-  double c = 0;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    if (v[i] < thr) c += 1.0;
-  c = fk::block_sum(c, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = c;
-}
-
-static __global__ void k_u64_to_u32(const uint64_t* __restrict__ a, uint32_t* __restrict__ b,
-                             long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    b[i] = static_cast<uint32_t>(a[i]);
-}
-
-static __global__ void k_fill_u32(uint32_t* __restrict__ a, uint32_t v, long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    a[i] = v;
-}
-}  // namespace ek
-
 // Real space: the cells with R >= r_min, ranked by the white noise in
 // descending order (ties by cell index), receive the sorted N(0,1) targets.
 template <typename T>
 long long Engine<T>::rom_real(T* s, uint64_t event) {
-  const unsigned G = grid_for(P_, kThreads);
-  const int vbits = 8 * sizeof(T);
-  rk::k_real_keys<T><<<G, kThreads, 0, st_>>>(s, resp_, static_cast<T>(prob_.r_min), keys_,
-                                              vals_, small_, P_);
-  IC_LAUNCHED();
-  radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, P_, vbits, st_);
-  sk::k_gather_u32_key<<<G, kThreads, 0, st_>>>(small_, vals_, keys_, P_);
-  IC_LAUNCHED();
-  radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, P_, 4, st_);
-  const unsigned g = grid_for(P_, fk::kRedThreads, kRedBlocks);
-  ek::k_count_below<<<g, fk::kRedThreads, 0, st_>>>(small_, 1u, part_, P_);
-  IC_LAUNCHED();
-  double cnt = 0;
-  reduce_parts(g, 1, &cnt);
-  const long long n = (long long)cnt;
+  using K = sk::key_t<T>;
+  const SortBufs<K> b = sort_bufs();
+  // the matched set, compacted in index order, with its size
+  radix_pass(sk::FromValues<T>{s}, rk::InSet<T>{resp_, static_cast<T>(prob_.r_min)},
+             sk::ToPairs<K>{b.k[0], b.v[0]}, P_, shist_, binc_, st_);
+  uint32_t cnt = 0;
+  IC_HIP(hipMemcpyAsync(&cnt, binc_, sizeof(uint32_t), hipMemcpyDeviceToHost, st_));
+  IC_HIP(hipStreamSynchronize(st_));
+  const long long n = cnt;
   dbg_n_[0] = n;
   if (n == 0) return 0;
-  IC_HIP(hipMemcpyAsync(dbg_idx_[0], vals_, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st_));
-  rk::k_gather<T><<<grid_for(n, kThreads), kThreads, 0, st_>>>(s, dbg_idx_[0], dbg_key_[0], n);
+  radix_sort(sk::FromPairs<K>{b.k[0], b.v[0]}, b, 1, rk::ToRanks<T>{dbg_idx_[0], dbg_key_[0]}, n,
+             st_);
+  rk::k_real_targets<T><<<grid_for(n, kThreads), kThreads, 0, st_>>>(event, prob_.seed, b.k[0],
+                                                                      n);
   IC_LAUNCHED();
-  rk::k_real_targets<T><<<grid_for(n, kThreads), kThreads, 0, st_>>>(event, prob_.seed, tbuf_,
-                                                                      keys_, vals_, n);
-  IC_LAUNCHED();
-  radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, n, vbits, st_);
-  rk::k_scatter_sorted<T><<<grid_for(n, kThreads), kThreads, 0, st_>>>(s, dbg_idx_[0], tbuf_,
-                                                                        vals_, n);
-  IC_LAUNCHED();
+  radix_sort(sk::FromKeys<K>{b.k[0]}, b, 1, rk::ToElements<T>{s, dbg_idx_[0]}, n, st_);
   return n;
 }
 
@@ -89,78 +50,47 @@ long long Engine<T>::rom_fourier(T* s, uint64_t event, int32_t* bins_used, bool 
   const double kf = 2.0 * 3.14159265358979323846 / prob_.box;
   const double kmax = std::sqrt(3.0) * 3.14159265358979323846 * np_ / prob_.box;
   const double dk = (kmax - prob_.rom_kmin) / nbins;
+  using K = sk::key_t<T>;
+  const SortBufs<K> b = sort_bufs();
   const long long E = reim ? 2 * Hq_ : Hq_;  // ranked elements
   const unsigned G = grid_for(Hq_, kThreads);
-  const unsigned GE = grid_for(E, kThreads);
-  const int vbits = 8 * sizeof(T);
-  if (reim)
-    rk::k_part_keys<T><<<G, kThreads, 0, st_>>>(Z, np_, kpp_, static_cast<T>(1.0 / n3h), kf,
-                                                prob_.rom_kmin, dk, nbins, vbuf_, keys_, vals_,
-                                                small_, Hq_);
-  else
-    rk::k_mode_keys<T><<<G, kThreads, 0, st_>>>(Z, np_, kpp_, static_cast<T>(1.0 / n3h), kf,
-                                                prob_.rom_kmin, dk, nbins, vbuf_, keys_, vals_,
-                                                small_, Hq_);
+  rk::k_bin_table<<<blocks_for(wtab_len_, 256), 256, 0, st_>>>(wtab_len_, kf, prob_.rom_kmin, dk,
+                                                               nbins, bintab_);
   IC_LAUNCHED();
-  radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, E, vbits, st_);
-  sk::k_gather_u32_key<<<GE, kThreads, 0, st_>>>(small_, vals_, keys_, E);
+  const rk::Modes modes = rk::make_modes(np_, bintab_);
+  rk::k_mode_keys<T><<<G, kThreads, 0, st_>>>(Z, modes, kpp_, static_cast<T>(1.0 / n3h),
+                                              reim ? 1 : 0, b.k[0], Hq_);
   IC_LAUNCHED();
-  radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, E, 8, st_);
-  ek::k_fill_u32<<<1, 256, 0, st_>>>(binc_, 0u, 256);
-  IC_LAUNCHED();
-  rk::k_bin_ends<<<GE, kThreads, 0, st_>>>(keys_, binc_, E);
+  // by value, then (stably) by bin; the modes outside every bin are dropped
+  radix_sort(sk::FromPairs<K>{b.k[0], nullptr}, b, 1, sk::ToPairs<K>{b.k[0], b.v[0]}, E, st_);
+  radix_pass(sk::FromPairs<K>{b.k[0], b.v[0]}, rk::ByBin{modes, reim ? 1 : 0},
+             rk::ToRanksAndBins<T>{dbg_idx_[1], dbg_key_[1], dbg_bin_}, E, shist_, binc_, st_);
+  rk::k_bin_starts<<<1, sk::kDigits, 0, st_>>>(binc_, binc_ + sk::kDigits);
   IC_LAUNCHED();
   std::vector<uint32_t>& counts = bin_count_;
   IC_HIP(hipMemcpyAsync(counts.data(), binc_, 256 * sizeof(uint32_t), hipMemcpyDeviceToHost, st_));
   IC_HIP(hipStreamSynchronize(st_));
-  // run ends -> counts (bins are sorted ascending; absent bins read 0)
-  for (uint32_t b = 0, prev = 0; b < 255; ++b) {
-    if (counts[b] == 0) continue;
-    const uint32_t e = counts[b];
-    counts[b] = e - prev;
-    prev = e;
-  }
-  std::vector<uint32_t>& start = bin_start_;
-  std::fill(start.begin(), start.end(), 0u);
   long long n = 0;
   int used = 0;
-  for (int b = 0; b < nbins; ++b) {
-    start[b] = static_cast<uint32_t>(n);
-    n += counts[b];
-    used += counts[b] > 0;
+  for (int k = 0; k < nbins; ++k) {
+    n += counts[k];
+    used += counts[k] > 0;
   }
   if (bins_used) *bins_used = used;
   dbg_n_[1] = n;
   if (n > 0) {
-    IC_HIP(hipMemcpyAsync(binc_ + 128, start.data(), 128 * sizeof(uint32_t),
-                          hipMemcpyHostToDevice, st_));
-    IC_HIP(hipMemcpyAsync(dbg_idx_[1], vals_, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st_));
-    const unsigned Gn = grid_for(n, kThreads);
-    ek::k_u64_to_u32<<<Gn, kThreads, 0, st_>>>(keys_, dbg_bin_, n);
-    IC_LAUNCHED();
-    rk::k_gather<T><<<Gn, kThreads, 0, st_>>>(vbuf_, dbg_idx_[1], dbg_key_[1], n);
-    IC_LAUNCHED();
     // Rayleigh draws (stream 3) for amplitudes; N(0, 1/2) draws (stream 5)
     // for the parts
-    rk::k_fourier_targets<T><<<Gn, kThreads, 0, st_>>>(
-        keys_, binc_ + 128, reim ? 0 : 1, reim ? 5 : 3, reim ? std::sqrt(0.5) : 1.0, event,
-        prob_.seed, tbuf_, keys_, vals_, small_, n);
+    rk::k_fourier_targets<T><<<grid_for(n, kThreads), kThreads, 0, st_>>>(
+        binc_ + sk::kDigits, nbins, reim ? 0 : 1, reim ? 5 : 3, reim ? std::sqrt(0.5) : 1.0,
+        event, prob_.seed, b.k[0], b.v[0], n);
     IC_LAUNCHED();
-    radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, n, vbits, st_);
-    sk::k_gather_u32_key<<<Gn, kThreads, 0, st_>>>(small_, vals_, keys_, n);
+    radix_sort(sk::FromPairs<K>{b.k[0], b.v[0]}, b, 1, sk::ToPairs<K>{b.k[0], b.v[0]}, n, st_);
+    radix_pass(sk::FromPairs<K>{b.k[0], b.v[0]}, sk::ValByte{},
+               rk::ToElements<T>{vbuf_, dbg_idx_[1]}, n, shist_, nullptr, st_);
+    rk::k_modes_back<T><<<G, kThreads, 0, st_>>>(Z, modes, kpp_, vbuf_, static_cast<T>(n3h),
+                                                 reim ? 1 : 0, Hq_);
     IC_LAUNCHED();
-    radix_sort_pairs(keys_, vals_, keys2_, vals2_, shist_, n, 8, st_);
-    if (reim) {
-      rk::k_part_scatter<T><<<Gn, kThreads, 0, st_>>>(Z, np_, kpp_, dbg_idx_[1], tbuf_, vals_,
-                                                      static_cast<T>(n3h), n);
-      IC_LAUNCHED();
-      rk::k_part_mirror<T><<<Gn, kThreads, 0, st_>>>(Z, np_, kpp_, dbg_idx_[1], n);
-      IC_LAUNCHED();
-    } else {
-      rk::k_fourier_scatter<T><<<Gn, kThreads, 0, st_>>>(Z, np_, kpp_, dbg_idx_[1], tbuf_,
-                                                         vals_, static_cast<T>(n3h), n);
-      IC_LAUNCHED();
-    }
   }
   fft_x<T>(f, Z, Z, false, static_cast<T>(1.0 / (double)P_));
   fft_y<T>(f, Z, false);

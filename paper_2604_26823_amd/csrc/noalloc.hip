@@ -12,14 +12,18 @@ namespace ic {
 namespace na {
 
 constexpr long long kMaxN = IC_NOALLOC_SORT_MAX;
-constexpr long long kTiles = (kMaxN + sk::kTile - 1) / sk::kTile;
-// keys, keys (ping-pong), indices, indices (ping-pong), histogram, NaN count
+// rows of the radix passes' prefix table (sk::table_len(kMaxN): tiles of 1024 up
+// to kSmallMax elements, of 4096 beyond)
+constexpr long long kRows = sk::kSmallMax / sk::kSmallTile + 1;
+static_assert(kMaxN / 4096 < kRows, "the short tiles need the longest table");
+constexpr size_t kTableLen = (kRows + kRows / sk::kChunkRows + 2) * sk::kDigits;
+// keys, keys (ping-pong), indices, indices (ping-pong), prefix table, NaN count
 constexpr size_t kKeysOff = 0;
 constexpr size_t kKeys2Off = kKeysOff + 8 * kMaxN;
 constexpr size_t kValsOff = kKeys2Off + 8 * kMaxN;
 constexpr size_t kVals2Off = kValsOff + 4 * kMaxN;
 constexpr size_t kHistOff = kVals2Off + 4 * kMaxN;
-constexpr size_t kCountOff = (kHistOff + 4 * sk::kDigits * kTiles + 255) & ~size_t(255);
+constexpr size_t kCountOff = (kHistOff + 4 * kTableLen + 255) & ~size_t(255);
 constexpr size_t kScratchBytes = kCountOff + 256;
 
 // Each device that runs the entry point holds its own copy until the
@@ -64,11 +68,12 @@ __global__ void k_zero_u32(unsigned* __restrict__ x) { *x = 0u; }
 template <typename T>
 void sort_desc(const T* values, long long n, int32_t* order, hipStream_t st) {
   char* base = static_cast<char*>(scratch_address());
-  uint64_t* keys = reinterpret_cast<uint64_t*>(base + kKeysOff);
-  uint64_t* keys2 = reinterpret_cast<uint64_t*>(base + kKeys2Off);
-  uint32_t* vals = reinterpret_cast<uint32_t*>(base + kValsOff);
-  uint32_t* vals2 = reinterpret_cast<uint32_t*>(base + kVals2Off);
-  uint32_t* hist = reinterpret_cast<uint32_t*>(base + kHistOff);
+  using K = sk::key_t<T>;
+  const SortBufs<K> b{{reinterpret_cast<K*>(base + kKeysOff),
+                       reinterpret_cast<K*>(base + kKeys2Off)},
+                      {reinterpret_cast<uint32_t*>(base + kValsOff),
+                       reinterpret_cast<uint32_t*>(base + kVals2Off)},
+                      reinterpret_cast<uint32_t*>(base + kHistOff)};
   unsigned* count = reinterpret_cast<unsigned*>(base + kCountOff);
   k_zero_u32<<<1, 1, 0, st>>>(count);
   IC_LAUNCHED();
@@ -78,10 +83,8 @@ void sort_desc(const T* values, long long n, int32_t* order, hipStream_t st) {
   IC_HIP(hipMemcpyAsync(&nan, count, sizeof(unsigned), hipMemcpyDeviceToHost, st));
   IC_HIP(hipStreamSynchronize(st));
   if (nan) throw ApiError(IC_ERR_NONFINITE, "NaN in sort input");
-  sk::k_desc_keys<T><<<grid_for(n, 256), 256, 0, st>>>(values, keys, vals, n);
-  IC_LAUNCHED();
-  radix_sort_pairs(keys, vals, keys2, vals2, hist, n, 8 * sizeof(T), st);
-  IC_HIP(hipMemcpyAsync(order, vals, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+  radix_sort(sk::FromValues<T>{values}, b, 0,
+             sk::ToOrder<K>{reinterpret_cast<uint32_t*>(order)}, n, st);
 }
 
 }  // namespace na

@@ -1,190 +1,450 @@
-// Stable least-significant-digit radix sort of (uint64 key, uint32 index)
-// pairs, and the key transforms of rank-order matching (gfx950).
+// Stable least-significant-digit radix sort and stable partition passes, and
+// the key transforms of rank-order matching (gfx950).
 //
-// Each pass sorts one 4-bit digit: a per-tile histogram, one exclusive scan
-// of the digit-major histogram table, and a scatter in which every thread
-// places a contiguous run of keys in input order, so equal digits keep their
-// order across threads and tiles (stability is what makes ties rank by index).
+// A pass orders n elements (a key of the value's own width, optionally a
+// 32-bit payload) by one 8-bit digit.  Tiles of THREADS x ITEMS elements:
+//   k_hist     counts the digits of each tile (one row of 256 per tile);
+//   k_chunks   turns the rows of up to kChunkRows tiles into exclusive
+//              prefixes and leaves the chunk's totals;
+//   k_top      (many chunks only) the exclusive prefixes of the chunks, with
+//              every digit's first position;
+//   k_scatter  ranks the tile's elements, orders them in LDS and writes them
+//              out in runs of one digit.
+// Where elements come from, which digit counts and where they go are functors,
+// so the first pass reads the values themselves, the last writes what the
+// caller wants (indices, values, a scatter through them) and a partition or a
+// sort by k bin is one more pass.
+//
+// Bound by HBM traffic and by how long the runs of a digit are in the output:
+// 8-bit digits halve the passes of 4-bit ones (20 bytes per element and pass
+// for a 32-bit key with its index); a tile of 8192 makes the average run 32
+// elements, 128 bytes.  Ranks come from ballots, one 64-lane group of equal
+// digits at a time, in input order, so equal digits keep their order
+// (stability makes ties rank by index) without a serial run per thread: the
+// earlier 4-bit passes over 64-bit keys, 16 consecutive elements per thread,
+// took 205 us per pass at 2^24 elements (scatter 125, one-workgroup scan 60,
+// histogram 19), 8 passes per FP32 sort.  A matching event at 256^3 in FP32
+// went from 9.71 to 1.82 ms with these passes, a sort of 300007 values from
+// 252 to 103 us.
 #pragma once
+
+#include <algorithm>
 
 #include "common.h"
 
 namespace ic {
 namespace sk {
 
-constexpr int kThreads = 256;
-constexpr int kItems = 16;
-constexpr int kTile = kThreads * kItems;
-constexpr int kDigits = 16;
+constexpr int kDigits = 256;
+constexpr int kChunkRows = 32;  // tiles per chunk of the prefix table
+// Chunks up to which k_scatter adds the chunk totals itself instead of
+// reading k_top's prefixes: one 3 us launch against one row load per chunk.
+constexpr int kInlineChunks = 16;
+
+// Tile shapes: elements up to kSmallMax take tiles of 1024, which spread a
+// short sort over the chip, longer ones tiles of 8192 (4096 for 64-bit keys,
+// whose tile would not leave room for two workgroups in a CU's LDS).
+constexpr long long kSmallMax = 1ll << 20;
+constexpr int kSmallTile = 256 * 4;
+template <typename K> constexpr int big_threads() { return sizeof(K) == 4 ? 512 : 256; }
+template <typename K> constexpr int big_tile() { return big_threads<K>() * 16; }
+
+inline long long tiles_for(long long n, long long tile) { return (n + tile - 1) / tile; }
+// Entries of the prefix table that passes over at most n elements need: the
+// tile rows and the chunk rows, and one row of totals.
+inline size_t table_len(long long n) {
+  const long long rows =
+      std::max(tiles_for(n, 4096), tiles_for(std::min(n, kSmallMax), kSmallTile)) + 1;
+  return static_cast<size_t>(rows + rows / kChunkRows + 2) * kDigits;
+}
+
+// Unsigned integer of a value's width.
+template <typename T> struct KeyOf;
+template <> struct KeyOf<float> { using type = uint32_t; };
+template <> struct KeyOf<double> { using type = uint64_t; };
+template <typename T> using key_t = typename KeyOf<T>::type;
 
 // Order-preserving unsigned image of a float or double with -0 mapped to +0
 // and larger values giving larger images.
-__device__ __forceinline__ uint64_t ordered_bits(float v) {
+__device__ __forceinline__ uint32_t ordered_bits(float v) {
   uint32_t b = __float_as_uint(v);
   if (b == 0x80000000u) b = 0;
-  b = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-  return b;
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 __device__ __forceinline__ uint64_t ordered_bits(double v) {
   uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
   if (b == 0x8000000000000000ull) b = 0;
-  b = (b & 0x8000000000000000ull) ? ~b : (b | 0x8000000000000000ull);
-  return b;
+  return (b & 0x8000000000000000ull) ? ~b : (b | 0x8000000000000000ull);
 }
 template <typename T>
-__device__ __forceinline__ uint64_t descending_key(T v) {
-  constexpr uint64_t mask = sizeof(T) == 4 ? 0xFFFFFFFFull : ~0ull;
-  return (~ordered_bits(v)) & mask;
+__device__ __forceinline__ key_t<T> descending_key(T v) {
+  return ~ordered_bits(v);
+}
+// The value of a descending key (-0 comes back as +0).
+__device__ __forceinline__ float key_value(uint32_t key) {
+  const uint32_t b = ~key;
+  return __uint_as_float((b & 0x80000000u) ? (b ^ 0x80000000u) : ~b);
+}
+__device__ __forceinline__ double key_value(uint64_t key) {
+  const uint64_t b = ~key;
+  return __longlong_as_double(
+      static_cast<long long>((b & 0x8000000000000000ull) ? (b ^ 0x8000000000000000ull) : ~b));
 }
 
-static __global__ __launch_bounds__(kThreads) void k_hist(const uint64_t* __restrict__ keys,
-                                                   long long n, int shift,
-                                                   uint32_t* __restrict__ hist, int nblocks) {
+// ------------------------------------------------------------------ sources
+// key(i) and val(i) of input element i < n.
+template <typename T>
+struct FromValues {  // the values themselves, their indices as payload
+  using K = key_t<T>;
+  static constexpr bool kVals = true;
+  const T* x;
+  __device__ __forceinline__ K key(long long i) const { return descending_key<T>(x[i]); }
+  __device__ __forceinline__ uint32_t val(long long i) const { return static_cast<uint32_t>(i); }
+};
+template <typename KK>
+struct FromPairs {
+  using K = KK;
+  static constexpr bool kVals = true;
+  const K* k;
+  const uint32_t* v;  // null: the index
+  __device__ __forceinline__ K key(long long i) const { return k[i]; }
+  __device__ __forceinline__ uint32_t val(long long i) const {
+    return v ? v[i] : static_cast<uint32_t>(i);
+  }
+};
+template <typename KK>
+struct FromKeys {  // keys without a payload
+  using K = KK;
+  static constexpr bool kVals = false;
+  const K* k;
+  __device__ __forceinline__ K key(long long i) const { return k[i]; }
+  __device__ __forceinline__ uint32_t val(long long) const { return 0u; }
+};
+
+// ------------------------------------------------------------------- digits
+// Digit (< 256) of an element.  Elements of digit kDrop are counted, not written.
+struct KeyByte {
+  static constexpr int kDrop = 256;
+  int shift;
+  template <typename K>
+  __device__ __forceinline__ unsigned operator()(K k, uint32_t) const {
+    return static_cast<unsigned>(k >> shift) & 255u;
+  }
+};
+struct ValByte {  // the payload itself
+  static constexpr int kDrop = 256;
+  template <typename K>
+  __device__ __forceinline__ unsigned operator()(K, uint32_t v) const {
+    return v & 255u;
+  }
+};
+
+// --------------------------------------------------------------------- sinks
+// put(position, key, payload, digit).
+template <typename K>
+struct ToPairs {
+  K* k;
+  uint32_t* v;
+  __device__ __forceinline__ void operator()(long long p, K key, uint32_t val, unsigned) const {
+    k[p] = key;
+    v[p] = val;
+  }
+};
+template <typename K>
+struct ToKeys {
+  K* k;
+  __device__ __forceinline__ void operator()(long long p, K key, uint32_t, unsigned) const {
+    k[p] = key;
+  }
+};
+template <typename K>
+struct ToOrder {
+  uint32_t* v;
+  __device__ __forceinline__ void operator()(long long p, K, uint32_t val, unsigned) const {
+    v[p] = val;
+  }
+};
+
+// ------------------------------------------------------------------- kernels
+// table[tile][d] = elements of digit d in the tile.
+template <class Src, class Dig, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_hist(Src src, Dig dig, long long n,
+                                                  uint32_t* __restrict__ table) {
   __shared__ uint32_t cnt[kDigits];
-  if (threadIdx.x < kDigits) cnt[threadIdx.x] = 0;
+  for (int d = threadIdx.x; d < kDigits; d += THREADS) cnt[d] = 0;
   __syncthreads();
-  const long long base = (long long)blockIdx.x * kTile;
-  for (int i = threadIdx.x; i < kTile; i += kThreads) {
-    const long long g = base + i;
-    if (g < n) atomicAdd(&cnt[(keys[g] >> shift) & (kDigits - 1)], 1u);
+  const long long base = (long long)blockIdx.x * THREADS * ITEMS;
+  unsigned dg[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const long long g = base + i * THREADS + threadIdx.x;
+    const long long c = g < n ? g : n - 1;
+    dg[i] = dig(src.key(c), src.val(c));
   }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (base + i * THREADS + threadIdx.x < n) atomicAdd(&cnt[dg[i]], 1u);
   __syncthreads();
-  if (threadIdx.x < kDigits) hist[(long long)threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];
+  for (int d = threadIdx.x; d < kDigits; d += THREADS)
+    table[(long long)blockIdx.x * kDigits + d] = cnt[d];
 }
 
-// Exclusive scan of n values in place, one block of 1024 threads.
-static __global__ __launch_bounds__(1024) void k_scan_excl(uint32_t* __restrict__ v, long long n) {
-  __shared__ uint32_t part[1024];
-  const long long per = (n + blockDim.x - 1) / blockDim.x;
-  const long long lo = threadIdx.x * per;
-  const long long hi = lo + per < n ? lo + per : n;
-  uint32_t s = 0;
-  for (long long i = lo; i < hi; ++i) s += v[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    uint32_t t = threadIdx.x >= off ? part[threadIdx.x - off] : 0;
-    __syncthreads();
-    part[threadIdx.x] += t;
-    __syncthreads();
+// One workgroup per kChunkRows tile rows: exclusive prefixes over them in
+// place, the chunk's totals into chunks[chunk][d].
+static __global__ __launch_bounds__(kDigits) void k_chunks(uint32_t* __restrict__ table,
+                                                           int ntiles,
+                                                           uint32_t* __restrict__ chunks) {
+  const int d = threadIdx.x;
+  const int lo = blockIdx.x * kChunkRows;
+  uint32_t v[kChunkRows];
+#pragma unroll
+  for (int t = 0; t < kChunkRows; ++t)
+    v[t] = table[(long long)min(lo + t, ntiles - 1) * kDigits + d];
+  uint32_t run = 0;
+#pragma unroll
+  for (int t = 0; t < kChunkRows; ++t) {
+    if (lo + t >= ntiles) break;
+    table[(long long)(lo + t) * kDigits + d] = run;
+    run += v[t];
   }
-  uint32_t run = part[threadIdx.x] - s;
-  for (long long i = lo; i < hi; ++i) {
-    const uint32_t x = v[i];
-    v[i] = run;
-    run += x;
+  chunks[(long long)blockIdx.x * kDigits + d] = run;
+}
+
+// Exclusive scan over the 256 digits of the value of thread d < 256 (all
+// threads of the workgroup call it); wsum: four words of LDS.
+__device__ __forceinline__ uint32_t scan_digits(uint32_t v, uint32_t* wsum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t s = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_up(s, off, 64);
+    if (lane >= off) s += o;
+  }
+  if (w < kDigits / 64 && lane == 63) wsum[w] = s;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int q = 0; q < kDigits / 64; ++q) before += q < w ? wsum[q] : 0u;
+  return before + s - v;
+}
+
+// One workgroup: totals[d] = all elements of digit d and, with prefix, the
+// chunk rows in place to the first output position of the chunk's digit d.
+static __global__ __launch_bounds__(1024) void k_top(uint32_t* __restrict__ chunks, int nchunks,
+                                                     uint32_t* __restrict__ totals,
+                                                     bool prefix) {
+  __shared__ uint32_t part[4][kDigits];
+  __shared__ uint32_t wsum[kDigits / 64];
+  const int d = threadIdx.x & (kDigits - 1), q = threadIdx.x >> 8;
+  const int per = (nchunks + 3) / 4, lo = q * per, hi = min(lo + per, nchunks);
+  uint32_t s = 0;
+#pragma unroll 8
+  for (int c = lo; c < hi; ++c) s += chunks[(long long)c * kDigits + d];
+  part[q][d] = s;
+  __syncthreads();
+  uint32_t before = 0, tot = 0;
+  for (int j = 0; j < 4; ++j) {
+    before += j < q ? part[j][d] : 0u;
+    tot += part[j][d];
+  }
+  const uint32_t first = scan_digits(q == 0 ? tot : 0u, wsum);
+  if (q == 0) totals[d] = tot;
+  if (!prefix) return;
+  __syncthreads();
+  if (q == 0) part[0][d] = first;
+  __syncthreads();
+  uint32_t run = part[0][d] + before;
+#pragma unroll 8
+  for (int c = lo; c < hi; ++c) {
+    const uint32_t v = chunks[(long long)c * kDigits + d];
+    chunks[(long long)c * kDigits + d] = run;
+    run += v;
   }
 }
 
-static __global__ __launch_bounds__(kThreads) void k_scatter(
-    const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-    uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, long long n, int shift,
-    const uint32_t* __restrict__ hist, int nblocks) {
-  __shared__ uint64_t sk[kTile];
-  __shared__ uint32_t sv[kTile];
-  __shared__ uint32_t pre[kDigits * kThreads];
-  __shared__ uint32_t wsum[kThreads];
+// Lanes of the wavefront that are active and hold digit d.
+__device__ __forceinline__ unsigned long long same_digit(unsigned d, bool active) {
+  unsigned long long m = __ballot(active);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const bool bit = (d >> b) & 1u;
+    const unsigned long long v = __ballot(bit);
+    m &= bit ? v : ~v;
+  }
+  return m;
+}
+
+// nchunks = 0: a single tile (no table); > kInlineChunks: chunks holds k_top's prefixes.
+template <class Src, class Dig, class Out, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_scatter(Src src, Dig dig, Out out, long long n,
+                                                     const uint32_t* __restrict__ table,
+                                                     const uint32_t* __restrict__ chunks,
+                                                     int nchunks) {
+  using K = typename Src::K;
+  constexpr int kTile = THREADS * ITEMS;
+  constexpr int kWaves = THREADS / 64;
+  __shared__ K sk[kTile];
+  __shared__ uint32_t sv[Src::kVals ? kTile : 1];
+  __shared__ volatile uint32_t wh[kWaves][kDigits];
+  __shared__ uint32_t gofs[kDigits];
+  __shared__ uint32_t wsum[kDigits / 64], wsum2[kDigits / 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const long long base = (long long)blockIdx.x * kTile;
-  for (int i = threadIdx.x; i < kTile; i += kThreads) {
-    const long long g = base + i;
-    sk[i] = g < n ? kin[g] : 0;
-    sv[i] = g < n ? vin[g] : 0;
+  // wavefront w takes ITEMS consecutive rows of 64 elements
+  const long long first = base + (long long)w * (64 * ITEMS) + lane;
+  K k[ITEMS];
+  uint32_t v[Src::kVals ? ITEMS : 1];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const long long g = first + i * 64;
+    const long long c = g < n ? g : n - 1;
+    k[i] = src.key(c);
+    if constexpr (Src::kVals) v[i] = src.val(c);
+  }
+  // this tile's rows of the table: first output position of each digit
+  uint32_t pre = 0, tot = 0;
+  if (nchunks > 0 && t < kDigits) {
+    const int mine = blockIdx.x / kChunkRows;
+    if (nchunks > kInlineChunks) {
+      pre = chunks[(long long)mine * kDigits + t];
+    } else {
+      for (int c = 0; c < nchunks; ++c) {
+        const uint32_t x = chunks[c * kDigits + t];
+        tot += x;
+        pre += c < mine ? x : 0u;
+      }
+    }
+    pre += table[(long long)blockIdx.x * kDigits + t];
+  }
+  for (int d = t; d < kWaves * kDigits; d += THREADS) wh[d / kDigits][d % kDigits] = 0;
+  __syncthreads();
+  unsigned r[ITEMS];  // digit << 16 | rank within the wavefront's elements of it
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const bool ok = first + i * 64 < n;
+    const unsigned d = dig(k[i], Src::kVals ? v[Src::kVals ? i : 0] : 0u);
+    const unsigned long long m = same_digit(d, ok);
+    const unsigned before = __builtin_amdgcn_mbcnt_hi(
+        static_cast<unsigned>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0u));
+    const unsigned have = wh[w][d];
+    __builtin_amdgcn_wave_barrier();
+    if (ok && before == 0) wh[w][d] = have + static_cast<unsigned>(__popcll(m));
+    __builtin_amdgcn_wave_barrier();
+    r[i] = d << 16 | (have + before);
   }
   __syncthreads();
-  const int t = threadIdx.x;
-  uint32_t cnt[kDigits];
-#pragma unroll
-  for (int d = 0; d < kDigits; ++d) cnt[d] = 0;
-  for (int i = 0; i < kItems; ++i) {
-    const long long g = base + t * kItems + i;
-    if (g < n) cnt[(sk[t * kItems + i] >> shift) & (kDigits - 1)]++;
-  }
-#pragma unroll
-  for (int d = 0; d < kDigits; ++d) pre[d * kThreads + t] = cnt[d];
-  __syncthreads();
-  // exclusive scan over the digit-major table: thread t owns 16 consecutive entries
-  uint32_t own[kDigits];
-  uint32_t s = 0;
-#pragma unroll
-  for (int j = 0; j < kDigits; ++j) {
-    own[j] = pre[t * kDigits + j];
-    s += own[j];
-  }
-  wsum[t] = s;
-  __syncthreads();
-  for (int off = 1; off < kThreads; off <<= 1) {
-    uint32_t x = t >= off ? wsum[t - off] : 0;
-    __syncthreads();
-    wsum[t] += x;
-    __syncthreads();
-  }
-  uint32_t run = wsum[t] - s;
-#pragma unroll
-  for (int j = 0; j < kDigits; ++j) {
-    pre[t * kDigits + j] = run;
-    run += own[j];
-  }
-  __syncthreads();
-  uint32_t pos[kDigits];
-#pragma unroll
-  for (int d = 0; d < kDigits; ++d)
-    pos[d] = hist[(long long)d * nblocks + blockIdx.x] + pre[d * kThreads + t] - pre[d * kThreads];
-  for (int i = 0; i < kItems; ++i) {
-    const long long g = base + t * kItems + i;
-    if (g < n) {
-      const uint64_t k = sk[t * kItems + i];
-      const int d = (k >> shift) & (kDigits - 1);
-      kout[pos[d]] = k;
-      vout[pos[d]] = sv[t * kItems + i];
-      pos[d]++;
+  // exclusive prefixes: over the wavefronts, then over the digits
+  uint32_t count = 0;
+  if (t < kDigits) {
+    for (int q = 0; q < kWaves; ++q) {
+      const uint32_t x = wh[q][t];
+      wh[q][t] = count;
+      count += x;
     }
   }
-}
-
-template <typename T>
-__global__ void k_desc_keys(const T* __restrict__ x, uint64_t* __restrict__ keys,
-                            uint32_t* __restrict__ vals, long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    keys[i] = descending_key<T>(x[i]);
-    vals[i] = static_cast<uint32_t>(i);
+  const uint32_t local = scan_digits(count, wsum);
+  if (nchunks == 0)
+    pre = local;
+  else if (nchunks <= kInlineChunks)
+    pre += scan_digits(tot, wsum2);
+  if (t < kDigits) {
+    gofs[t] = pre - local;  // output position minus position in the tile
+    for (int q = 0; q < kWaves; ++q) wh[q][t] += local;
   }
-}
-
-// keys[i] = small[vals[i]] (second-level key gathered through the order).
-static __global__ void k_gather_u32_key(const uint32_t* __restrict__ small,
-                                 const uint32_t* __restrict__ vals, uint64_t* __restrict__ keys,
-                                 long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    keys[i] = small[vals[i]];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    if (first + i * 64 >= n) continue;
+    const unsigned p = wh[w][r[i] >> 16] + (r[i] & 0xFFFFu);
+    sk[p] = k[i];
+    if constexpr (Src::kVals) sv[p] = v[i];
+  }
+  __syncthreads();
+  const int have = n - base < kTile ? static_cast<int>(n - base) : kTile;
+#pragma unroll 4
+  for (int j = t; j < have; j += THREADS) {
+    const K key = sk[j];
+    const uint32_t val = Src::kVals ? sv[Src::kVals ? j : 0] : 0u;
+    const unsigned d = dig(key, val);
+    if (d == static_cast<unsigned>(Dig::kDrop)) continue;
+    out(static_cast<long long>(gofs[d] + static_cast<uint32_t>(j)), key, val, d);
+  }
 }
 
 }  // namespace sk
 
-// Sorts (keys, vals) ascending on the low nbits of keys, stably; the result
-// ends in keys/vals (ka/va are scratch of the same size).  hist needs
-// 16 * ceil(n / 4096) entries.
-inline void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* ka, uint32_t* va,
-                             uint32_t* hist, long long n, int nbits, hipStream_t st) {
-  if (n <= 1) return;
-  const int nblocks = static_cast<int>((n + sk::kTile - 1) / sk::kTile);
-  uint64_t *kin = keys, *kout = ka;
-  uint32_t *vin = vals, *vout = va;
-  for (int shift = 0; shift < nbits; shift += 4) {
-    sk::k_hist<<<nblocks, sk::kThreads, 0, st>>>(kin, n, shift, hist, nblocks);
+// One stable pass over n elements by dig: out receives them in digit order.
+// table: sk::table_len(n) entries.  totals (nullable, 256 device words):
+// elements of each digit.
+template <int THREADS, int ITEMS, class Src, class Dig, class Out>
+void radix_pass_tiled(const Src& src, const Dig& dig, const Out& out, long long n,
+                      uint32_t* table, uint32_t* totals, hipStream_t st) {
+  constexpr int kTile = THREADS * ITEMS;
+  const int ntiles = static_cast<int>(sk::tiles_for(n, kTile));
+  int nchunks = 0;
+  uint32_t* chunks = table + (size_t)ntiles * sk::kDigits;
+  if (ntiles > 1 || totals) {
+    sk::k_hist<Src, Dig, THREADS, ITEMS><<<ntiles, THREADS, 0, st>>>(src, dig, n, table);
     IC_LAUNCHED();
-    sk::k_scan_excl<<<1, 1024, 0, st>>>(hist, (long long)sk::kDigits * nblocks);
+    nchunks = (ntiles + sk::kChunkRows - 1) / sk::kChunkRows;
+    sk::k_chunks<<<nchunks, sk::kDigits, 0, st>>>(table, ntiles, chunks);
     IC_LAUNCHED();
-    sk::k_scatter<<<nblocks, sk::kThreads, 0, st>>>(kin, vin, kout, vout, n, shift, hist,
-                                                   nblocks);
-    IC_LAUNCHED();
-    std::swap(kin, kout);
-    std::swap(vin, vout);
+    if (totals || nchunks > sk::kInlineChunks) {
+      sk::k_top<<<1, 1024, 0, st>>>(chunks, nchunks,
+                                    totals ? totals : chunks + (size_t)nchunks * sk::kDigits,
+                                    nchunks > sk::kInlineChunks);
+      IC_LAUNCHED();
+    }
   }
-  if (kin != keys) {
-    IC_HIP(hipMemcpyAsync(keys, kin, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
-    IC_HIP(hipMemcpyAsync(vals, vin, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+  sk::k_scatter<Src, Dig, Out, THREADS, ITEMS>
+      <<<ntiles, THREADS, 0, st>>>(src, dig, out, n, table, chunks, nchunks);
+  IC_LAUNCHED();
+}
+template <class Src, class Dig, class Out>
+void radix_pass(const Src& src, const Dig& dig, const Out& out, long long n, uint32_t* table,
+                uint32_t* totals, hipStream_t st) {
+  using K = typename Src::K;
+  if (n <= sk::kSmallMax)
+    radix_pass_tiled<256, 4>(src, dig, out, n, table, totals, st);
+  else
+    radix_pass_tiled<sk::big_threads<K>(), 16>(src, dig, out, n, table, totals, st);
+}
+
+// Two buffers of n keys and payloads (payloads null where not used).
+template <typename K>
+struct SortBufs {
+  K* k[2];
+  uint32_t* v[2];
+  uint32_t* table;
+};
+
+// Sorts n elements ascending by their keys, stably: the first pass reads src,
+// the passes between go through b, starting with b[first], the last feeds out.
+template <class Src, class Out>
+void radix_sort(const Src& src, const SortBufs<typename Src::K>& b, int first, const Out& out,
+                long long n, hipStream_t st) {
+  using K = typename Src::K;
+  if (n <= 0) return;
+  constexpr int kPasses = sizeof(K);
+  int to = first;
+  if constexpr (Src::kVals) {
+    radix_pass(src, sk::KeyByte{0}, sk::ToPairs<K>{b.k[to], b.v[to]}, n, b.table, nullptr, st);
+    for (int p = 1; p < kPasses; ++p, to ^= 1) {
+      const sk::FromPairs<K> in{b.k[to], b.v[to]};
+      if (p + 1 < kPasses)
+        radix_pass(in, sk::KeyByte{8 * p}, sk::ToPairs<K>{b.k[to ^ 1], b.v[to ^ 1]}, n, b.table,
+                   nullptr, st);
+      else
+        radix_pass(in, sk::KeyByte{8 * p}, out, n, b.table, nullptr, st);
+    }
+  } else {
+    radix_pass(src, sk::KeyByte{0}, sk::ToKeys<K>{b.k[to]}, n, b.table, nullptr, st);
+    for (int p = 1; p < kPasses; ++p, to ^= 1) {
+      const sk::FromKeys<K> in{b.k[to]};
+      if (p + 1 < kPasses)
+        radix_pass(in, sk::KeyByte{8 * p}, sk::ToKeys<K>{b.k[to ^ 1]}, n, b.table, nullptr, st);
+      else
+        radix_pass(in, sk::KeyByte{8 * p}, out, n, b.table, nullptr, st);
+    }
   }
 }
 
