@@ -56,13 +56,27 @@ constexpr int kThreads = 256;
 constexpr int kPer = 4;                // particles per thread
 constexpr int kChunk = kThreads * kPer;  // particles per work item
 
-// Blocks of one grid of side 2^lm (lm >= 3).
+// Blocks of one grid of side 2^lm (lm >= 3), and how its fields lie in memory:
+// [x][y][z], or in slabs [z / 8][x][y][z mod 8].  The force mesh is in
+// slabs (its fields pass between the paints, the FFT's z passes and the
+// readouts only): a block's window is then nine runs of 72 cells and one of
+// nine cells 32 bytes apart per x, where [x][y][z] makes it 81 rows of nine
+// cells, each in a 128-byte line of its own, and the rows of a window lie
+// 64 n bytes apart instead of 4 n^2 (FP32).  Loading those rows cost 120 us of the 345 us step and
+// 150 us of the 389 us force adjoint at 256^3 in FP32, several times what the
+// bytes take.
 struct Layout {
-  int lm;   // log2 of the grid side
-  int lnb;  // log2 of the blocks per side
+  int lm;     // log2 of the grid side
+  int lnb;    // log2 of the blocks per side
+  int slabs;  // 1: fields in slabs
 };
 
-inline Layout layout_for(int lm) { return Layout{lm, lm - kLB}; }
+inline Layout layout_for(int lm, bool slabs) { return Layout{lm, lm - kLB, slabs ? 1 : 0}; }
+// Index of cell (x, y, z).
+__device__ __forceinline__ unsigned cell_at(unsigned x, unsigned y, unsigned z, const Layout& L) {
+  return L.slabs ? ((((z >> kLB) << L.lm | x) << L.lm | y) << kLB) | (z & (kB - 1))
+                 : (x << L.lm | y) << L.lm | z;
+}
 inline unsigned block_count(const Layout& L) { return 1u << (3 * L.lnb); }
 // Upper bound of the work items of P particles: each non-empty block gives
 // ceil(count / kChunk) <= count / kChunk + 1 items.
@@ -112,9 +126,8 @@ __device__ __forceinline__ unsigned win_cell(const int o[3], int k, const Layout
   const unsigned mask = (1u << L.lm) - 1;
   const int kx = k / (kW * kW), r = k - kx * kW * kW;
   const int ky = r / kW, kz = r - ky * kW;
-  return ((static_cast<unsigned>(o[0] + kx) & mask) << (2 * L.lm)) |
-         ((static_cast<unsigned>(o[1] + ky) & mask) << L.lm) |
-         (static_cast<unsigned>(o[2] + kz) & mask);
+  return cell_at(static_cast<unsigned>(o[0] + kx) & mask, static_cast<unsigned>(o[1] + ky) & mask,
+                 static_cast<unsigned>(o[2] + kz) & mask, L);
 }
 
 // Lanes of the wavefront grouped by key with ballots: each active lane gets
@@ -163,10 +176,16 @@ __device__ __forceinline__ unsigned rank_in_block(unsigned key, bool active,
 
 // Ranks aggregated over a workgroup whose particles all start in block b0:
 // after a drift nearly every particle is in b0 or one of its 26 neighbours,
-// so the wavefront groups reserve offsets on 27 LDS counters, one thread per
+// so particles reserve offsets on 27 LDS counters, and one thread per
 // non-empty counter then reserves the workgroup's range in that block's
-// global count with one atomic, and each particle's rank is that base plus
-// its offset.  Keys farther away keep the per-wavefront global atomic.
+// global count with one atomic and leaves its first rank in the work item's
+// row of a table (kNbrRow entries).  A particle keeps its neighbour slot and
+// its offset within the workgroup, packed in one word (key and rank took
+// two); the sort that follows adds the table's entry, so nothing in the
+// counting kernel waits for the global atomics.  Keys farther away take a
+// global atomic each and keep their key in an array of their own.
+constexpr int kNbrRow = 32;   // table entries per work item
+constexpr int kRankBits = 27;  // packed word: slot << kRankBits | rank (P <= 2^27)
 constexpr int kNbr = 27;
 
 // Neighbour slot (0..26) of block key relative to block b0, or kNbr if the
@@ -200,31 +219,47 @@ __device__ __forceinline__ unsigned neighbour_key(unsigned b0, int s, const Layo
   return key;
 }
 
-// First half: each wavefront group's leader reserves the group's offsets,
-// on the workgroup counter wcnt[slot] for neighbour keys, else on the global
-// count; all of a thread's reservations can be in flight at once.
+// First half.  Most particles of a wavefront stay in block b0 (a drift moves
+// them by a fraction of the block's eight cells): their lanes take offsets
+// from one ballot and one reservation by the first of them.  Every other lane
+// reserves for itself, all lanes in the same instruction, on the workgroup
+// counter of its neighbour slot or, farther away, on the global count.  All
+// of a thread's reservations can be in flight at once.
+constexpr int kStay = kNbr / 2;  // slot of b0 itself
 __device__ __forceinline__ RankTicket rank_issue_wg(unsigned key, int slot, bool active,
                                                     unsigned* __restrict__ count,
                                                     unsigned* wcnt) {
-  unsigned size;
-  RankTicket t = group_by_key(key, active, size);
-  if (size) t.base = slot < kNbr ? atomicAdd(wcnt + slot, size) : atomicAdd(count + key, size);
+  const int lane = static_cast<int>(threadIdx.x & 63);
+  const unsigned long long stay = __ballot(active && slot == kStay);
+  RankTicket t{0u, lane, 0u};
+  unsigned size = 1u;
+  bool reserve = active;
+  if (slot == kStay) {
+    t.leader = stay ? __ffsll(static_cast<long long>(stay)) - 1 : lane;
+    t.off = __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(stay >> 32),
+                                      __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(stay), 0u));
+    size = static_cast<unsigned>(__popcll(stay));
+    reserve = active && lane == t.leader;
+  }
+  if (reserve) {
+    if (slot < kNbr)
+      t.base = atomicAdd(wcnt + slot, size);
+    else
+      t.base = atomicAdd(count + key, size);
+  }
   return t;
 }
 
-// Between the halves (with barriers around it): the workgroup's ranges.
-__device__ __forceinline__ void rank_reserve_wg(unsigned b0, const Layout& L,
-                                                unsigned* __restrict__ count, const unsigned* wcnt,
-                                                unsigned* wbase) {
-  const int t = static_cast<int>(threadIdx.x);
-  if (t < kNbr && wcnt[t]) wbase[t] = atomicAdd(count + neighbour_key(b0, t, L), wcnt[t]);
+__device__ __forceinline__ unsigned rank_of(const RankTicket& t) {
+  return static_cast<unsigned>(__shfl(static_cast<int>(t.base), t.leader, 64)) + t.off;
 }
 
-__device__ __forceinline__ unsigned rank_finish_wg(const RankTicket& t, int slot, bool active,
-                                                   const unsigned* wbase) {
-  unsigned base = static_cast<unsigned>(__shfl(static_cast<int>(t.base), t.leader, 64));
-  if (slot < kNbr) base += wbase[slot];
-  return active ? base + t.off : 0u;
+// Second half, after a barrier: the workgroup's ranges into the item's row.
+__device__ __forceinline__ void rank_reserve_wg(unsigned b0, const Layout& L,
+                                                unsigned* __restrict__ count, const unsigned* wcnt,
+                                                unsigned* __restrict__ row) {
+  const int t = static_cast<int>(threadIdx.x);
+  if (t < kNbr && wcnt[t]) row[t] = atomicAdd(count + neighbour_key(b0, t, L), wcnt[t]);
 }
 
 // ---------------------------------------------------------------- sorting
@@ -352,19 +387,44 @@ static __global__ __launch_bounds__(256) void k_scan_out(const unsigned* __restr
   }
 }
 
-// Work items: item istart[b] + j = (block b, first slot start[b] + j kChunk).
+// One work item: block b, its slots [s0, s1) and its index i (kSingle set when
+// it is the block's only item).  s0 = s1 marks the workgroups past the last.
+constexpr unsigned kSingle = 1u << 31;
+constexpr int kXcds = 8;
+
+// Work items istart[b] + j, slots [start[b] + j kChunk, ...) of every block, in
+// two orders of nwg = item_grid() records, one per workgroup: by_index in
+// index order, by_xcd dealt so that each XCD gets a contiguous range (see
+// item_of).  A workgroup then starts with one 16-byte load; looking up the
+// item count, the item and the block's slots took three dependent ones.
 static __global__ __launch_bounds__(256) void k_fill_items(const unsigned* __restrict__ start,
                                                     const unsigned* __restrict__ istart,
-                                                    unsigned nb, uint2* __restrict__ items) {
-  for (unsigned b = blockIdx.x * 256 + threadIdx.x; b < nb; b += gridDim.x * 256) {
+                                                    unsigned nb, unsigned nwg,
+                                                    uint4* __restrict__ by_index,
+                                                    uint4* __restrict__ by_xcd) {
+  const unsigned n = istart[nb];
+  const unsigned per = (n + kXcds - 1) / kXcds;
+  const unsigned t0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+  for (unsigned b = t0; b < nb; b += step) {
     const unsigned s0 = start[b], s1 = start[b + 1];
     unsigned i = istart[b];
-    for (unsigned s = s0; s < s1; s += kChunk) items[i++] = make_uint2(b, s);
+    const unsigned flag = s1 - s0 <= static_cast<unsigned>(kChunk) ? kSingle : 0u;
+    for (unsigned s = s0; s < s1; s += kChunk, ++i) {
+      const uint4 v = make_uint4(b, s, min(s + kChunk, s1), i | flag);
+      by_index[i] = v;
+      by_xcd[(i % per) * kXcds + i / per] = v;
+    }
+  }
+  for (unsigned w = t0; w < nwg; w += step) {
+    if (w >= n) by_index[w] = make_uint4(0u, 0u, 0u, 0u);
+    if (w / kXcds >= per || (w % kXcds) * per + w / kXcds >= n)
+      by_xcd[w] = make_uint4(0u, 0u, 0u, 0u);
   }
 }
 
 // Moves nf fields (and the ids) of slot a to slot start[key[a]] + rank[a] of
 // the new order; dest[a] receives that slot.  ids_src null means identity.
+// (Keys and ranks of k_keys; the moves between block orders are k_scatter_b.)
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_scatter(
     const unsigned* __restrict__ key, const unsigned* __restrict__ rank,
@@ -421,10 +481,10 @@ __global__ __launch_bounds__(kThreads) void k_to_lattice(const unsigned* __restr
 }
 
 // ------------------------------------------------------------ work items
+// Records of the order's work items (k_fill_items) and its particle ids.
 struct Items {
-  const uint2* items;
-  const unsigned* start;   // nb + 1 entries
-  const unsigned* nitems;  // device pointer to the item total
+  const uint4* by_index;
+  const uint4* by_xcd;
   const unsigned* ids;
 };
 
@@ -435,10 +495,8 @@ struct Items {
 // one contiguous range of neighbouring blocks whose windows share cache
 // lines in that XCD's L2; paints take item w, so neighbouring blocks, whose
 // flushes add into the same halo cells, run on different XCDs and their
-// atomics do not queue behind each other.  The grid must hold at least
-// items + 7 workgroups.
-constexpr int kXcds = 8;
-
+// atomics do not queue behind each other.  The grid must hold item_grid()
+// workgroups, as many as there are records.
 struct Item {
   unsigned b;
   int o[3];
@@ -449,62 +507,164 @@ struct Item {
 
 template <bool CONTIG>
 __device__ __forceinline__ bool item_of(const Items& it, const Layout& L, Item& m) {
-  const unsigned n = *it.nitems;
-  const unsigned w = blockIdx.x;
-  unsigned i = w;
-  if (CONTIG) {
-    const unsigned per = (n + kXcds - 1) / kXcds;
-    i = (w % kXcds) * per + w / kXcds;
-    if (w / kXcds >= per) return false;
-  }
-  if (i >= n) return false;
-  const uint2 v = it.items[i];
+  const uint4 v = (CONTIG ? it.by_xcd : it.by_index)[blockIdx.x];
+  if (v.y == v.z) return false;
   m.b = v.x;
   m.s0 = v.y;
-  const unsigned e = it.start[v.x + 1];
-  m.s1 = (m.s0 + kChunk < e) ? m.s0 + kChunk : e;
-  m.i = i;
-  m.single = e - it.start[v.x] <= static_cast<unsigned>(kChunk);
+  m.s1 = v.z;
+  m.i = v.w & ~kSingle;
+  m.single = (v.w & kSingle) != 0;
   block_origin(m.b, L, m.o);
   return true;
+}
+
+// Block of the grid of layout Ld (side 2^rs times smaller) that holds the
+// item's block's origin: the centre of the neighbour slots.
+__device__ __forceinline__ unsigned block_around(const Item& m, const Layout& Ld, int rs) {
+  return ((static_cast<unsigned>(m.o[0] >> rs) >> kLB) << (2 * Ld.lnb)) |
+         ((static_cast<unsigned>(m.o[1] >> rs) >> kLB) << Ld.lnb) |
+         (static_cast<unsigned>(m.o[2] >> rs) >> kLB);
+}
+
+// f(R) with R = ceil(particles / kThreads) <= kPer as a compile-time constant.
+// A block of the mean density holds two particles per thread, and rounds past
+// its end would still issue their loads, so the kernels load by rounds (step
+// and force adjoint 2 % faster in FP32, 2 and 3 % in FP64).  Only loads: arithmetic compiled once per R could round differently in each, and
+// which particles of a dense block share an item differs from run to run.
+template <class F>
+__device__ __forceinline__ void with_rounds(const Item& m, F&& f) {
+  switch ((m.s1 - m.s0 + kThreads - 1) / kThreads) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    default: f(std::integral_constant<int, kPer>{}); break;
+  }
 }
 
 // Slots a[k] = s0 + threadIdx.x + k kThreads of this thread in the item and
 // whether they hold a particle; slots past the item's end are clamped to its
 // first slot (an item is never empty).  The kernels issue the loads of all
-// kPer particles from these slots in one branch-free run and wait once:
+// R particles from these slots in one branch-free run and wait once:
 // behind a branch per particle, the in-order memory counter made every
 // particle's loads wait for all of the previous particle's.
-__device__ __forceinline__ void item_slots(const Item& m, long long (&a)[kPer],
-                                           bool (&ok)[kPer]) {
+template <int R>
+__device__ __forceinline__ void item_slots(const Item& m, long long (&a)[R], bool (&ok)[R]) {
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
+  for (int k = 0; k < R; ++k) {
     const long long s = static_cast<long long>(m.s0) + threadIdx.x + k * kThreads;
     ok[k] = s < static_cast<long long>(m.s1);
     a[k] = ok[k] ? s : static_cast<long long>(m.s0);
   }
 }
 
-// u[k] = map[a[k]] (particle ids, slot maps).
+// u[k] = map[a[k]] for k < R (particle ids, slot maps).
+template <int R, int N>
 __device__ __forceinline__ void load_u32(const unsigned* __restrict__ map,
-                                         const long long (&a)[kPer], unsigned (&u)[kPer]) {
+                                         const long long (&a)[N], unsigned (&u)[N]) {
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) u[k] = map[a[k]];
+  for (int k = 0; k < R; ++k) u[k] = map[a[k]];
 }
 
-// v[k] = the three fields of f (P apart) at slot s[k].
-template <typename T, typename S>
+// v[k] = the three fields of f (P apart) at slot s[k], k < R.
+template <int R, typename T, typename S, int N>
 __device__ __forceinline__ void load3_at(const T* __restrict__ f, long long P,
-                                         const S (&s)[kPer], T (&v)[kPer][3]) {
+                                         const S (&s)[N], T (&v)[N][3]) {
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) pk::load3(f, P, static_cast<long long>(s[k]), v[k]);
+  for (int k = 0; k < R; ++k) pk::load3(f, P, static_cast<long long>(s[k]), v[k]);
 }
 
 // Lagrangian lattice indices of the particle ids.
-__device__ __forceinline__ void lattice_all(const unsigned (&id)[kPer], int lp,
-                                            int (&idx)[kPer][3]) {
+template <int R>
+__device__ __forceinline__ void lattice_all(const unsigned (&id)[R], int lp, int (&idx)[R][3]) {
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) pk::lattice(static_cast<long long>(id[k]), lp, idx[k]);
+  for (int k = 0; k < R; ++k) pk::lattice(static_cast<long long>(id[k]), lp, idx[k]);
+}
+
+// Where the particles of one order go in the next, as a counting kernel over
+// that order's items left it: packed neighbour slots and ranks, the keys of
+// the far ones, the items' rows of first ranks, and the next order's block
+// starts.
+struct Moves {
+  const unsigned* key;
+  const unsigned* rank;
+  const unsigned* nbr_base;
+  const unsigned* start;
+};
+
+// Slots in the next order of the particles of item m: f(a, ok, id, s) with
+// their slots a in this order, their ids and their slots s in the next; Ld is
+// the next order's layout, rs = log2 of this grid's side over that one's;
+// first: kNbr words of LDS.
+template <class F>
+__device__ __forceinline__ void for_moves(const Item& m, const unsigned* __restrict__ ids,
+                                          const Moves& mv, const Layout& Ld, int rs,
+                                          unsigned* first, F&& f) {
+  const unsigned b0 = block_around(m, Ld, rs);
+  if (threadIdx.x < kNbr)
+    first[threadIdx.x] = mv.start[neighbour_key(b0, static_cast<int>(threadIdx.x), Ld)] +
+                         mv.nbr_base[static_cast<size_t>(m.i) * kNbrRow + threadIdx.x];
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    long long a[R];
+    bool ok[R];
+    unsigned w[R], id[R];
+    item_slots(m, a, ok);
+    load_u32<R>(mv.rank, a, w);
+    load_u32<R>(ids, a, id);
+    __syncthreads();
+    unsigned s[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const unsigned slot = w[k] >> kRankBits;
+      s[k] = (slot < kNbr ? first[slot] : mv.start[mv.key[a[k]]]) + (w[k] & ((1u << kRankBits) - 1));
+    }
+    f(a, ok, id, s);
+  });
+}
+
+// Moves nf fields (and the ids) of the order's particles to the next order's
+// slots; dest[a] receives the slot of slot a.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_scatter_b(Items it, Layout L, Layout Ld, int rs,
+                                                        Moves mv, Ptrs<T> src, MPtrs<T> dst,
+                                                        int nf, unsigned* __restrict__ ids_dst,
+                                                        unsigned* __restrict__ dest) {
+  __shared__ unsigned first[kNbr];
+  Item m;
+  if (!item_of<true>(it, L, m)) return;
+  for_moves(m, it.ids, mv, Ld, rs, first, [&](const auto& a, const auto& ok, const auto& id,
+                                              const auto& s) {
+    constexpr int R = sizeof(s) / sizeof(s[0]);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if (!ok[k]) continue;
+      for (int f = 0; f < nf; ++f) dst.p[f][s[k]] = src.p[f][a[k]];
+      ids_dst[s[k]] = id[k];
+      dest[a[k]] = s[k];
+    }
+  });
+}
+
+// The ids alone to the next order's slots, dest[a] = the slot of slot a, and
+// inv[s] = a: the new order's map back to this one, through which the next
+// kernels read the state left in this order.
+static __global__ __launch_bounds__(kThreads) void k_scatter_ids_b(
+    Items it, Layout L, Layout Ld, int rs, Moves mv, unsigned* __restrict__ ids_dst,
+    unsigned* __restrict__ dest, unsigned* __restrict__ inv) {
+  __shared__ unsigned first[kNbr];
+  Item m;
+  if (!item_of<true>(it, L, m)) return;
+  for_moves(m, it.ids, mv, Ld, rs, first, [&](const auto& a, const auto& ok, const auto& id,
+                                              const auto& s) {
+    constexpr int R = sizeof(s) / sizeof(s[0]);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if (!ok[k]) continue;
+      ids_dst[s[k]] = id[k];
+      inv[s[k]] = static_cast<unsigned>(a[k]);
+      dest[a[k]] = s[k];
+    }
+  });
 }
 
 template <typename T>
@@ -517,28 +677,31 @@ __device__ __forceinline__ Stencil<T> wrapped_stencil(const int idx[3], const T 
   return s;
 }
 
-// Loads nf window fields (mesh fields src.p[f]) into lds[f * kWin + k].
+// One cell of a gather window: its fields side by side, so a corner of a
+// stencil is one 16-byte LDS read (two in FP64) instead of one read per field
+// (force adjoint 344 -> 341 us at 256^3 in FP32; the others unchanged).
 template <typename T>
+struct alignas(4 * sizeof(T)) WinCell {
+  T v[4];
+};
+
+// Loads the NF window fields (mesh fields src.p[f]) into lds[k].v[f].
+template <int NF, typename T>
 __device__ __forceinline__ void load_window(const int o[3], const Layout& L, const Ptrs<T>& src,
-                                            int nf, T* lds) {
+                                            WinCell<T>* lds) {
   constexpr int kIt = (kWin + kThreads - 1) / kThreads;
-  T v[kIt][4];
+  WinCell<T> v[kIt];
 #pragma unroll
   for (int j = 0; j < kIt; ++j) {
     const int k = min(static_cast<int>(threadIdx.x) + j * kThreads, kWin - 1);
     const unsigned c = win_cell(o, k, L);
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-      if (f < nf) v[j][f] = src.p[f][c];
+    for (int f = 0; f < 4; ++f) v[j].v[f] = f < NF ? src.p[f][c] : T(0);
   }
 #pragma unroll
   for (int j = 0; j < kIt; ++j) {
     const int k = static_cast<int>(threadIdx.x) + j * kThreads;
-    if (k < kWin) {
-#pragma unroll
-      for (int f = 0; f < 4; ++f)
-        if (f < nf) lds[f * kWin + k] = v[j][f];
-    }
+    if (k < kWin) lds[k] = v[j];
   }
 }
 
@@ -549,8 +712,16 @@ __device__ __forceinline__ void load_window(const int o[3], const Layout& L, con
 // on the order of the atomics).  e is chosen per work item so that nothing
 // overflows: every contribution is at most amax in magnitude (CIC weights
 // are at most 1), a window cell receives at most kChunk of them, and
-// amax 2^e < 2^52, so every partial sum stays below 2^62.  The rounding of
-// a contribution, at most 2^-53 amax, is far below the FP32 result's.
+// amax 2^e < 2^51, so every partial sum stays below 2^61.  The rounding of
+// a contribution, at most 2^-52 amax, is far below the FP32 result's.
+//
+// A contribution w x becomes its integer with one fused multiply-add: x 2^e is
+// taken once per particle (exact), and fma(w, x 2^e, 1.5 2^52) leaves
+// the rounded integer (below 2^51 in magnitude) in the low 52 bits of the
+// result, above a constant whose low word is zero.  gfx950 has no conversion
+// from FP64 to 64-bit integers; the emulated one (a dozen FP64 and integer
+// instructions) for 24 contributions per particle cost the cotangent paint
+// 10 of 257 us at 256^3.
 template <typename T>
 struct WinAcc {
   using Cell = double;
@@ -558,7 +729,9 @@ struct WinAcc {
     double s, inv;
   };
   __device__ static Scale scale_for(double) { return Scale{1.0, 1.0}; }
-  __device__ static void add(Cell* c, double v, const Scale&) { atomicAdd(c, v); }
+  // x ready for add: the contribution w x is added to the cell
+  __device__ static double scaled(double x, const Scale&) { return x; }
+  __device__ static void add(Cell* c, double w, double x) { atomicAdd(c, w * x); }
   __device__ static double get(Cell c, const Scale&) { return c; }
 };
 struct FixAcc {
@@ -566,12 +739,12 @@ struct FixAcc {
   struct Scale {
     double s, inv;
   };
-  // 2^e with amax 2^e < 2^52 (amax < 2^k from frexp, e = 52 - k)
+  // 2^e with amax 2^e < 2^51 (amax < 2^k from frexp, e = 51 - k)
   __device__ static Scale scale_for(double amax) {
     if (!(amax > 0.0)) return Scale{1.0, 1.0};
     int k;
     frexp(amax, &k);
-    return Scale{ldexp(1.0, 52 - k), ldexp(1.0, k - 52)};
+    return Scale{ldexp(1.0, 51 - k), ldexp(1.0, k - 51)};
   }
   // The scale of a deterministic paint, one for the whole paint: amax 2^e
   // 2^lpc < 2^62, so that a cell may receive one contribution from each of
@@ -583,8 +756,10 @@ struct FixAcc {
     frexp(amax, &k);
     return Scale{ldexp(1.0, 62 - lpc - k), ldexp(1.0, k + lpc - 62)};
   }
-  __device__ static void add(Cell* c, double v, const Scale& sc) {
-    atomicAdd(c, static_cast<unsigned long long>(__double2ll_rn(v * sc.s)));
+  __device__ static double scaled(double x, const Scale& sc) { return x * sc.s; }
+  __device__ static void add(Cell* c, double w, double x) {
+    const long long b = __double_as_longlong(fma(w, x, 0x1.8p52));
+    atomicAdd(c, static_cast<unsigned long long>(b - 0x4338000000000000ll));
   }
   __device__ static double get(Cell c, const Scale& sc) {
     return static_cast<double>(static_cast<long long>(c)) * sc.inv;
@@ -592,11 +767,18 @@ struct FixAcc {
 };
 template <>
 struct WinAcc<float> : FixAcc {};
+// Deterministic paints: scale_det lets contributions grow past 2^51 on the
+// smallest grid (8^3 particles), so they convert with the general rounding.
+struct DetAcc : FixAcc {
+  __device__ static void add(Cell* c, double w, double x) {
+    atomicAdd(c, static_cast<unsigned long long>(__double2ll_rn(w * x)));
+  }
+};
 
 // Window accumulator of a paint: WinAcc<T>, or fixed point in deterministic
 // mode (DET) for both precisions.
 template <typename T, bool DET>
-using PaintAcc = typename std::conditional<DET, FixAcc, WinAcc<T>>::type;
+using PaintAcc = typename std::conditional<DET, DetAcc, WinAcc<T>>::type;
 
 // Largest |contribution| a deterministic paint's scale is chosen for: the
 // CIC weights (at most 1) times coef times the largest |v| (vmax, device;
@@ -706,7 +888,8 @@ __global__ __launch_bounds__(kThreads) void k_zero_unowned(const unsigned* __res
   int o[3];
   block_origin(static_cast<unsigned>(b), L, o);
   const long long cx = o[0] + (lane >> 3), cy = o[1] + (lane & 7);
-  const long long row = ((cx << L.lm) | cy) << L.lm | o[2];
+  const unsigned row = cell_at(static_cast<unsigned>(cx), static_cast<unsigned>(cy),
+                               static_cast<unsigned>(o[2]), L);
   const long long zplane = 1ll << (2 * L.lm + L.lnb);
   const unsigned bz = ((static_cast<unsigned>(o[2]) >> kLB) + 1) & ((1u << L.lnb) - 1);
   const long long zc = ((static_cast<long long>(bz) << L.lm | cx) << L.lm) | cy;
@@ -779,18 +962,19 @@ __device__ __forceinline__ void flush_det(const Item& m, const Layout& L, const 
 
 // The fields of a deterministic paint: out_f[i] = (det_f[i] + the z-halo
 // entry of cell i when its z is a multiple of 8) 2^-e with the paint's scale
-// (vmax, coef, lpc as given to the paint); lm = log2 of the grid side.
+// (vmax, coef, lpc as given to the paint).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_det_to_field(const unsigned long long* __restrict__ det,
                                                            const unsigned long long* __restrict__ zh,
-                                                           int nf, long long ncells, int lm,
+                                                           int nf, long long ncells, Layout L,
                                                            const double* __restrict__ vmax,
                                                            T coef, int lpc, MPtrs<T> out) {
   const double inv = FixAcc::scale_det(det_amax<T>(vmax, coef), lpc).inv;
   const long long zplane = ncells >> kLB;
   for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < ncells;
        i += (long long)gridDim.x * kThreads) {
-    const long long zi = ((i & ((1ll << lm) - 1)) >> kLB << (2 * lm)) | (i >> lm);
+    const unsigned c = static_cast<unsigned>(i), m = (1u << L.lm) - 1;
+    const unsigned zi = L.slabs ? c >> kLB : (c & m) >> kLB << (2 * L.lm) | c >> L.lm;
     const bool zcell = (i & (kB - 1)) == 0;
     for (int f = 0; f < nf; ++f) {
       const unsigned long long z = zh[f * zplane + zi];
@@ -814,9 +998,8 @@ __host__ __device__ __forceinline__ long long face_waves(const Layout& L) {
 // (ly, lz) is cell (8 b0, 8 b1 + ly, 8 b2 + lz), on a y face lane (lx, lz)
 // is cell (8 b0 + lx, 8 b1, 8 b2 + lz) with lx = 0 idle (an x face cell).
 // The main halo value of the face's 64 cells then sits in one contiguous
-// run of the staging of one item, and the four wavefronts of a workgroup
-// take neighbouring faces along z, so the mesh rows they update are
-// 128-byte runs.  istart: the order's item starts per block (nb + 1).
+// run of the staging of one item, and with the field in slabs an x face's
+// cells are one run too.  istart: the order's item starts per block (nb + 1).
 template <typename T, int NF>
 __global__ __launch_bounds__(kThreads) void k_halo_rows(const T* __restrict__ halo,
                                                         const unsigned* __restrict__ istart,
@@ -881,13 +1064,14 @@ __global__ __launch_bounds__(kThreads) void k_halo_rows(const T* __restrict__ ha
   const long long cx = (static_cast<long long>(bb[0]) << kLB) | l[0];
   const long long cy = (static_cast<long long>(bb[1]) << kLB) | l[1];
   const long long cz = (static_cast<long long>(bb[2]) << kLB) | l[2];
-  const long long c = (((cx << L.lm) | cy) << L.lm) | cz;
+  const unsigned c = cell_at(static_cast<unsigned>(cx), static_cast<unsigned>(cy),
+                             static_cast<unsigned>(cz), L);
 #pragma unroll
   for (int f = 0; f < NF; ++f) dst.p[f][c] += sum[f];
 }
 
-// cell (x, y, 8 bz) += zh[(bz, x, y)] for one field of side 2^lm (the
-// consumers that read a paint's field directly).
+// cell (x, y, 8 bz) += zh[(bz, x, y)] for one [x][y][z] field of side 2^lm (the
+// callers that want the painted field itself).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_add_zh(T* __restrict__ rho, const T* __restrict__ zh,
                                                      int lm, long long nz) {
@@ -913,19 +1097,22 @@ __global__ __launch_bounds__(kThreads) void k_paint_b(const T* __restrict__ d,
   __shared__ typename A::Cell acc[kWin];
   Item m;
   if (!item_of<false>(it, L, m)) return;
+  typename A::Scale sc{};
   long long a[kPer];
   bool ok[kPer];
   unsigned id[kPer];
   int idx[kPer][3];
   T dsp[kPer][3];
   item_slots(m, a, ok);  // loads in flight while the window is cleared
-  load_u32(it.ids, a, id);
+  // all rounds at once: by rounds the paint took 158 us instead of 148 (FP32,
+  // 256^3), its loads through gsrc starting later
+  load_u32<kPer>(it.ids, a, id);
   if (gsrc) {
     unsigned sa[kPer];
-    load_u32(gsrc, a, sa);
-    load3_at(d, P, sa, dsp);
+    load_u32<kPer>(gsrc, a, sa);
+    load3_at<kPer>(d, P, sa, dsp);
   } else {
-    load3_at(d, P, a, dsp);
+    load3_at<kPer>(d, P, a, dsp);
   }
   zero_window(acc, 1);
   if (dcopy) {
@@ -938,18 +1125,18 @@ __global__ __launch_bounds__(kThreads) void k_paint_b(const T* __restrict__ d,
     }
   }
   lattice_all(id, lp, idx);
-  typename A::Scale sc;  // weights are at most 1
   if constexpr (DET)
     sc = FixAcc::scale_det(1.0, dt.lpc);
   else
     sc = A::scale_for(1.0);
+  const double one = A::scaled(1.0, sc);
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     if (!ok[k]) continue;
     const Stencil<T> s = wrapped_stencil(idx[k], dsp[k], g);
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
-      A::add(&acc[win_index(m.o, cx, cy, cz)], static_cast<double>(w), sc);
+      A::add(&acc[win_index(m.o, cx, cy, cz)], static_cast<double>(w), one);
     });
   }
   __syncthreads();
@@ -977,16 +1164,20 @@ __global__ __launch_bounds__(kThreads) void k_paint_vec_b(const T* __restrict__ 
   __shared__ double red[kThreads / 64];
   Item m;
   if (!item_of<false>(it, L, m)) return;
+  typename A::Scale sc{};
   long long a[kPer];
   bool ok[kPer];
   unsigned id[kPer], sa[kPer];
   int idx[kPer][3];
   T dsp[kPer][3], vv[kPer][3];
   item_slots(m, a, ok);  // loads in flight while the window is cleared
-  load_u32(it.ids, a, id);
-  load_u32(src, a, sa);
-  load3_at(d, P, a, dsp);
-  load3_at(v, P, sa, vv);
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    load_u32<R>(it.ids, a, id);
+    load_u32<R>(src, a, sa);
+    load3_at<R>(d, P, a, dsp);
+    load3_at<R>(v, P, sa, vv);
+  });
   zero_window(acc, 3);
   lattice_all(id, lp, idx);
   double amax = 0.0;  // largest |coef v| of the item (the weights are at most 1)
@@ -1000,7 +1191,6 @@ __global__ __launch_bounds__(kThreads) void k_paint_vec_b(const T* __restrict__ 
   }
   wg_max_issue(amax, red);
   __syncthreads();
-  typename A::Scale sc;
   if constexpr (DET)
     sc = FixAcc::scale_det(det_amax<T>(dt.vmax, coef), dt.lpc);
   else
@@ -1008,16 +1198,16 @@ __global__ __launch_bounds__(kThreads) void k_paint_vec_b(const T* __restrict__ 
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     if (!ok[k]) continue;
-    const double v0 = static_cast<double>(coef * vv[k][0]),
-                 v1 = static_cast<double>(coef * vv[k][1]),
-                 v2 = static_cast<double>(coef * vv[k][2]);
+    const double v0 = A::scaled(static_cast<double>(coef * vv[k][0]), sc),
+                 v1 = A::scaled(static_cast<double>(coef * vv[k][1]), sc),
+                 v2 = A::scaled(static_cast<double>(coef * vv[k][2]), sc);
     const Stencil<T> s = wrapped_stencil(idx[k], dsp[k], g);
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
       const int c = win_index(m.o, cx, cy, cz);
       const double wd = static_cast<double>(w);
-      A::add(&acc[c], wd * v0, sc);
-      A::add(&acc[kWin + c], wd * v1, sc);
-      A::add(&acc[2 * kWin + c], wd * v2, sc);
+      A::add(&acc[c], wd, v0);
+      A::add(&acc[kWin + c], wd, v1);
+      A::add(&acc[2 * kWin + c], wd, v2);
     });
   }
   __syncthreads();
@@ -1037,8 +1227,10 @@ __global__ __launch_bounds__(kThreads) void k_step_b(
     const T* __restrict__ d, const T* __restrict__ p, const unsigned* __restrict__ pinv,
     const T* __restrict__ g, long long M, T kick, T drift, long long P, int lp, Grid<T> gr,
     Layout L, Items it, T* __restrict__ dn, T* __restrict__ pn, unsigned* __restrict__ count,
-    unsigned* __restrict__ key, unsigned* __restrict__ rank) {
-  __shared__ T lds[3 * kWin];
+    unsigned* __restrict__ key, unsigned* __restrict__ rank,
+    unsigned* __restrict__ nbr_base) {
+  __shared__ WinCell<T> lds[kWin];
+  __shared__ unsigned wcnt[kNbr];
   Item m;
   if (!item_of<true>(it, L, m)) return;
   long long a[kPer];
@@ -1047,17 +1239,21 @@ __global__ __launch_bounds__(kThreads) void k_step_b(
   int idx[kPer][3];
   T dsp[kPer][3], mom[kPer][3];
   item_slots(m, a, ok);  // particle loads in flight while the window loads
-  load_u32(it.ids, a, id);
-  if (pinv) {
-    unsigned sa[kPer];
-    load_u32(pinv, a, sa);
-    load3_at(d, P, a, dsp);
-    load3_at(p, P, sa, mom);
-  } else {
-    load3_at(d, P, a, dsp);
-    load3_at(p, P, a, mom);
-  }
-  load_window<T>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M}}, 3, lds);
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    load_u32<R>(it.ids, a, id);
+    if (pinv) {
+      unsigned sa[kPer];
+      load_u32<R>(pinv, a, sa);
+      load3_at<R>(d, P, a, dsp);
+      load3_at<R>(p, P, sa, mom);
+    } else {
+      load3_at<R>(d, P, a, dsp);
+      load3_at<R>(p, P, a, mom);
+    }
+  });
+  load_window<3>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M}}, lds);
+  if (threadIdx.x < kNbr) wcnt[threadIdx.x] = 0;
   lattice_all(id, lp, idx);
   __syncthreads();
 #pragma unroll
@@ -1067,10 +1263,10 @@ __global__ __launch_bounds__(kThreads) void k_step_b(
     T F[3] = {0, 0, 0};
     const Stencil<T> s = wrapped_stencil(idx[k], dsp[k], gr);
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
-      const int c = win_index(m.o, cx, cy, cz);
-      F[0] += w * lds[c];
-      F[1] += w * lds[kWin + c];
-      F[2] += w * lds[2 * kWin + c];
+      const WinCell<T> q = lds[win_index(m.o, cx, cy, cz)];
+      F[0] += w * q.v[0];
+      F[1] += w * q.v[1];
+      F[2] += w * q.v[2];
     });
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -1084,9 +1280,6 @@ __global__ __launch_bounds__(kThreads) void k_step_b(
   }
   if (!count) return;
   // ranks aggregated over the workgroup (see rank_issue_wg)
-  __shared__ unsigned wcnt[kNbr], wbase[kNbr];
-  if (threadIdx.x < kNbr) wcnt[threadIdx.x] = 0;
-  __syncthreads();
   RankTicket t[kPer];
   int slot[kPer];
 #pragma unroll
@@ -1094,17 +1287,16 @@ __global__ __launch_bounds__(kThreads) void k_step_b(
     slot[k] = neighbour_slot(m.b, b[k], L);
     t[k] = rank_issue_wg(b[k], slot[k], ok[k], count, wcnt);
   }
-  __syncthreads();
-  rank_reserve_wg(m.b, L, count, wcnt, wbase);
-  __syncthreads();
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const unsigned r = rank_finish_wg(t[k], slot[k], ok[k], wbase);
-    if (ok[k]) {
-      key[a[k]] = b[k];
-      rank[a[k]] = r;
-    }
+    const unsigned r = rank_of(t[k]);
+    if (!ok[k]) continue;
+    rank[a[k]] = static_cast<unsigned>(slot[k]) << kRankBits | r;
+    if (slot[k] == kNbr) key[a[k]] = b[k];
   }
+  if (!count) return;
+  __syncthreads();
+  rank_reserve_wg(m.b, L, count, wcnt, nbr_base + static_cast<size_t>(m.i) * kNbrRow);
 }
 
 // Position cotangent of one force evaluation with cotangent v = coef p_bar:
@@ -1120,7 +1312,7 @@ __global__ __launch_bounds__(kThreads) void k_force_adjoint_b(
     const T* __restrict__ g, const T* __restrict__ rho_bar, long long M, T drift, long long P,
     int lp, Grid<T> gm, Layout L, Items it, const unsigned* __restrict__ src,
     T* __restrict__ dbar_out, T* __restrict__ pbar_out) {
-  __shared__ T lds[4 * kWin];
+  __shared__ WinCell<T> lds[kWin];
   Item m;
   if (!item_of<true>(it, L, m)) return;
   long long a[kPer];
@@ -1129,12 +1321,15 @@ __global__ __launch_bounds__(kThreads) void k_force_adjoint_b(
   unsigned id[kPer], sa[kPer];
   T dsp[kPer][3], pb[kPer][3], db[kPer][3];
   item_slots(m, a, ok);  // particle loads in flight while the window loads
-  load_u32(it.ids, a, id);
-  load_u32(src, a, sa);
-  load3_at(d, P, a, dsp);
-  load3_at(pbar, P, sa, pb);
-  load3_at(dbar, P, sa, db);
-  load_window<T>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M, rho_bar}}, 4, lds);
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    load_u32<R>(it.ids, a, id);
+    load_u32<R>(src, a, sa);
+    load3_at<R>(d, P, a, dsp);
+    load3_at<R>(pbar, P, sa, pb);
+    load3_at<R>(dbar, P, sa, db);
+  });
+  load_window<4>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M, rho_bar}}, lds);
   lattice_all(id, lp, idx);
   __syncthreads();
 #pragma unroll
@@ -1144,8 +1339,8 @@ __global__ __launch_bounds__(kThreads) void k_force_adjoint_b(
     const T v0 = coef * pb[k][0], v1 = coef * pb[k][1], v2 = coef * pb[k][2];
     T xb[3] = {0, 0, 0};
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T, T d0, T d1, T d2) {
-      const int c = win_index(m.o, cx, cy, cz);
-      const T h = v0 * lds[c] + v1 * lds[kWin + c] + v2 * lds[2 * kWin + c] + lds[3 * kWin + c];
+      const WinCell<T> q = lds[win_index(m.o, cx, cy, cz)];
+      const T h = v0 * q.v[0] + v1 * q.v[1] + v2 * q.v[2] + q.v[3];
       xb[0] += d0 * h;
       xb[1] += d1 * h;
       xb[2] += d2 * h;
@@ -1157,6 +1352,7 @@ __global__ __launch_bounds__(kThreads) void k_force_adjoint_b(
       pbar_out[q * P + a[k]] = pb[k][q] + drift * db[k][q];
     }
   }
+
 }
 
 // Kick-synchronised snapshot of a state in its own block order (lightcone,
@@ -1166,7 +1362,7 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_snapshot_b(
     const T* __restrict__ d, const T* __restrict__ p, const T* __restrict__ g, long long M,
     T half_kick, long long P, int lp, Grid<T> gm, Layout L, Items it, T* __restrict__ snap) {
-  __shared__ T lds[3 * kWin];
+  __shared__ WinCell<T> lds[kWin];
   Item m;
   if (!item_of<true>(it, L, m)) return;
   long long a[kPer];
@@ -1175,10 +1371,13 @@ __global__ __launch_bounds__(kThreads) void k_snapshot_b(
   int idx[kPer][3];
   T dsp[kPer][3], mom[kPer][3];
   item_slots(m, a, ok);  // particle loads in flight while the window loads
-  load_u32(it.ids, a, id);
-  load3_at(d, P, a, dsp);
-  load3_at(p, P, a, mom);
-  load_window<T>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M}}, 3, lds);
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    load_u32<R>(it.ids, a, id);
+    load3_at<R>(d, P, a, dsp);
+    load3_at<R>(p, P, a, mom);
+  });
+  load_window<3>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M}}, lds);
   lattice_all(id, lp, idx);
   __syncthreads();
 #pragma unroll
@@ -1187,10 +1386,10 @@ __global__ __launch_bounds__(kThreads) void k_snapshot_b(
     T F[3] = {0, 0, 0};
     const Stencil<T> s = wrapped_stencil(idx[k], dsp[k], gm);
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
-      const int c = win_index(m.o, cx, cy, cz);
-      F[0] += w * lds[c];
-      F[1] += w * lds[kWin + c];
-      F[2] += w * lds[2 * kWin + c];
+      const WinCell<T> q = lds[win_index(m.o, cx, cy, cz)];
+      F[0] += w * q.v[0];
+      F[1] += w * q.v[1];
+      F[2] += w * q.v[2];
     });
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -1198,6 +1397,7 @@ __global__ __launch_bounds__(kThreads) void k_snapshot_b(
       snap[(3 + q) * P + a[k]] = mom[k][q] + half_kick * F[q];
     }
   }
+
 }
 
 // Last kick (readout of g at d) of the momenta p into pout in this order,
@@ -1210,27 +1410,36 @@ __global__ __launch_bounds__(kThreads) void k_final_b(
     const T* __restrict__ d, const T* p, const unsigned* __restrict__ pinv, T* pout,
     const T* __restrict__ g, long long M, T kick, long long P, int lp, Grid<T> gm, Layout L,
     Items it, pk::Rsd<T> rsd, Grid<T> gd, Layout Ld, unsigned* __restrict__ count,
-    unsigned* __restrict__ key, unsigned* __restrict__ rank) {
-  __shared__ T lds[3 * kWin];
+    unsigned* __restrict__ key, unsigned* __restrict__ rank,
+    unsigned* __restrict__ nbr_base) {
+  __shared__ WinCell<T> lds[kWin];
+  __shared__ unsigned wcnt[kNbr];
   Item m;
   if (!item_of<true>(it, L, m)) return;
+  // ranks aggregated over the workgroup around the data-grid block that
+  // holds this mesh block's origin (see rank_issue_wg)
+  const unsigned b0 = block_around(m, Ld, L.lm - Ld.lm);
   long long a[kPer];
   bool ok[kPer];
   unsigned b[kPer], id[kPer];
   int idx[kPer][3];
   T dsp[kPer][3], mom[kPer][3];
   item_slots(m, a, ok);  // particle loads in flight while the window loads
-  load_u32(it.ids, a, id);
-  if (pinv) {
-    unsigned sa[kPer];
-    load_u32(pinv, a, sa);
-    load3_at(d, P, a, dsp);
-    load3_at(p, P, sa, mom);
-  } else {
-    load3_at(d, P, a, dsp);
-    load3_at(p, P, a, mom);
-  }
-  load_window<T>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M}}, 3, lds);
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    load_u32<R>(it.ids, a, id);
+    if (pinv) {
+      unsigned sa[kPer];
+      load_u32<R>(pinv, a, sa);
+      load3_at<R>(d, P, a, dsp);
+      load3_at<R>(p, P, sa, mom);
+    } else {
+      load3_at<R>(d, P, a, dsp);
+      load3_at<R>(p, P, a, mom);
+    }
+  });
+  load_window<3>(m.o, L, Ptrs<T>{{g, g + M, g + 2 * M}}, lds);
+  if (threadIdx.x < kNbr) wcnt[threadIdx.x] = 0;
   lattice_all(id, lp, idx);
   __syncthreads();
 #pragma unroll
@@ -1240,10 +1449,10 @@ __global__ __launch_bounds__(kThreads) void k_final_b(
     T F[3] = {0, 0, 0}, ds[3];
     const Stencil<T> s = wrapped_stencil(idx[k], dsp[k], gm);
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
-      const int c = win_index(m.o, cx, cy, cz);
-      F[0] += w * lds[c];
-      F[1] += w * lds[kWin + c];
-      F[2] += w * lds[2 * kWin + c];
+      const WinCell<T> q = lds[win_index(m.o, cx, cy, cz)];
+      F[0] += w * q.v[0];
+      F[1] += w * q.v[1];
+      F[2] += w * q.v[2];
     });
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -1254,15 +1463,6 @@ __global__ __launch_bounds__(kThreads) void k_final_b(
     Stencil<T> s2 = pk::stencil(idx[k], gd.ratio, ds, gd.inv_cell, gd.cell);
     b[k] = block_of(s2, Ld);
   }
-  // ranks aggregated over the workgroup around the data-grid block that
-  // holds this mesh block's origin (see rank_issue_wg)
-  const int rs = L.lm - Ld.lm;
-  const unsigned b0 = ((static_cast<unsigned>(m.o[0] >> rs) >> kLB) << (2 * Ld.lnb)) |
-                      ((static_cast<unsigned>(m.o[1] >> rs) >> kLB) << Ld.lnb) |
-                      (static_cast<unsigned>(m.o[2] >> rs) >> kLB);
-  __shared__ unsigned wcnt[kNbr], wbase[kNbr];
-  if (threadIdx.x < kNbr) wcnt[threadIdx.x] = 0;
-  __syncthreads();
   RankTicket t[kPer];
   int slot[kPer];
 #pragma unroll
@@ -1270,17 +1470,15 @@ __global__ __launch_bounds__(kThreads) void k_final_b(
     slot[k] = neighbour_slot(b0, b[k], Ld);
     t[k] = rank_issue_wg(b[k], slot[k], ok[k], count, wcnt);
   }
-  __syncthreads();
-  rank_reserve_wg(b0, Ld, count, wcnt, wbase);
-  __syncthreads();
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const unsigned r = rank_finish_wg(t[k], slot[k], ok[k], wbase);
-    if (ok[k]) {
-      key[a[k]] = b[k];
-      rank[a[k]] = r;
-    }
+    const unsigned r = rank_of(t[k]);
+    if (!ok[k]) continue;
+    rank[a[k]] = static_cast<unsigned>(slot[k]) << kRankBits | r;
+    if (slot[k] == kNbr) key[a[k]] = b[k];
   }
+  __syncthreads();
+  rank_reserve_wg(b0, Ld, count, wcnt, nbr_base + static_cast<size_t>(m.i) * kNbrRow);
 }
 
 // Data-grid paint of the redshift-space positions (items of the data order).
@@ -1297,22 +1495,26 @@ __global__ __launch_bounds__(kThreads) void k_data_paint_b(const T* __restrict__
   __shared__ typename A::Cell acc[kWin];
   Item m;
   if (!item_of<false>(it, Ld, m)) return;
+  typename A::Scale sc{};
   long long a[kPer];
   bool ok[kPer];
   unsigned id[kPer];
   int idx[kPer][3];
   T dsp[kPer][3], mom[kPer][3];
   item_slots(m, a, ok);  // loads in flight while the window is cleared
-  load_u32(it.ids, a, id);
-  load3_at(d, P, a, dsp);
-  load3_at(p, P, a, mom);
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    load_u32<R>(it.ids, a, id);
+    load3_at<R>(d, P, a, dsp);
+    load3_at<R>(p, P, a, mom);
+  });
   zero_window(acc, 1);
   lattice_all(id, lp, idx);
-  typename A::Scale sc;  // weights are at most 1
   if constexpr (DET)
     sc = FixAcc::scale_det(1.0, dt.lpc);
   else
     sc = A::scale_for(1.0);
+  const double one = A::scaled(1.0, sc);
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
@@ -1321,7 +1523,7 @@ __global__ __launch_bounds__(kThreads) void k_data_paint_b(const T* __restrict__
     pk::rsd_shift(rsd, idx[k], dsp[k], mom[k], ds);
     const Stencil<T> s = wrapped_stencil(idx[k], ds, gd);
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
-      A::add(&acc[win_index(m.o, cx, cy, cz)], static_cast<double>(w), sc);
+      A::add(&acc[win_index(m.o, cx, cy, cz)], static_cast<double>(w), one);
     });
   }
   __syncthreads();
@@ -1347,10 +1549,24 @@ __global__ __launch_bounds__(kThreads) void k_data_adjoint_b(
   int idx[kPer][3];
   T dsp[kPer][3], mom[kPer][3];
   item_slots(m, a, ok);  // particle loads in flight while the window loads
-  load_u32(it.ids, a, id);
-  load3_at(d, P, a, dsp);
-  load3_at(p, P, a, mom);
-  load_window<T>(m.o, Ld, Ptrs<T>{{rho_bar}}, 1, lds);
+  with_rounds(m, [&](auto RC) {
+    constexpr int R = decltype(RC)::value;
+    load_u32<R>(it.ids, a, id);
+    load3_at<R>(d, P, a, dsp);
+    load3_at<R>(p, P, a, mom);
+  });
+  {
+    constexpr int kIt = (kWin + kThreads - 1) / kThreads;
+    T v[kIt];
+#pragma unroll
+    for (int j = 0; j < kIt; ++j)
+      v[j] = rho_bar[win_cell(m.o, min(static_cast<int>(threadIdx.x) + j * kThreads, kWin - 1), Ld)];
+#pragma unroll
+    for (int j = 0; j < kIt; ++j) {
+      const int k = static_cast<int>(threadIdx.x) + j * kThreads;
+      if (k < kWin) lds[k] = v[j];
+    }
+  }
   lattice_all(id, lp, idx);
   __syncthreads();
 #pragma unroll
@@ -1376,6 +1592,7 @@ __global__ __launch_bounds__(kThreads) void k_data_adjoint_b(
       pbar[q * P + a[k]] = pb[q];
     }
   }
+
 }
 
 }  // namespace bk

@@ -72,8 +72,8 @@ class Engine final : public EngineBase {
     tape_forces_ = p.tape_forces != 0;
     // Checkpoint spacing; a spacing beyond the last step keeps state 0 only.
     K_ = p.ckpt_every > 0 ? std::min(p.ckpt_every, S_ + 1) : 0;
-    Lm_ = bk::layout_for(lm_);
-    Ld_ = bk::layout_for(lp_);
+    Lm_ = bk::layout_for(lm_, true);
+    Ld_ = bk::layout_for(lp_, false);
     nbm_ = bk::block_count(Lm_);
     nbd_ = bk::block_count(Ld_);
     mim_ = bk::max_items(Lm_, P_);
@@ -129,14 +129,15 @@ class Engine final : public EngineBase {
     desttape_ = c.take<uint32_t>((size_t)(S_ + 2) * P_);
     ostart_ = c.take<uint32_t>((size_t)(S_ + 1) * (nbm_ + 1));
     oistart_ = c.take<uint32_t>((size_t)(S_ + 1) * (nbm_ + 1));
-    oitems_ = c.take<uint2>((size_t)(S_ + 1) * mim_);
+    oitems_ = c.take<uint4>((size_t)(S_ + 1) * 2 * bk::item_grid(Lm_, P_));
     dstart_ = c.take<uint32_t>(nbd_ + 1);
     distart_ = c.take<uint32_t>(nbd_ + 1);
-    ditems_ = c.take<uint2>(mid_);
+    ditems_ = c.take<uint4>(2 * bk::item_grid(Ld_, P_));
     dids_ = c.take<uint32_t>(P_);
     bcount_ = c.take<uint32_t>(std::max(nbm_, nbd_));
     bkey_ = c.take<uint32_t>(P_);
     brank_ = c.take<uint32_t>(P_);
+    bnbr_ = c.take<uint32_t>((size_t)bk::kNbrRow * mim_);
     pinv_ = c.take<uint32_t>(P_);
     bsums_ = c.take<uint2>(1024);
     // halos of the paints (blocks.h): the x/y staging, one slot of
@@ -392,7 +393,7 @@ class Engine final : public EngineBase {
     fill(tmpp_, T(0), 3 * P_);
     bk::k_step_b<T><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
         tmpd_, tmpp_, nullptr, gtape_, M_, T(1), T(0), P_, lp_, gmesh(), Lm_,
-        items(mesh_order(0), dids_), dbar2_, pbar2_, nullptr, nullptr, nullptr);
+        items(mesh_order(0), dids_), dbar2_, pbar2_, nullptr, nullptr, nullptr, nullptr);
     IC_LAUNCHED();
     T* F = static_cast<T*>(force);
     bk::k_to_lattice<T><<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
@@ -590,21 +591,23 @@ class Engine final : public EngineBase {
   struct Order {
     unsigned* start;   // nb + 1
     unsigned* istart;  // nb + 1 (istart[nb] = item count)
-    uint2* items;
+    uint4* items;      // nwg records by index, nwg dealt to the XCDs
     unsigned nb;
     unsigned max_items;
+    unsigned nwg;
   };
   Order mesh_order(int n) const {
     return Order{ostart_ + (size_t)n * (nbm_ + 1), oistart_ + (size_t)n * (nbm_ + 1),
-                 oitems_ + (size_t)n * mim_, nbm_, mim_};
+                 oitems_ + (size_t)n * 2 * bk::item_grid(Lm_, P_), nbm_, mim_,
+                 bk::item_grid(Lm_, P_)};
   }
-  Order data_order() const { return Order{dstart_, distart_, ditems_, nbd_, mid_}; }
+  Order data_order() const { return Order{dstart_, distart_, ditems_, nbd_, mid_, bk::item_grid(Ld_, P_)}; }
   unsigned* ids(int n) const { return idtape_ + (size_t)n * P_; }
   // dest(n): slot in order n + 1 of each slot of order n (n = -1: lattice
   // order to order 0); dest(S) maps order S to the data order.
   unsigned* dest(int n) const { return desttape_ + (size_t)(n + 1) * P_; }
   bk::Items items(const Order& o, const unsigned* id) const {
-    return bk::Items{o.items, o.start, o.istart + o.nb, id};
+    return bk::Items{o.items, o.items + o.nwg, id};
   }
 
   void zero_counts(unsigned nb) { ek_fill_u32(bcount_, 0u, nb); }
@@ -620,7 +623,8 @@ class Engine final : public EngineBase {
     IC_LAUNCHED();
     bk::k_scan_out<<<chunks, 256, 0, st_>>>(bcount_, o.nb, bsums_, o.start, o.istart);
     IC_LAUNCHED();
-    bk::k_fill_items<<<grid_for(o.nb, 256), 256, 0, st_>>>(o.start, o.istart, o.nb, o.items);
+    bk::k_fill_items<<<grid_for(o.nwg, 256), 256, 0, st_>>>(o.start, o.istart, o.nb, o.nwg,
+                                                            o.items, o.items + o.nwg);
     IC_LAUNCHED();
   }
 
@@ -641,6 +645,24 @@ class Engine final : public EngineBase {
     auto sc = timer_.scope("sort_scatter_ids", P_ * 24.0);
     bk::k_scatter_ids<<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
         bkey_, brank_, o.start, ids_src, ids_dst, dst_slots, pinv_, P_);
+    IC_LAUNCHED();
+  }
+
+  // The same for particles of the mesh order of src that a counting kernel over
+  // its items ranked (packed in brank_): six fields and the ids, or the ids
+  // alone with pinv_, to the order o of layout Ld.
+  void move(const bk::Items& src, const Order& o, const bk::Layout& Ld, const bk::Ptrs<T>& from,
+            const bk::MPtrs<T>& to, unsigned* ids_dst, unsigned* dst_slots) {
+    auto sc = timer_.scope("sort_scatter", P_ * (12.0 * sizeT() + 16.0));
+    bk::k_scatter_b<T><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
+        src, Lm_, Ld, Lm_.lm - Ld.lm, bk::Moves{bkey_, brank_, bnbr_, o.start}, from, to, 6,
+        ids_dst, dst_slots);
+    IC_LAUNCHED();
+  }
+  void move_ids(const bk::Items& src, const Order& o, unsigned* ids_dst, unsigned* dst_slots) {
+    auto sc = timer_.scope("sort_scatter_ids", P_ * 20.0);
+    bk::k_scatter_ids_b<<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
+        src, Lm_, Lm_, 0, bk::Moves{bkey_, brank_, bnbr_, o.start}, ids_dst, dst_slots, pinv_);
     IC_LAUNCHED();
   }
 
@@ -710,7 +732,7 @@ class Engine final : public EngineBase {
           <<<grid, bk::kThreads, 0, st_>>>(detstage_, o.istart, L, det_fields(ncells));
     IC_LAUNCHED();
     bk::k_det_to_field<T><<<grid_for(ncells, bk::kThreads), bk::kThreads, 0, st_>>>(
-        det64_, detzh_, nf, ncells, L.lm, vmax, coef, 3 * lp_, out);
+        det64_, detzh_, nf, ncells, L, vmax, coef, 3 * lp_, out);
     IC_LAUNCHED();
   }
   // *out = max |x_i| over n values.
@@ -764,11 +786,13 @@ class Engine final : public EngineBase {
   }
 
   // rho = CIC density of displacements d given in lattice order (sorted into
-  // the scratch order o first; tmpd_ receives the sorted positions); with
-  // complete = false the z halo stays in zh_ for a consumer that adds it.
+  // the scratch order o first; tmpd_ receives the sorted positions).  The field
+  // is the caller's, [x][y][z]; with complete = false it is the force chain's,
+  // in the grid's own layout, its z halo left in zh_.
   void paint_lattice(const T* d, int grid, T* rho, bool complete = true) {
     const pk::Grid<T> g = grid ? gmesh() : gdata();
-    const bk::Layout& L = grid ? Lm_ : Ld_;
+    bk::Layout L = grid ? Lm_ : Ld_;
+    if (complete) L.slabs = 0;
     const Order o = grid ? mesh_order(0) : data_order();
     const long long ncells = grid ? M_ : P_;
     keys_lattice(d, g, L, o.nb);
@@ -791,7 +815,8 @@ class Engine final : public EngineBase {
   }
 
   // outs[j] = Op_{spec_j}[alpha (a + zh) + beta b] on the chosen grid (zh:
-  // a paint's z halo, nullable).
+  // a paint's z halo).  Fields of the force mesh (grid 1) are painted ones with
+  // their z halo going in and particle windows' fields coming out, in slabs.
   void chain_scatter(int grid, const T* a, T alpha, const T* b, T beta, T* const* outs,
                      const MulSpec* specs, int m, const T* zh = nullptr) {
     auto f = fa(grid);
@@ -806,7 +831,7 @@ class Engine final : public EngineBase {
       auto sc = timer_.scope("fft_x_scatter", (1 + m) * Hb);
       fft_x_scatter<T>(f, S0, So, specs, m);
     }
-    for (int j = 0; j < m; ++j) c2r_yz(f, So[j], outs[j], nullptr, T(0), U, Hb);
+    for (int j = 0; j < m; ++j) c2r_yz(f, So[j], outs[j], nullptr, T(0), U, Hb, grid == 1);
   }
 
   // The z and y passes of a chain: fused into one pass where the grid allows
@@ -826,10 +851,10 @@ class Engine final : public EngineBase {
     fft_y<T>(f, S, true);
   }
   void c2r_yz(const FftArgs<T>& f, cx<T>* S, T* out, const T* aux, T beta_aux, double U,
-              double Hb) {
+              double Hb, bool slab) {
     if (!aux && fft_zy_fused<T>(f.n)) {
       auto sc = timer_.scope("fft_c2r_yz", Hb + U);
-      fft_c2r_yz<T>(f, S, out);
+      fft_c2r_yz<T>(f, S, out, slab);
       return;
     }
     {
@@ -837,7 +862,7 @@ class Engine final : public EngineBase {
       fft_y<T>(f, S, false);
     }
     auto sc = timer_.scope("fft_c2r_z", Hb + (aux ? 2 : 1) * U);
-    fft_c2r_z<T>(f, S, out, T(1), aux, beta_aux);
+    fft_c2r_z<T>(f, S, out, T(1), aux, beta_aux, slab);
   }
 
   struct GIn {
@@ -865,7 +890,7 @@ class Engine final : public EngineBase {
       auto sc = timer_.scope("fft_x_gather", (1 + m) * Hb);
       fft_x_gather<T>(f, Si, specs, m, pool_);
     }
-    c2r_yz(f, pool_, out, aux, beta_aux, U, Hb);
+    c2r_yz(f, pool_, out, aux, beta_aux, U, Hb, grid == 1);
   }
 
   // -------------------------------------------------------------- forward
@@ -961,13 +986,13 @@ class Engine final : public EngineBase {
       step(n, true, pin, pinv, pout);
       build_order(mesh_order(n + 1));
       if (complete) {
-        scatter(mesh_order(n + 1), state_ptrs(tmpd_, pout),
-                state_mptrs(dslot(n + 1), pslot(n + 1)), 6, ids(n), ids(n + 1), dest(n));
+        move(items(mesh_order(n), ids(n)), mesh_order(n + 1), Lm_, state_ptrs(tmpd_, pout),
+             state_mptrs(dslot(n + 1), pslot(n + 1)), ids(n + 1), dest(n));
         force_mesh(n + 1, gslot(n + 1));
         pin = pslot(n + 1);
         pinv = nullptr;
       } else {
-        scatter_ids(mesh_order(n + 1), ids(n), ids(n + 1), dest(n));
+        move_ids(items(mesh_order(n), ids(n)), mesh_order(n + 1), ids(n + 1), dest(n));
         force_mesh(n + 1, gslot(n + 1), pinv_);
         pin = pout;
         pinv = pinv_;
@@ -991,7 +1016,7 @@ class Engine final : public EngineBase {
       bk::k_final_b<T><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
           dslot(S_), pin, pinv, pslot(S_), gslot(S_), M_, static_cast<T>(co_.kick[S_]), P_, lp_,
           gmesh(), Lm_, items(mesh_order(S_), ids(S_)), rsd(), gdata(), Ld_, bcount_, bkey_,
-          brank_);
+          brank_, bnbr_);
       IC_LAUNCHED();
     }
     const T* fd = dslot(S_);
@@ -1025,8 +1050,12 @@ class Engine final : public EngineBase {
       fp = tmpp_;
     }
     build_order(data_order());
-    scatter(data_order(), state_ptrs(fd, fp), state_mptrs(dsd_, psd_), 6, ids(S_), dids_,
-            dest(S_));
+    if (lc_on_)  // ranked by k_keys above
+      scatter(data_order(), state_ptrs(fd, fp), state_mptrs(dsd_, psd_), 6, ids(S_), dids_,
+              dest(S_));
+    else
+      move(items(mesh_order(S_), ids(S_)), data_order(), Ld_, state_ptrs(fd, fp),
+           state_mptrs(dsd_, psd_), dids_, dest(S_));
     if (det_) {
       det_zero_unowned(data_order(), Ld_, 1, P_);
       {
@@ -1061,7 +1090,7 @@ class Engine final : public EngineBase {
     bk::k_step_b<T><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
         dslot(n), pin, pinv, gslot(n), M_, static_cast<T>(co_.kick[n]),
         static_cast<T>(co_.Dr[n]), P_, lp_, gmesh(), Lm_, items(mesh_order(n), ids(n)), tmpd_,
-        pout, keyed ? bcount_ : nullptr, bkey_, brank_);
+        pout, keyed ? bcount_ : nullptr, bkey_, brank_, bnbr_);
     IC_LAUNCHED();
   }
 
@@ -1354,8 +1383,9 @@ class Engine final : public EngineBase {
   bk::Layout Lm_{}, Ld_{};  // 8^3-cell blocks of the mesh and of the data grid
   unsigned nbm_ = 0, nbd_ = 0, mim_ = 0, mid_ = 0;
   uint32_t *idtape_, *desttape_, *ostart_, *oistart_, *dstart_, *distart_, *dids_;
-  uint2 *oitems_, *ditems_, *bsums_;
-  uint32_t *bcount_, *bkey_, *brank_;
+  uint4 *oitems_, *ditems_;
+  uint2* bsums_;
+  uint32_t *bcount_, *bkey_, *brank_, *bnbr_;
   uint32_t* pinv_;  // the newest order's slots to the previous order's
   T* hstage_ = nullptr;
   T* zh_ = nullptr;

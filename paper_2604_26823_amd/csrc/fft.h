@@ -61,6 +61,10 @@ struct FftArgs {
   hipStream_t stream = nullptr;
 };
 
+// Real fields are [x][y][z] or in the slab layout
+// [z / 8][x][y][z mod 8] of the fields that particles paint and read: inputs with a z halo zh are in slabs,
+// outputs with slab set.
+
 // out = forward rfft along z of (alpha a + beta b); b may be null.
 template <typename T>
 void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* out,
@@ -68,7 +72,8 @@ void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<
 
 // out = alpha * (unnormalised inverse rfft along z of in) + beta * aux (aux may be null).
 template <typename T>
-void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* aux, T beta);
+void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* aux, T beta,
+               bool slab = false);
 
 // Whether the fused z and y passes below serve grid side n at this precision.
 template <typename T>
@@ -83,7 +88,7 @@ void fft_r2c_zy(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx
 // fft_zy_fused), for the spectrum of a real field: its kz = 0 and kz = n/2
 // columns must be Hermitian along y (their inverse along y real).
 template <typename T>
-void fft_c2r_yz(const FftArgs<T>& f, const cx<T>* in, T* out);
+void fft_c2r_yz(const FftArgs<T>& f, const cx<T>* in, T* out, bool slab = false);
 
 // In-place complex FFT along y of the half spectrum (forward or inverse, unnormalised).
 template <typename T>

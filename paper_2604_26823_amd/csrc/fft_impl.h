@@ -335,25 +335,66 @@ __device__ __forceinline__ void load_table(cx<T>* dst, const cx<T>* __restrict__
   for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
 }
 
+// The cell pairs (z = 2e, 2e + 1) of one z row `line` = x N + y of a real field:
+// [x][y][z], or the slab layout of the fields that particles read and paint
+// (cell_at in blocks.h), [z / 8][x][y][z mod 8].  In the latter a
+// wavefront that handles a few consecutive rows moves runs of 32 bytes (64 in
+// FP64) per row side by side.
+//
+// A pair is addressed by a base that is the same for the whole workgroup
+// (that of row line0 <= line, on the same or a lower plane), a constant of the
+// element, and one 32-bit byte offset per lane: with TPL a multiple of the
+// slab's four pairs, a lane's elements are lane + multiples of TPL and
+// share that offset.  Addresses of their own for every element cost the
+// fused passes, which hold a plane in all their registers, spills.
+template <typename T, int N, bool SLAB, int TPL>
+struct RowPairs {
+  static constexpr int kP = kZHalo / 2;
+  static constexpr bool kShared = !SLAB || TPL % kP == 0;
+  char* p;
+  uint32_t off;
+  int lane;
+  static __device__ __forceinline__ size_t pair(size_t line, int e) {
+    if (!SLAB) return line * (N / 2) + e;
+    return (static_cast<size_t>(e / kP) * (N * N) + line) * kP + e % kP;
+  }
+  __device__ __forceinline__ RowPairs(const T* field, size_t line0, size_t line, int lane_)
+      : lane(lane_) {
+    p = const_cast<char*>(reinterpret_cast<const char*>(field)) + pair(line0, 0) * sizeof(cx<T>);
+    off = static_cast<uint32_t>((pair(line, kShared ? lane_ : 0) - pair(line0, 0)) *
+                                sizeof(cx<T>));
+  }
+  __device__ __forceinline__ cx<T>& operator()(int e) const {
+    if constexpr (!SLAB)
+      return *reinterpret_cast<cx<T>*>(p + (e - lane) * static_cast<int>(sizeof(cx<T>)) + off);
+    if constexpr (kShared)
+      return *reinterpret_cast<cx<T>*>(
+          p + (e - lane) / kP * static_cast<long long>(N * N * kP * sizeof(cx<T>)) + off);
+    return *reinterpret_cast<cx<T>*>(
+        p + static_cast<uint32_t>(off + (e / kP * (N * N * kP) + e % kP) * sizeof(cx<T>)));
+  }
+};
+
 // ------------------------------------------------------------ z pass R2C
 // Element e of z row `line` (its complex pair 2e, 2e + 1) of
 // alpha (a + zh) + beta b, without a branch: ZH and B are compile-time, and
 // the z-halo value (added to the cells z = 0 mod 8) is loaded for every e and
 // selected, so the loads of a transform's first stage are all issued before
 // its first wait (a branch per element made each load wait for the previous).
+// A field with a z halo (a painted one) is in the slab layout (slab_pair).
 template <typename T, int N, bool ZH, bool B>
-__device__ __forceinline__ cx<T> r2c_elem(const cx<T>* __restrict__ ain,
-                                          const cx<T>* __restrict__ bin,
+__device__ __forceinline__ cx<T> r2c_elem(const RowPairs<T, N, ZH, Plan<N / 2>::TPL>& ra,
+                                          const RowPairs<T, N, false, Plan<N / 2>::TPL>& rb,
                                           const T* __restrict__ zh, size_t line, int e,
                                           T alpha, T beta) {
-  cx<T> u = ain[e];
+  cx<T> u = ra(e);
   if constexpr (ZH) {
     const T z = zh[(size_t)(2 * e / kZHalo) * N * N + line];
     u.x += (e & (kZHalo / 2 - 1)) == 0 ? z : static_cast<T>(0);
   }
   cx<T> v = cscale<T>(u, alpha);
   if constexpr (B) {
-    const cx<T> w = bin[e];
+    const cx<T> w = rb(e);
     v.x += beta * w.x;
     v.y += beta * w.y;
   }
@@ -366,31 +407,28 @@ __device__ __forceinline__ cx<T> r2c_elem(const cx<T>* __restrict__ ain,
 template <typename T, int N, bool ZH, bool B>
 __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_r2c_z(
     const T* __restrict__ a, T alpha, const T* __restrict__ b, T beta,
-    cx<T>* __restrict__ out, const cx<T>* __restrict__ twg, int nlines, int kp,
+    cx<T>* __restrict__ out, const cx<T>* __restrict__ twg, int kp,
     const T* __restrict__ zh) {
   using C = ZCfg<T, N>;
   constexpr int n = C::n;
+  static_assert(N * N % C::LINES == 0, "whole workgroups of rows");
   __shared__ cx<T> buf[C::LINES * C::LS];
   __shared__ cx<T> tw[N];
   load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
   const int lane = threadIdx.x % C::TPL;
   const int l = threadIdx.x / C::TPL;
-  const int line = blockIdx.x * C::LINES + l;
-  const bool valid = line < nlines;
-  // past the last line: row 0 is transformed and not stored
-  const size_t lrow = valid ? static_cast<size_t>(line) : 0;
-  const cx<T>* ain = reinterpret_cast<const cx<T>*>(a + lrow * N);
-  const cx<T>* bin = B ? reinterpret_cast<const cx<T>*>(b + lrow * N) : nullptr;
+  const size_t line0 = static_cast<size_t>(blockIdx.x) * C::LINES, line = line0 + l;
+  const RowPairs<T, N, ZH, C::TPL> ra(a, line0, line, lane);
+  const RowPairs<T, N, false, C::TPL> rb(b, line0, line, lane);
   auto load0 = [&](int e) -> cx<T> {
-    return r2c_elem<T, N, ZH, B>(ain, bin, zh, lrow, e, alpha, beta);
+    return r2c_elem<T, N, ZH, B>(ra, rb, zh, line, e, alpha, beta);
   };
   cx<T>* lb = buf + l * C::LS;
   auto lidx = [&](int e) { return l * C::LS + zl(e); };
   auto storeL = [&](int e, cx<T> v) { lb[zl(e)] = v; };
   fft_line<T, n, true>(lane, buf, lidx, tw, 2, load0, storeL);
   __syncthreads();
-  if (!valid) return;
-  cx<T>* o = out + (size_t)line * kp;
+  cx<T>* o = out + line * kp;
   const T half = static_cast<T>(0.5);
   for (int k = lane; k <= n; k += C::TPL) {
     cx<T> zk = lb[zl(k == n ? 0 : k)];
@@ -404,23 +442,23 @@ __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_r2c_z(
 }
 
 // ------------------------------------------------------------ z pass C2R
-template <typename T, int N>
+template <typename T, int N, bool SLAB>
 __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_c2r_z(
     const cx<T>* __restrict__ in, T* __restrict__ out, T alpha, const T* __restrict__ aux,
-    T beta, const cx<T>* __restrict__ twg, int nlines, int kp) {
+    T beta, const cx<T>* __restrict__ twg, int kp) {
   using C = ZCfg<T, N>;
   constexpr int n = C::n;
+  static_assert(N * N % C::LINES == 0, "whole workgroups of rows");
   __shared__ cx<T> buf[C::LINES * C::LS];
   __shared__ cx<T> tw[N];
   load_table<T>(tw, twg, N);
   const int lane = threadIdx.x % C::TPL;
   const int l = threadIdx.x / C::TPL;
-  const int line = blockIdx.x * C::LINES + l;
-  const bool valid = line < nlines;
+  const size_t line0 = static_cast<size_t>(blockIdx.x) * C::LINES, line = line0 + l;
   cx<T>* lb = buf + l * C::LS;
   // the row's n + 1 values, all loads out before the first wait (no branch:
-  // indices clamped, lines past the end read line 0 and store zeros)
-  const cx<T>* src = in + (valid ? (size_t)line : 0) * kp;
+  // indices clamped)
+  const cx<T>* src = in + line * kp;
   constexpr int KS = n / C::TPL + 1;
   cx<T> rv[KS];
 #pragma unroll
@@ -429,7 +467,7 @@ __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_c2r_z(
   for (int j = 0; j < KS; ++j) {
     const int k = lane + j * C::TPL;
     if (k > n) continue;
-    cx<T> v = valid ? rv[j] : mkc<T>(0, 0);
+    cx<T> v = rv[j];
     if (k == 0 || k == n) v.y = 0;  // the real transform ignores these imaginary parts
     lb[zl(k)] = v;
   }
@@ -444,17 +482,16 @@ __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_c2r_z(
     return mkc<T>(s.x - wd.y, s.y + wd.x);  // s + i w d
   };
   auto lidx = [&](int e) { return l * C::LS + zl(e); };
-  cx<T>* dst = reinterpret_cast<cx<T>*>(out + (size_t)line * N);
-  const cx<T>* ax = aux ? reinterpret_cast<const cx<T>*>(aux + (size_t)line * N) : nullptr;
+  const RowPairs<T, N, SLAB, C::TPL> dst(out, line0, line, lane);
+  const cx<T>* ax = aux ? reinterpret_cast<const cx<T>*>(aux + line * N) : nullptr;
   auto storeL = [&](int e, cx<T> v) {
-    if (!valid) return;
     cx<T> r = cscale<T>(v, alpha);
     if (ax) {
       cx<T> u = ax[e];
       r.x += beta * u.x;
       r.y += beta * u.y;
     }
-    dst[e] = r;
+    dst(e) = r;
   };
   fft_line<T, n, false>(lane, buf, lidx, tw, 2, load0, storeL);
 }
@@ -526,8 +563,6 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_r2c_zy(
   const T* zt = reinterpret_cast<const T*>(buf);
   for (int h = 0; h < 2; ++h) {
     const size_t line = x * N + h * n + l;
-    const cx<T>* ain = reinterpret_cast<const cx<T>*>(a + line * N);
-    const cx<T>* bin = B ? reinterpret_cast<const cx<T>*>(b + line * N) : nullptr;
     if constexpr (ZH) {
       if (h == 1) __syncthreads();  // the first half's held values are read
       T* zw = reinterpret_cast<T*>(buf);
@@ -542,15 +577,17 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_r2c_zy(
       for (int q = 0; q < QZ; ++q) zw[t + q * C::THREADS] = zv[q];
       __syncthreads();
     }
+    const RowPairs<T, N, ZH, C::TPL> ra(a, x * N, line, lane);
+    const RowPairs<T, N, false, C::TPL> rb(b, x * N, line, lane);
     auto load0 = [&](int e) -> cx<T> {  // no branch: all loads out before the first wait
-      cx<T> u = ain[e];
+      cx<T> u = ra(e);
       if constexpr (ZH) {
         const T z = zt[(2 * e / kZHalo) * n + l];
         u.x += (e & (kZHalo / 2 - 1)) == 0 ? z : static_cast<T>(0);
       }
       cx<T> v = cscale<T>(u, alpha);
       if constexpr (B) {
-        const cx<T> w = bin[e];
+        const cx<T> w = rb(e);
         v.x += beta * w.x;
         v.y += beta * w.y;
       }
@@ -625,7 +662,7 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_r2c_zy(
   }
 }
 
-template <typename T, int N>
+template <typename T, int N, bool SLAB>
 __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ twg, int kp) {
   using C = ZYCfg<T, N>;
@@ -701,8 +738,9 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
       if (k != n / 2) lb[zl(n - k)] = merge(xm, cconj<T>(xk), n - k);
     }
     __syncthreads();
-    cx<T>* dst = reinterpret_cast<cx<T>*>(out + (x * N + h * n + l) * N);
-    auto storeL = [&](int e, cx<T> v) { dst[e] = v; };
+    const size_t line = x * N + h * n + l;
+    const RowPairs<T, N, SLAB, C::TPL> dst(out, x * N, line, lane);
+    auto storeL = [&](int e, cx<T> v) { dst(e) = v; };
     fft_line<T, n, false>(lane, buf, lidx, tw, 2, lload, storeL);
   }
 }
@@ -940,20 +978,26 @@ void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<
     fftk::with_flags(zh != nullptr, b != nullptr, [&](auto ZH, auto B) {
       fftk::k_r2c_z<T, N, ZH.value, B.value>
           <<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(a, alpha, b, beta, out,
-                                                                      f.tw, nlines, f.kp, zh);
+                                                                      f.tw, f.kp, zh);
     });
   });
   IC_LAUNCHED();
 }
 
 template <typename T>
-void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* aux, T beta) {
+void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* aux, T beta,
+               bool slab) {
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     using C = fftk::ZCfg<T, N>;
     const int nlines = f.n * f.n;
-    fftk::k_c2r_z<T, N><<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(
-        in, out, alpha, aux, beta, f.tw, nlines, f.kp);
+    const unsigned grid = blocks_for(nlines, C::LINES);
+    if (slab)
+      fftk::k_c2r_z<T, N, true><<<grid, C::THREADS, 0, f.stream>>>(in, out, alpha, aux, beta,
+                                                                   f.tw, f.kp);
+    else
+      fftk::k_c2r_z<T, N, false><<<grid, C::THREADS, 0, f.stream>>>(in, out, alpha, aux, beta,
+                                                                    f.tw, f.kp);
   });
   IC_LAUNCHED();
 }
@@ -981,11 +1025,14 @@ void fft_r2c_zy(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx
 }
 
 template <typename T>
-void fft_c2r_yz(const FftArgs<T>& f, const cx<T>* in, T* out) {
+void fft_c2r_yz(const FftArgs<T>& f, const cx<T>* in, T* out, bool slab) {
   if constexpr (fftk::ZYCfg<T, 256>::ok) {
     if (f.n == 256) {
       using C = fftk::ZYCfg<T, 256>;
-      fftk::k_c2r_yz<T, 256><<<f.n, C::THREADS, 0, f.stream>>>(in, out, f.tw, f.kp);
+      if (slab)
+        fftk::k_c2r_yz<T, 256, true><<<f.n, C::THREADS, 0, f.stream>>>(in, out, f.tw, f.kp);
+      else
+        fftk::k_c2r_yz<T, 256, false><<<f.n, C::THREADS, 0, f.stream>>>(in, out, f.tw, f.kp);
       IC_LAUNCHED();
       return;
     }

@@ -1,7 +1,6 @@
 // Particle building blocks shared by the block-ordered kernels (blocks.h)
-// and the lightcone (lightcone.h): cloud-in-cell stencils and weights, the
-// readout of the force meshes, and the redshift-space distortion with its
-// transpose (gfx950).
+// and the lightcone (lightcone.h): cloud-in-cell stencils and weights and the
+// redshift-space distortion with its transpose (gfx950).
 //
 // Particles are lattice points q_n = n dq plus a displacement d_n stored in
 // structure-of-arrays form [3][P] in lattice order, so consecutive threads
@@ -60,11 +59,6 @@ __device__ __forceinline__ Stencil<T> stencil(const int idx[3], int ratio, const
   return s;
 }
 
-__device__ __forceinline__ long long cell_index(const int c[3], int mask, int lm) {
-  return ((long long)(c[0] & mask) << (2 * lm)) | ((long long)(c[1] & mask) << lm) |
-         (long long)(c[2] & mask);
-}
-
 // Geometry of one grid the particles are painted to or read from.
 template <typename T>
 struct Grid {
@@ -103,47 +97,11 @@ __device__ __forceinline__ void for_corners_xyz(const Stencil<T>& s, F&& f) {
   }
 }
 
-// Calls f(cell, w, dw0, dw1, dw2) for the 8 CIC corners, where w is the
-// weight and dwa its derivative along axis a in units of 1/cell.
-template <typename T, class F>
-__device__ __forceinline__ void for_corners(const Stencil<T>& s, int lm, F&& f) {
-  const int mask = (1 << lm) - 1;
-#pragma unroll
-  for (int ox = 0; ox < 2; ++ox) {
-    const T wx = ox ? s.t[0] : T(1) - s.t[0];
-    const T gx = ox ? T(1) : T(-1);
-#pragma unroll
-    for (int oy = 0; oy < 2; ++oy) {
-      const T wy = oy ? s.t[1] : T(1) - s.t[1];
-      const T gy = oy ? T(1) : T(-1);
-#pragma unroll
-      for (int oz = 0; oz < 2; ++oz) {
-        const T wz = oz ? s.t[2] : T(1) - s.t[2];
-        const T gz = oz ? T(1) : T(-1);
-        const int c[3] = {s.i0[0] + ox, s.i0[1] + oy, s.i0[2] + oz};
-        f(cell_index(c, mask, lm), wx * wy * wz, gx * wy * wz, wx * gy * wz, wx * wy * gz);
-      }
-    }
-  }
-}
-
 template <typename T>
 __device__ __forceinline__ void load3(const T* __restrict__ v, long long P, long long n, T out[3]) {
   out[0] = v[n];
   out[1] = v[P + n];
   out[2] = v[2 * P + n];
-}
-
-// Readout of the three force meshes at particle positions: F_j = sum W g_j.
-template <typename T>
-__device__ __forceinline__ void readout3(const Stencil<T>& s, int lm, const T* __restrict__ g,
-                                         long long M, T F[3]) {
-  F[0] = F[1] = F[2] = T(0);
-  for_corners(s, lm, [&](long long c, T w, T, T, T) {
-    F[0] += w * g[c];
-    F[1] += w * g[M + c];
-    F[2] += w * g[2 * M + c];
-  });
 }
 
 // Redshift-space displacement.  mode 1: shift c p_z along z; mode 2: shift
