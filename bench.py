@@ -117,8 +117,6 @@ LEDGER = {
     "fft_r2c_z": (0, 2),       # real field in, half spectrum out (mesh chains)
     "fft_y": (0, 2),
     "fft_c2r_z": (0, 2),
-    "fft_r2c_zy": (0, 2),      # the z and y passes fused (FP32, 256^3 grids)
-    "fft_c2r_yz": (0, 2),
 }
 
 
@@ -183,8 +181,8 @@ def stored_traffic(kernel, dtype_tag):
 
 def ledger_bytes(name, cfg, elem):
     """Ledger bytes of one launch of a kernel, or None when the ledger has
-    no row of its own for it (the x passes count (1 + m) half spectra, as the
-    library's own figure does)."""
+    no row of its own for it (the x passes count (1 + m) half spectra and the
+    fused z and y passes m fields and spectra, as the library's own figure does)."""
     if name not in LEDGER:
         return None
     a, b = LEDGER[name]

@@ -814,6 +814,14 @@ class Engine final : public EngineBase {
     return s;
   }
 
+  struct GIn {
+    const T* a;
+    T alpha;
+    const T* b;
+    T beta;
+    const T* zh;  // a paint's z halo added to a (nullable)
+  };
+
   // outs[j] = Op_{spec_j}[alpha (a + zh) + beta b] on the chosen grid (zh:
   // a paint's z halo).  Fields of the force mesh (grid 1) are painted ones with
   // their z halo going in and particle windows' fields coming out, in slabs.
@@ -826,52 +834,65 @@ class Engine final : public EngineBase {
     cx<T>* S0 = pool_;
     cx<T>* So[kMaxMul];
     for (int j = 0; j < m; ++j) So[j] = pool_ + (j + 1) * H;
-    r2c_zy(f, a, alpha, b, beta, S0, zh, U, Hb);
+    const GIn in{a, alpha, b, beta, zh};
+    cx<T>* const S[1] = {S0};
+    r2c_zy(f, &in, S, 1, U, Hb);
     {
       auto sc = timer_.scope("fft_x_scatter", (1 + m) * Hb);
       fft_x_scatter<T>(f, S0, So, specs, m);
     }
-    for (int j = 0; j < m; ++j) c2r_yz(f, So[j], outs[j], nullptr, T(0), U, Hb, grid == 1);
+    c2r_yz(f, So, outs, m, nullptr, T(0), U, Hb, grid == 1);
   }
 
-  // The z and y passes of a chain: fused into one pass where the grid allows
-  // (the chains' spectra are those of real fields), else two.
-  void r2c_zy(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* S,
-              const T* zh, double U, double Hb) {
+  // The z and y passes of a chain's m fields: fused into one launch where the
+  // grid allows (the chains' spectra are those of real fields), else two passes
+  // per field.
+  void r2c_zy(const FftArgs<T>& f, const GIn* in, cx<T>* const* S, int m, double U, double Hb) {
     if (fft_zy_fused<T>(f.n)) {
-      auto sc = timer_.scope("fft_r2c_zy", (b ? 2 : 1) * U + Hb);
-      fft_r2c_zy<T>(f, a, alpha, b, beta, S, zh);
+      auto sc = timer_.scope("fft_r2c_zy", m * ((in[0].b ? 2 : 1) * U + Hb));
+      PlaneFwd<T> fl[kMaxMul];
+      // the fields with a second input and those without go in launches of their own
+      for (int j0 = 0; j0 < m;) {
+        int k = 0;
+        for (; j0 + k < m && !in[j0 + k].b == !in[j0].b; ++k) {
+          const GIn& g = in[j0 + k];
+          fl[k] = PlaneFwd<T>{g.a, g.alpha, g.b, g.beta, g.zh, S[j0 + k]};
+        }
+        fft_r2c_zy<T>(f, fl, k);
+        j0 += k;
+      }
       return;
     }
-    {
-      auto sc = timer_.scope("fft_r2c_z", (b ? 2 : 1) * U + Hb);
-      fft_r2c_z<T>(f, a, alpha, b, beta, S, zh);
-    }
-    auto sc = timer_.scope("fft_y", 2 * Hb);
-    fft_y<T>(f, S, true);
-  }
-  void c2r_yz(const FftArgs<T>& f, cx<T>* S, T* out, const T* aux, T beta_aux, double U,
-              double Hb, bool slab) {
-    if (!aux && fft_zy_fused<T>(f.n)) {
-      auto sc = timer_.scope("fft_c2r_yz", Hb + U);
-      fft_c2r_yz<T>(f, S, out, slab);
-      return;
-    }
-    {
+    for (int j = 0; j < m; ++j) {
+      {
+        auto sc = timer_.scope("fft_r2c_z", (in[j].b ? 2 : 1) * U + Hb);
+        fft_r2c_z<T>(f, in[j].a, in[j].alpha, in[j].b, in[j].beta, S[j], in[j].zh);
+      }
       auto sc = timer_.scope("fft_y", 2 * Hb);
-      fft_y<T>(f, S, false);
+      fft_y<T>(f, S[j], true);
     }
-    auto sc = timer_.scope("fft_c2r_z", Hb + (aux ? 2 : 1) * U);
-    fft_c2r_z<T>(f, S, out, T(1), aux, beta_aux, slab);
   }
-
-  struct GIn {
-    const T* a;
-    T alpha;
-    const T* b;
-    T beta;
-    const T* zh;  // a paint's z halo added to a (nullable)
-  };
+  // The inverse passes of m spectra; aux (times beta_aux) is added to the first.
+  void c2r_yz(const FftArgs<T>& f, cx<T>* const* S, T* const* outs, int m, const T* aux,
+              T beta_aux, double U, double Hb, bool slab) {
+    if (fft_zy_fused<T>(f.n, aux != nullptr)) {
+      auto sc = timer_.scope("fft_c2r_yz", m * (Hb + U) + (aux ? U : 0));
+      PlaneInv<T> fl[kMaxMul];
+      for (int j = 0; j < m; ++j)
+        fl[j] = PlaneInv<T>{S[j], outs[j], j == 0 ? aux : nullptr, beta_aux};
+      fft_c2r_yz<T>(f, fl, m, slab);
+      return;
+    }
+    for (int j = 0; j < m; ++j) {
+      const T* ax = j == 0 ? aux : nullptr;
+      {
+        auto sc = timer_.scope("fft_y", 2 * Hb);
+        fft_y<T>(f, S[j], false);
+      }
+      auto sc = timer_.scope("fft_c2r_z", Hb + (ax ? 2 : 1) * U);
+      fft_c2r_z<T>(f, S[j], outs[j], T(1), ax, beta_aux, slab);
+    }
+  }
 
   // out = sum_j Op_{spec_j}[alpha_j a_j + beta_j b_j] + beta_aux aux.
   void chain_gather(int grid, const GIn* ins, const MulSpec* specs, int m, T* out, const T* aux,
@@ -880,17 +901,16 @@ class Engine final : public EngineBase {
     const long long H = grid ? Hm_ : Hp_;
     const double U = (double)(grid ? M_ : P_) * sizeT();
     const double Hb = half_spectrum_bytes(f.n);
+    cx<T>* S[kMaxMul];
     const cx<T>* Si[kMaxMul];
-    for (int j = 0; j < m; ++j) {
-      cx<T>* Sj = pool_ + j * H;
-      r2c_zy(f, ins[j].a, ins[j].alpha, ins[j].b, ins[j].beta, Sj, ins[j].zh, U, Hb);
-      Si[j] = Sj;
-    }
+    for (int j = 0; j < m; ++j) Si[j] = S[j] = pool_ + j * H;
+    r2c_zy(f, ins, S, m, U, Hb);
     {
       auto sc = timer_.scope("fft_x_gather", (1 + m) * Hb);
       fft_x_gather<T>(f, Si, specs, m, pool_);
     }
-    c2r_yz(f, pool_, out, aux, beta_aux, U, Hb, grid == 1);
+    T* const outs[1] = {out};
+    c2r_yz(f, S, outs, 1, aux, beta_aux, U, Hb, grid == 1);
   }
 
   // -------------------------------------------------------------- forward

@@ -10,8 +10,9 @@
 // one kernel runs the forward x FFT, multiplies by m multipliers and runs m
 // inverse x FFTs (scatter), or the reverse for m inputs summed into one
 // output (gather).  Inverse passes are unnormalised; the 1/n^3 of the
-// inverse real DFT is folded into the multiplier scale.  For FP32 at n = 256
-// the z and y passes also run fused, one x plane per workgroup.
+// inverse real DFT is folded into the multiplier scale.  Where an x plane of the
+// half spectrum fits a workgroup the z and y passes run fused, several fields
+// per launch.
 #pragma once
 
 #include "common.h"
@@ -75,20 +76,41 @@ template <typename T>
 void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* aux, T beta,
                bool slab = false);
 
-// Whether the fused z and y passes below serve grid side n at this precision.
+// One field of a fused z and y pass: forward, the half spectrum S of
+// alpha (a + zh) + beta b transformed along z and y; inverse, the real field
+// out = (inverse of S) + beta_aux aux.
 template <typename T>
-bool fft_zy_fused(int n);
-
-// fft_r2c_z then the forward fft_y in one pass (where fft_zy_fused).
+struct PlaneFwd {
+  const T* a;
+  T alpha;
+  const T* b;    // nullable (all fields of one call alike)
+  T beta;
+  const T* zh;   // a paint's z halo, a then in slabs (nullable, all alike)
+  cx<T>* S;
+};
 template <typename T>
-void fft_r2c_zy(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* out,
-                const T* zh = nullptr);
+struct PlaneInv {
+  const cx<T>* S;
+  T* out;
+  const T* aux;  // nullable
+  T beta_aux;
+};
 
-// The inverse fft_y then fft_c2r_z (alpha 1, no aux) in one pass (where
-// fft_zy_fused), for the spectrum of a real field: its kz = 0 and kz = n/2
+// Whether the fused z and y passes below serve grid side n at this precision
+// (n <= 128, and 256 in FP32); with_aux: also with fields added to the result
+// (n <= 128).
+template <typename T>
+bool fft_zy_fused(int n, bool with_aux = false);
+
+// fft_r2c_z then the forward fft_y of m fields in one launch (where fft_zy_fused).
+template <typename T>
+void fft_r2c_zy(const FftArgs<T>& f, const PlaneFwd<T>* fields, int m);
+
+// The inverse fft_y then fft_c2r_z of m fields in one launch (where
+// fft_zy_fused), for spectra of real fields: their kz = 0 and kz = n/2
 // columns must be Hermitian along y (their inverse along y real).
 template <typename T>
-void fft_c2r_yz(const FftArgs<T>& f, const cx<T>* in, T* out, bool slab = false);
+void fft_c2r_yz(const FftArgs<T>& f, const PlaneInv<T>* fields, int m, bool slab);
 
 // In-place complex FFT along y of the half spectrum (forward or inverse, unnormalised).
 template <typename T>

@@ -155,11 +155,10 @@ __device__ __forceinline__ void stage(int lane, int Ns, const cx<T>* __restrict_
 // Full length-n transform: first stage from load0, intermediate stages in
 // the LDS buffer buf (element e of this thread's line at buf[lidx(e)]), last
 // stage to storeL.
-template <typename T, int n, bool FWD, class Load, class Store, class LIdx>
+template <typename T, int n, bool FWD, class P = Plan<n>, class Load, class Store, class LIdx>
 __device__ __forceinline__ void fft_line(int lane, cx<T>* buf, LIdx lidx,
                                          const cx<T>* __restrict__ tw, int tws, Load&& load0,
                                          Store&& storeL) {
-  using P = Plan<n>;
   constexpr int TPL = P::TPL;
   auto ld = [&](int e) { return buf[lidx(e)]; };
   auto st = [&](int e, cx<T> v) { buf[lidx(e)] = v; };
@@ -496,6 +495,16 @@ __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_c2r_z(
   fft_line<T, n, false>(lane, buf, lidx, tw, 2, load0, storeL);
 }
 
+// The fields of one fused launch, one per blockIdx.y.
+template <typename T>
+struct FwdSet {
+  PlaneFwd<T> f[kMaxMul];
+};
+template <typename T>
+struct InvSet {
+  PlaneInv<T> f[kMaxMul];
+};
+
 // ------------------------------------------ fused z and y passes (FP32, n = 256)
 // One workgroup transforms a whole x plane along z and y, so the plane's half
 // spectrum crosses HBM once instead of three times.  The plane (256 rows y of
@@ -533,11 +542,14 @@ struct ZYCfg<float, 256> {
 
 template <typename T, int N, bool ZH, bool B>
 __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_r2c_zy(
-    const T* __restrict__ a, T alpha, const T* __restrict__ b, T beta,
-    cx<T>* __restrict__ out, const cx<T>* __restrict__ twg, int kp,
-    const T* __restrict__ zh) {
+    FwdSet<T> fields, const cx<T>* __restrict__ twg, int kp) {
   using C = ZYCfg<T, N>;
   constexpr int n = C::n;
+  const T* __restrict__ a = fields.f[blockIdx.y].a;
+  const T* __restrict__ b = fields.f[blockIdx.y].b;
+  const T* __restrict__ zh = fields.f[blockIdx.y].zh;
+  const T alpha = fields.f[blockIdx.y].alpha, beta = fields.f[blockIdx.y].beta;
+  cx<T>* __restrict__ out = fields.f[blockIdx.y].S;
   __shared__ cx<T> buf[n * C::LS];
   __shared__ cx<T> tw[N];
   __shared__ cx<T> pk[2 * n];  // the packed column's even and odd outputs
@@ -664,9 +676,11 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_r2c_zy(
 
 template <typename T, int N, bool SLAB>
 __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
-    const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ twg, int kp) {
+    InvSet<T> fields, const cx<T>* __restrict__ twg, int kp) {
   using C = ZYCfg<T, N>;
   constexpr int n = C::n;
+  const cx<T>* __restrict__ in = fields.f[blockIdx.y].S;
+  T* __restrict__ out = fields.f[blockIdx.y].out;
   __shared__ cx<T> buf[n * C::LS];
   __shared__ cx<T> tw[N];
   load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
@@ -745,6 +759,183 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
   }
 }
 
+// ------------------------------------------- fused z and y passes (n <= 128)
+// A plane x = const of the half spectrum, N rows of N/2 complex values with the
+// columns kz = 0 and N/2 packed into one as above, fits the LDS of one
+// workgroup (143 KiB at N = 128 in FP64), so the z and y passes of a field are
+// one kernel that crosses HBM once each way, and all fields of a chain go in
+// one launch.  At 32^3 and 64^3 every launch takes 3-4 us whatever it does:
+// there the launches saved count (nine per force chain become three); at
+// 128^3 the two passes saved do as well: three fields take 41 us instead of 55
+// in FP64.  A 32^3 FP64 evaluation went from 1244 to 790 us, a 64^3 FP32 forward
+// run from 1245 to 832, a 128^3 FP64 forward run and gradient from 10.25 to
+// 9.47 ms.
+//
+// PlanY: the radix plan of the y transforms.  In FP64 at N = 128 one workgroup
+// fills a CU's LDS, so it takes 1024 threads (eight values each, radix 8 4 4).
+template <typename T, int N> struct PlanY : Plan<N> {};
+template <> struct PlanY<double, 128> {
+  static constexpr int R0 = 8, R1 = 4, R2 = 4;
+  static constexpr int S = 3;
+  static constexpr int RMAX = 8;
+  static constexpr int TPL = 128 / RMAX;
+};
+template <typename T, int N>
+struct PlCfg {
+  static constexpr int n = N / 2;
+  static constexpr int TZ = Plan<n>::TPL, TY = PlanY<T, N>::TPL;
+  static constexpr int T0 = N * TZ > n * TY ? N * TZ : n * TY;
+  static constexpr int TMAX = TY * n > 512 ? TY * n : 512;
+  static constexpr int THREADS = T0 > TMAX ? TMAX : T0;
+  static constexpr int ROWS = THREADS / TZ;                  // z transforms per round
+  static constexpr int ROUNDS = N > ROWS ? N / ROWS : 1;
+  static constexpr int TROWS = ROWS > N ? ROWS : N;          // tile rows (idle lanes have theirs)
+  static constexpr int COLS = THREADS / TY;                  // y transforms at a time
+  static constexpr int W = COLS > n ? COLS : n;
+  static constexpr int LS = W + W / 16 + 2;                  // tile row stride
+  static_assert(COLS >= n, "all columns in one round");
+};
+
+template <typename T, int N, bool ZH, bool B>
+__global__ __launch_bounds__((PlCfg<T, N>::THREADS)) void k_plane_fwd(
+    FwdSet<T> fields, const cx<T>* __restrict__ twg, int kp) {
+  using C = PlCfg<T, N>;
+  constexpr int n = C::n;
+  __shared__ cx<T> buf[C::TROWS * C::LS];
+  __shared__ cx<T> tw[N];
+  __shared__ cx<T> pk[N];  // the packed column's outputs
+  load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
+  const PlaneFwd<T>& fl = fields.f[blockIdx.y];
+  const T* __restrict__ zh = fl.zh;
+  const T alpha = fl.alpha, beta = fl.beta;
+  cx<T>* __restrict__ out = fl.S;
+  const int t = threadIdx.x;
+  const size_t x = blockIdx.x;
+  const int lane = t % C::TZ, l0 = t / C::TZ;
+  const T half = static_cast<T>(0.5);
+  for (int h = 0; h < C::ROUNDS; ++h) {
+    const int l = h * C::ROWS + l0;                       // tile row
+    const size_t line = x * N + (l < N ? l : 0);          // idle lanes transform row 0 again
+    const RowPairs<T, N, ZH, C::TZ> ra(fl.a, x * N, line, lane);
+    const RowPairs<T, N, false, C::TZ> rb(fl.b, x * N, line, lane);
+    auto load0 = [&](int e) -> cx<T> {
+      return r2c_elem<T, N, ZH, B>(ra, rb, zh, line, e, alpha, beta);
+    };
+    cx<T>* lb = buf + l * C::LS;
+    auto lidx = [&](int e) { return l * C::LS + zl(e); };
+    auto storeL = [&](int e, cx<T> v) { lb[zl(e)] = v; };
+    fft_line<T, n, true>(lane, buf, lidx, tw, 2, load0, storeL);
+  }
+  __syncthreads();
+  // the real transforms' split, in place (see k_r2c_zy)
+  for (int h = 0; h < C::ROUNDS; ++h) {
+    cx<T>* lb = buf + (h * C::ROWS + l0) * C::LS;
+    for (int k = lane; k <= n / 2; k += C::TZ) {
+      const cx<T> zk = lb[zl(k)];
+      if (k == 0) {
+        lb[zl(0)] = mkc<T>(zk.x + zk.y, zk.x - zk.y);
+        continue;
+      }
+      const cx<T> zm = lb[zl(n - k)];
+      auto split = [&](cx<T> p, cx<T> q, int j) {
+        const cx<T> qc = cconj<T>(q);
+        const cx<T> e = cscale<T>(cadd<T>(p, qc), half);
+        const cx<T> d = cscale<T>(csub<T>(p, qc), half);
+        return cadd<T>(e, cmul<T>(tw[j], mkc<T>(d.y, -d.x)));
+      };
+      lb[zl(k)] = split(zk, zm, k);
+      if (k != n / 2) lb[zl(n - k)] = split(zm, zk, n - k);
+    }
+  }
+  __syncthreads();
+  const int c = t % C::COLS, r0 = t / C::COLS;
+  auto cidx = [&](int e) { return e * C::LS + zl(c); };
+  auto cload = [&](int e) { return buf[cidx(e)]; };
+  auto storeC = [&](int e, cx<T> v) {
+    if (c == 0)
+      pk[e] = v;
+    else if (c < n)
+      out[(x * N + e) * kp + c] = v;
+  };
+  fft_line<T, N, true, PlanY<T, N>>(r0, buf, cidx, tw, 1, cload, storeC);
+  __syncthreads();
+  for (int e = t; e < N; e += C::THREADS) {
+    const cx<T> cc = pk[e], cm = cconj<T>(pk[(N - e) & (N - 1)]);
+    const cx<T> s = cadd<T>(cc, cm), d = csub<T>(cc, cm);
+    cx<T>* o = out + (x * N + e) * kp;
+    o[0] = cscale<T>(s, half);
+    o[n] = mkc<T>(half * d.y, -half * d.x);
+  }
+}
+
+template <typename T, int N, bool SLAB>
+__global__ __launch_bounds__((PlCfg<T, N>::THREADS)) void k_plane_inv(
+    InvSet<T> fields, const cx<T>* __restrict__ twg, int kp) {
+  using C = PlCfg<T, N>;
+  constexpr int n = C::n;
+  __shared__ cx<T> buf[C::TROWS * C::LS];
+  __shared__ cx<T> tw[N];
+  load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
+  const PlaneInv<T>& fl = fields.f[blockIdx.y];
+  const int t = threadIdx.x;
+  const size_t x = blockIdx.x;
+  {
+    const int c = t % C::COLS, r0 = t / C::COLS;
+    const int ci = c < n ? c : n - 1, cj = c == 0 ? n : ci;
+    const cx<T>* __restrict__ in = fl.S + x * N * kp;
+    auto load0 = [&](int e) -> cx<T> {  // both loads for every column: no branch
+      const cx<T> u = in[e * kp + ci], v = in[e * kp + cj];
+      return c != 0 ? u : mkc<T>(u.x - v.y, u.y + v.x);
+    };
+    auto cidx = [&](int e) { return e * C::LS + zl(c); };
+    auto cstore = [&](int e, cx<T> v) { buf[cidx(e)] = v; };
+    fft_line<T, N, false, PlanY<T, N>>(r0, buf, cidx, tw, 1, load0, cstore);
+  }
+  __syncthreads();
+  const int lane = t % C::TZ, l0 = t / C::TZ;
+  // the real inverse's merge Z[e] = S + i W^-e D, S, D = X[e] +- conj X[n - e]
+  auto merge = [&](cx<T> xk, cx<T> xc, int e) {
+    const cx<T> s = cadd<T>(xk, xc);
+    const cx<T> d = csub<T>(xk, xc);
+    const cx<T> wd = cmul<T>(cconj<T>(tw[e]), d);
+    return mkc<T>(s.x - wd.y, s.y + wd.x);
+  };
+  for (int h = 0; h < C::ROUNDS; ++h) {
+    cx<T>* lb = buf + (h * C::ROWS + l0) * C::LS;
+    for (int k = lane; k <= n / 2; k += C::TZ) {
+      const cx<T> xk = lb[zl(k)];
+      if (k == 0) {
+        lb[zl(0)] = merge(mkc<T>(xk.x, 0), mkc<T>(xk.y, 0), 0);
+        continue;
+      }
+      const cx<T> xm = lb[zl(n - k)];
+      lb[zl(k)] = merge(xk, cconj<T>(xm), k);
+      if (k != n / 2) lb[zl(n - k)] = merge(xm, cconj<T>(xk), n - k);
+    }
+  }
+  __syncthreads();
+  const T* __restrict__ aux = fl.aux;
+  const T beta = fl.beta_aux;
+  for (int h = 0; h < C::ROUNDS; ++h) {
+    const int l = h * C::ROWS + l0;
+    const size_t line = x * N + (l < N ? l : 0);
+    const cx<T>* lb = buf + l * C::LS;
+    const RowPairs<T, N, SLAB, C::TZ> dst(fl.out, x * N, line, lane);
+    auto lidx = [&](int e) { return l * C::LS + zl(e); };
+    auto lload = [&](int e) { return lb[zl(e)]; };
+    auto storeL = [&](int e, cx<T> v) {
+      if (l >= N) return;
+      if (aux) {
+        const cx<T> u = reinterpret_cast<const cx<T>*>(aux)[line * n + e];
+        v.x += beta * u.x;
+        v.y += beta * u.y;
+      }
+      dst(e) = v;
+    };
+    fft_line<T, n, false>(lane, buf, lidx, tw, 2, lload, storeL);
+  }
+}
+
 // ------------------------------------------------- strided C2C (y or x)
 // Line L of the batch starts at (L / group) * gstride + L % group and its
 // elements are estride apart; lines with L mod vmod >= vcnt are row padding
@@ -812,7 +1003,9 @@ struct InPtrs {
 };
 
 // Forward x FFT, then m inverse x FFTs of the multiplied spectrum; the
-// forward result stays in registers (XPlan layout) across the m inverses.
+// forward result stays in registers (XPlan layout) across the m inverses.  On
+// grids too small to fill the chip (fft_x_scatter) the outputs are dealt over
+// blockIdx.y and each workgroup repeats the forward transform.
 template <typename T, int N>
 __global__ __launch_bounds__((FCfg<T, N>::THREADS), (FCfg<T, N>::MINW)) void k_x_scatter(
     const cx<T>* __restrict__ in, OutPtrs<T> outs, MulSet ms, int m,
@@ -835,7 +1028,7 @@ __global__ __launch_bounds__((FCfg<T, N>::THREADS), (FCfg<T, N>::MINW)) void k_x
   auto load_in = [&](int e) -> cx<T> { return valid ? in[line + e * stride] : mkc<T>(0, 0); };
   cx<T> V[X::BPT][X::RL];
   fft_fwd_to_regs<T, N, PlanX<N>>(lane, B, lidx, tw, load_in, V);
-  for (int j = 0; j < m; ++j) {
+  for (int j = blockIdx.y; j < m; j += gridDim.y) {
     cx<T> W[X::BPT][X::RL];
 #pragma unroll
     for (int b = 0; b < X::BPT; ++b) {
@@ -901,6 +1094,66 @@ __global__ __launch_bounds__((FCfg<T, N, PlanG<N>>::THREADS)) void k_x_gather(
     if (valid) out[line + e * stride] = v;
   };
   fft_inv_from_regs<T, N, PlanG<N>>(lane, B, lidx, tw, acc, store_o);
+}
+
+// The gather of grids too small to fill the chip: thread group j of the
+// workgroup takes input j through its forward transform in an LDS tile of its
+// own, every group then sums all tiles (in the order of the inputs, as above)
+// and inverts, and the first one stores.  The m transforms run side by side
+// instead of one after the other.
+template <typename T, int N>
+__global__ __launch_bounds__(1024) void k_x_gather_wide(
+    InPtrs<T> ins, MulSet ms, int m, cx<T>* out, const T* __restrict__ wtab, T L_over_2pi,
+    const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
+  using C = FCfg<T, N, PlanG<N>>;
+  using X = XPlan<N, PlanG<N>>;
+  extern __shared__ char smem[];
+  cx<T>* tw = reinterpret_cast<cx<T>*>(smem);
+  cx<T>* tiles = tw + N;
+  load_table<T>(tw, twg, N);
+  const int j = threadIdx.x / C::THREADS, t = threadIdx.x % C::THREADS;
+  cx<T>* B = tiles + j * N * C::LP;
+  const int l = t % C::LINES;
+  const int lane = t / C::LINES;
+  const int line = blockIdx.x * C::LINES + l;
+  const int ky = line / kp, kz = line % kp;
+  const bool valid = line < nlines && kz < K;
+  const long long stride = (long long)nlines;  // = N * kp
+  const int iy = wave_index(ky, N), iz = kz;
+  const int dy = (ky == N / 2) ? 0 : iy, dz = (kz == N / 2) ? 0 : iz;
+  auto lidx = [&](int e) { return e * C::LP + l; };
+  const cx<T>* src = ins.p[j];
+  auto load_in = [&](int e) -> cx<T> { return valid ? src[line + e * stride] : mkc<T>(0, 0); };
+  cx<T> V[X::BPT][X::RL];
+  fft_fwd_to_regs<T, N, PlanG<N>>(lane, B, lidx, tw, load_in, V);
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < X::BPT; ++b) {
+#pragma unroll
+    for (int r = 0; r < X::RL; ++r) {
+      const int e = lane + b * X::TPL + r * X::NBL;
+      const int ix = wave_index(e, N);
+      const int n2 = ix * ix + iy * iy + iz * iz;
+      B[lidx(e)] = apply_mult<T>(V[b][r], ms, j, n2, (e == N / 2) ? 0 : ix, dy, dz, wtab,
+                                 L_over_2pi);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < X::BPT; ++b) {
+#pragma unroll
+    for (int r = 0; r < X::RL; ++r) {
+      const int i = lidx(lane + b * X::TPL + r * X::NBL);
+      cx<T> a = tiles[i];
+      for (int q = 1; q < m; ++q) a = cadd<T>(a, tiles[q * N * C::LP + i]);
+      V[b][r] = a;
+    }
+  }
+  __syncthreads();
+  auto store_o = [&](int e, cx<T> v) {
+    if (valid && j == 0) out[line + e * stride] = v;
+  };
+  fft_inv_from_regs<T, N, PlanG<N>>(lane, B, lidx, tw, V, store_o);
 }
 
 // ------------------------------------------------- layout conversion
@@ -1003,41 +1256,77 @@ void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* a
 }
 
 template <typename T>
-bool fft_zy_fused(int n) {
-  return fftk::ZYCfg<T, 256>::ok && n == 256;
+bool fft_zy_fused(int n, bool with_aux) {
+  return n <= 128 || (!with_aux && fftk::ZYCfg<T, 256>::ok && n == 256);
+}
+
+// f(integral_constant<N>) for the sides of the fused planes.
+template <class F>
+void dispatch_plane(int n, F&& f) {
+  switch (n) {
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    case 16: f(std::integral_constant<int, 16>{}); break;
+    case 32: f(std::integral_constant<int, 32>{}); break;
+    case 64: f(std::integral_constant<int, 64>{}); break;
+    case 128: f(std::integral_constant<int, 128>{}); break;
+    default: throw ApiError(-2, "fused z and y passes: n <= 128, and 256 in FP32");
+  }
 }
 
 template <typename T>
-void fft_r2c_zy(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* out,
-                const T* zh) {
-  if constexpr (fftk::ZYCfg<T, 256>::ok) {
-    if (f.n == 256) {
-      using C = fftk::ZYCfg<T, 256>;
-      fftk::with_flags(zh != nullptr, b != nullptr, [&](auto ZH, auto B) {
+void fft_r2c_zy(const FftArgs<T>& f, const PlaneFwd<T>* fields, int m) {
+  if (m < 1 || m > kMaxMul) throw ApiError(-1, "field count out of range");
+  fftk::FwdSet<T> set{};
+  for (int j = 0; j < m; ++j) set.f[j] = fields[j];
+  const dim3 grid(f.n, m);
+  fftk::with_flags(fields[0].zh != nullptr, fields[0].b != nullptr, [&](auto ZH, auto B) {
+    if constexpr (fftk::ZYCfg<T, 256>::ok) {
+      if (f.n == 256) {
+        using C = fftk::ZYCfg<T, 256>;
         fftk::k_r2c_zy<T, 256, ZH.value, B.value>
-            <<<f.n, C::THREADS, 0, f.stream>>>(a, alpha, b, beta, out, f.tw, f.kp, zh);
-      });
-      IC_LAUNCHED();
-      return;
+            <<<grid, C::THREADS, 0, f.stream>>>(set, f.tw, f.kp);
+        return;
+      }
     }
-  }
-  throw ApiError(-2, "fused z and y passes: FP32 at n = 256 only");
+    dispatch_plane(f.n, [&](auto NC) {
+      constexpr int N = decltype(NC)::value;
+      fftk::k_plane_fwd<T, N, ZH.value, B.value>
+          <<<grid, fftk::PlCfg<T, N>::THREADS, 0, f.stream>>>(set, f.tw, f.kp);
+    });
+  });
+  IC_LAUNCHED();
 }
 
 template <typename T>
-void fft_c2r_yz(const FftArgs<T>& f, const cx<T>* in, T* out, bool slab) {
-  if constexpr (fftk::ZYCfg<T, 256>::ok) {
-    if (f.n == 256) {
-      using C = fftk::ZYCfg<T, 256>;
-      if (slab)
-        fftk::k_c2r_yz<T, 256, true><<<f.n, C::THREADS, 0, f.stream>>>(in, out, f.tw, f.kp);
-      else
-        fftk::k_c2r_yz<T, 256, false><<<f.n, C::THREADS, 0, f.stream>>>(in, out, f.tw, f.kp);
-      IC_LAUNCHED();
-      return;
-    }
+void fft_c2r_yz(const FftArgs<T>& f, const PlaneInv<T>* fields, int m, bool slab) {
+  if (m < 1 || m > kMaxMul) throw ApiError(-1, "field count out of range");
+  fftk::InvSet<T> set{};
+  bool aux = false;
+  for (int j = 0; j < m; ++j) {
+    set.f[j] = fields[j];
+    aux = aux || fields[j].aux;
   }
-  throw ApiError(-2, "fused y and z passes: FP32 at n = 256 only");
+  if (!fft_zy_fused<T>(f.n, aux)) throw ApiError(-2, "fused y and z passes: unsupported");
+  const dim3 grid(f.n, m);
+  auto launch = [&](auto SL) {
+    if constexpr (fftk::ZYCfg<T, 256>::ok) {
+      if (f.n == 256) {
+        using C = fftk::ZYCfg<T, 256>;
+        fftk::k_c2r_yz<T, 256, SL.value><<<grid, C::THREADS, 0, f.stream>>>(set, f.tw, f.kp);
+        return;
+      }
+    }
+    dispatch_plane(f.n, [&](auto NC) {
+      constexpr int N = decltype(NC)::value;
+      fftk::k_plane_inv<T, N, SL.value>
+          <<<grid, fftk::PlCfg<T, N>::THREADS, 0, f.stream>>>(set, f.tw, f.kp);
+    });
+  };
+  if (slab)
+    launch(std::true_type{});
+  else
+    launch(std::false_type{});
+  IC_LAUNCHED();
 }
 
 template <typename T>
@@ -1092,6 +1381,10 @@ void spectrum_unpack(const FftArgs<T>& f, const cx<T>* dense, cx<T>* stored) {
   IC_LAUNCHED();
 }
 
+// Workgroups of an x pass up to which it counts as small: the chip has 256 CUs,
+// and a pass over m fields then spreads them over more workgroups or threads.
+constexpr unsigned kSmallGrid = 512;
+
 template <typename T>
 void fft_x_scatter(const FftArgs<T>& f, const cx<T>* in, cx<T>* const* outs,
                    const MulSpec* specs, int m) {
@@ -1104,8 +1397,11 @@ void fft_x_scatter(const FftArgs<T>& f, const cx<T>* in, cx<T>* const* outs,
     using C = fftk::FCfg<T, N>;
     const int K = N / 2 + 1;
     const int nlines = N * f.kp;
-    fftk::k_x_scatter<T, N><<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(
-        in, op, ms, m, f.wtab, l2p, f.tw, nlines, K, f.kp);
+    const unsigned blocks = blocks_for(nlines, C::LINES);
+    // fewer workgroups than CUs: one output per workgroup
+    const dim3 grid(blocks, blocks <= kSmallGrid ? m : 1);
+    fftk::k_x_scatter<T, N><<<grid, C::THREADS, 0, f.stream>>>(in, op, ms, m, f.wtab, l2p, f.tw,
+                                                               nlines, K, f.kp);
   });
   IC_LAUNCHED();
 }
@@ -1122,8 +1418,17 @@ void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const MulSpec* s
     using C = fftk::FCfg<T, N, fftk::PlanG<N>>;
     const int K = N / 2 + 1;
     const int nlines = N * f.kp;
-    fftk::k_x_gather<T, N><<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(
-        ip, ms, m, out, f.wtab, l2p, f.tw, nlines, K, f.kp);
+    const unsigned blocks = blocks_for(nlines, C::LINES);
+    if constexpr (N <= 64) {
+      if (m > 1 && blocks <= kSmallGrid && C::THREADS * m <= 1024) {
+        const size_t lds = sizeof(cx<T>) * (N + (size_t)m * N * C::LP);
+        fftk::k_x_gather_wide<T, N><<<blocks, C::THREADS * m, lds, f.stream>>>(
+            ip, ms, m, out, f.wtab, l2p, f.tw, nlines, K, f.kp);
+        return;
+      }
+    }
+    fftk::k_x_gather<T, N><<<blocks, C::THREADS, 0, f.stream>>>(ip, ms, m, out, f.wtab, l2p,
+                                                                f.tw, nlines, K, f.kp);
   });
   IC_LAUNCHED();
 }

@@ -34,13 +34,15 @@ SCOPES = {
     "k_data_adjoint_b": "data_adjoint",
     "k_paint_b": "cic_paint",
     "k_scatter": "sort_scatter",
-    "k_scatter_ids": "sort_scatter_ids",
+    "k_scatter_ids_b": "sort_scatter_ids",
     "k_gather_back": "sort_gather_back",
     "k_keys": "sort_keys",
     "k_r2c_z": "fft_r2c_z",
     "k_c2r_z": "fft_c2r_z",
     "k_r2c_zy": "fft_r2c_zy",
     "k_c2r_yz": "fft_c2r_yz",
+    "k_plane_fwd": "fft_r2c_zy",
+    "k_plane_inv": "fft_c2r_yz",
     "k_strided": "fft_y",
     "k_x_scatter": "fft_x_scatter",
     "k_x_gather": "fft_x_gather",
