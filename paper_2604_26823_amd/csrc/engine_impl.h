@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "../../include/ic_ops.h"
 #include "cosmo.h"
 #include "engine.h"
 #include "fft.h"
@@ -368,14 +369,13 @@ class Engine final : public EngineBase {
 
   void op_multiplier(int kinds, int a, int b, const void* x, void* y) override {
     if (a < 0 || a > 2 || b < 0 || b > 2) throw ApiError(IC_ERR_INVALID_ARG, "axis out of range");
-    MulSpec sp;
-    sp.kinds = kinds;
-    sp.ga = a;
-    sp.ha = a;
-    sp.hb = b;
-    sp.scale = 1.0 / (double)P_;
+    Mul mul;
+    mul.scale = 1.0 / (double)P_;
+    if (kinds & IC_MULT_WHITE) mul.white = 1;
+    if (kinds & IC_MULT_GRAD) mul = times(mul, grad(a, 1.0));
+    if (kinds & IC_MULT_HESS) mul = times(mul, hess(a, b, 1.0));
     T* outs[1] = {static_cast<T*>(y)};
-    chain_scatter(0, static_cast<const T*>(x), T(1), nullptr, T(0), outs, &sp, 1);
+    chain_scatter(0, static_cast<const T*>(x), outs, &mul, 1);
   }
 
   void op_paint(int grid, const void* disp, void* rho) override {
@@ -804,14 +804,37 @@ class Engine final : public EngineBase {
   }
 
   // ------------------------------------------------------ k-space chains
-  static MulSpec spec(int kinds, int a, int b, double scale) {
-    MulSpec s;
-    s.kinds = kinds;
-    s.ga = a;
-    s.ha = a;
-    s.hb = b;
-    s.scale = scale;
-    return s;
+  // scale i k~_a / k^2 (wave numbers in units of the fundamental inside Mul).
+  Mul grad(int a, double scale, int white = 0) const {
+    Mul m;
+    m.scale = scale * prob_.box / (2.0 * 3.14159265358979323846);
+    m.white = white;
+    m.div = 1;
+    m.imag = 1;
+    (a == 0 ? m.px : a == 1 ? m.py : m.pz) = 1;
+    return m;
+  }
+  // scale k~_a k~_b / k^2.
+  static Mul hess(int a, int b, double scale, int white = 0) {
+    Mul m;
+    m.scale = scale;
+    m.white = white;
+    m.div = 1;
+    m.px = (a == 0) + (b == 0);
+    m.py = (a == 1) + (b == 1);
+    m.pz = (a == 2) + (b == 2);
+    return m;
+  }
+  // The product of two multipliers, at most one of them with the factor i.
+  static Mul times(Mul a, const Mul& b) {
+    a.scale *= b.scale;
+    a.white |= b.white;
+    a.div += b.div;
+    a.px += b.px;
+    a.py += b.py;
+    a.pz += b.pz;
+    a.imag |= b.imag;
+    return a;
   }
 
   struct GIn {
@@ -822,26 +845,57 @@ class Engine final : public EngineBase {
     const T* zh;  // a paint's z halo added to a (nullable)
   };
 
-  // outs[j] = Op_{spec_j}[alpha (a + zh) + beta b] on the chosen grid (zh:
-  // a paint's z halo).  Fields of the force mesh (grid 1) are painted ones with
-  // their z halo going in and particle windows' fields coming out, in slabs.
-  void chain_scatter(int grid, const T* a, T alpha, const T* b, T beta, T* const* outs,
-                     const MulSpec* specs, int m, const T* zh = nullptr) {
+  // One real output of a chain: an x pass's spectrum, the rest of its multiplier.
+  struct YOut {
+    cx<T>* S;
+    YZMul<T> mul;
+    T* out;
+  };
+
+  // The x-pass outputs that m multipliers with common white and div need (one per
+  // power of k~x, spectra from S on, H apart, each scaled like its first
+  // multiplier) and the real outputs made of them.
+  static int classes(const Mul* muls, int m, T* const* outs, cx<T>* S, long long H, XOut<T>* xo,
+                     YOut* yo) {
+    int nx = 0;
+    double first[4];
+    int at[4] = {-1, -1, -1, -1};
+    for (int j = 0; j < m; ++j) {
+      const Mul& u = muls[j];
+      if (u.white != muls[0].white || u.div != muls[0].div)
+        throw ApiError(IC_ERR_STATE, "multipliers of a chain share w and |k|^-2");
+      if (at[u.px] < 0) {
+        at[u.px] = nx;
+        first[u.px] = u.scale;
+        xo[nx] = XOut<T>{S + nx * H, u.scale, 0.0, u.px};
+        ++nx;
+      }
+      yo[j] = YOut{xo[at[u.px]].S, yz_mul<T>(u.scale / first[u.px], u.py, u.pz, u.imag), outs[j]};
+    }
+    return nx;
+  }
+
+  // outs[j] = Op_{mul_j}[a + zh] on the chosen grid.  Fields of the force mesh
+  // (grid 1) are painted ones with their z halo zh going in and particle
+  // windows' fields coming out, in slabs.
+  void chain_scatter(int grid, const T* a, T* const* outs, const Mul* muls, int m,
+                     const T* zh = nullptr) {
     auto f = fa(grid);
     const long long H = grid ? Hm_ : Hp_;
     const double U = (double)(grid ? M_ : P_) * sizeT();
     const double Hb = half_spectrum_bytes(f.n);
-    cx<T>* S0 = pool_;
-    cx<T>* So[kMaxMul];
-    for (int j = 0; j < m; ++j) So[j] = pool_ + (j + 1) * H;
-    const GIn in{a, alpha, b, beta, zh};
-    cx<T>* const S[1] = {S0};
+    const GIn in{a, T(1), nullptr, T(0), zh};
+    cx<T>* const S[1] = {pool_};
     r2c_zy(f, &in, S, 1, U, Hb);
+    XOut<T> xo[kMaxXOut];
+    YOut yo[kMaxMul];
+    const int nx = classes(muls, m, outs, pool_ + H, H, xo, yo);
     {
-      auto sc = timer_.scope("fft_x_scatter", (1 + m) * Hb);
-      fft_x_scatter<T>(f, S0, So, specs, m);
+      auto sc = timer_.scope("fft_x_scatter", (1 + nx) * Hb);
+      const cx<T>* Si[1] = {pool_};
+      fft_x_scatter<T>(f, Si, &muls[0].white, 1, muls[0].div, xo, nx);
     }
-    c2r_yz(f, So, outs, m, nullptr, T(0), U, Hb, grid == 1);
+    c2r_yz(f, yo, m, pool_ + (1 + nx) * H, nullptr, T(0), U, Hb, grid == 1);
   }
 
   // The z and y passes of a chain's m fields: fused into one launch where the
@@ -872,14 +926,15 @@ class Engine final : public EngineBase {
       fft_y<T>(f, S[j], true);
     }
   }
-  // The inverse passes of m spectra; aux (times beta_aux) is added to the first.
-  void c2r_yz(const FftArgs<T>& f, cx<T>* const* S, T* const* outs, int m, const T* aux,
-              T beta_aux, double U, double Hb, bool slab) {
+  // The inverse passes to m real fields; aux (times beta_aux) is added to the
+  // first.  tmp: one spectrum (the spectra in yo may be shared).
+  void c2r_yz(const FftArgs<T>& f, const YOut* yo, int m, cx<T>* tmp, const T* aux, T beta_aux,
+              double U, double Hb, bool slab) {
     if (fft_zy_fused<T>(f.n, aux != nullptr)) {
       auto sc = timer_.scope("fft_c2r_yz", m * (Hb + U) + (aux ? U : 0));
       PlaneInv<T> fl[kMaxMul];
       for (int j = 0; j < m; ++j)
-        fl[j] = PlaneInv<T>{S[j], outs[j], j == 0 ? aux : nullptr, beta_aux};
+        fl[j] = PlaneInv<T>{yo[j].S, yo[j].mul, yo[j].out, j == 0 ? aux : nullptr, beta_aux};
       fft_c2r_yz<T>(f, fl, m, slab);
       return;
     }
@@ -887,15 +942,15 @@ class Engine final : public EngineBase {
       const T* ax = j == 0 ? aux : nullptr;
       {
         auto sc = timer_.scope("fft_y", 2 * Hb);
-        fft_y<T>(f, S[j], false);
+        fft_y_inv<T>(f, yo[j].S, tmp, yo[j].mul);
       }
       auto sc = timer_.scope("fft_c2r_z", Hb + (ax ? 2 : 1) * U);
-      fft_c2r_z<T>(f, S[j], outs[j], T(1), ax, beta_aux, slab);
+      fft_c2r_z<T>(f, tmp, yo[j].out, T(1), ax, beta_aux, slab);
     }
   }
 
-  // out = sum_j Op_{spec_j}[alpha_j a_j + beta_j b_j] + beta_aux aux.
-  void chain_gather(int grid, const GIn* ins, const MulSpec* specs, int m, T* out, const T* aux,
+  // out = sum_j Op_{mul_j}[alpha_j a_j + beta_j b_j] + beta_aux aux.
+  void chain_gather(int grid, const GIn* ins, const Mul* muls, int m, T* out, const T* aux,
                     T beta_aux) {
     auto f = fa(grid);
     const long long H = grid ? Hm_ : Hp_;
@@ -907,50 +962,66 @@ class Engine final : public EngineBase {
     r2c_zy(f, ins, S, m, U, Hb);
     {
       auto sc = timer_.scope("fft_x_gather", (1 + m) * Hb);
-      fft_x_gather<T>(f, Si, specs, m, pool_);
+      fft_x_gather<T>(f, Si, muls, m, pool_);
     }
-    T* const outs[1] = {out};
-    c2r_yz(f, S, outs, 1, aux, beta_aux, U, Hb, grid == 1);
+    const YOut yo{pool_, yz_one<T>(), out};
+    c2r_yz(f, &yo, 1, pool_, aux, beta_aux, U, Hb, grid == 1);
   }
 
   // -------------------------------------------------------------- forward
-  // 2LPT from white noise in lattice order: Psi1 -> d0, Psi2 -> p0, then
-  // assembled into the displacement d0 and momentum p0 at a_init.
+  // 2LPT from white noise in lattice order: the six second derivatives of the
+  // first-order potential, their product mu2, then the displacement
+  // d0 = D1 Psi1 + D2 Psi2 and momentum p0 = a^2 E (f1 D1 Psi1 + f2 D2 Psi2) at
+  // a_init, combined in k space: both are gradients, of potentials that are
+  // combinations of w s / k^2 and mu2 / k^2, so Psi1 and Psi2 are never formed (at
+  // 512^3 in FP32 combining them as fields took 1.55 of 12.0 ms, and nine
+  // x-pass outputs instead of three 2.3 ms).
   void lpt(const T* s, T* d0, T* p0) {
     const double inv = 1.0 / (double)P_;
-    MulSpec sp[9] = {spec(MUL_WHITE | MUL_GRAD, 0, 0, inv), spec(MUL_WHITE | MUL_GRAD, 1, 0, inv),
-                     spec(MUL_WHITE | MUL_GRAD, 2, 0, inv), spec(MUL_WHITE | MUL_HESS, 0, 0, inv),
-                     spec(MUL_WHITE | MUL_HESS, 1, 1, inv), spec(MUL_WHITE | MUL_HESS, 2, 2, inv),
-                     spec(MUL_WHITE | MUL_HESS, 0, 1, inv), spec(MUL_WHITE | MUL_HESS, 0, 2, inv),
-                     spec(MUL_WHITE | MUL_HESS, 1, 2, inv)};
-    T* outs[9] = {d0, d0 + P_, d0 + 2 * P_, phi_, phi_ + P_, phi_ + 2 * P_,
-                  phi_ + 3 * P_, phi_ + 4 * P_, phi_ + 5 * P_};
-    chain_scatter(0, s, T(1), nullptr, T(0), outs, sp, 9);
+    const Mul sp[6] = {hess(0, 0, inv, 1), hess(1, 1, inv, 1), hess(2, 2, inv, 1),
+                       hess(0, 1, inv, 1), hess(0, 2, inv, 1), hess(1, 2, inv, 1)};
+    T* outs[6] = {phi_, phi_ + P_, phi_ + 2 * P_, phi_ + 3 * P_, phi_ + 4 * P_, phi_ + 5 * P_};
+    chain_scatter(0, s, outs, sp, 6);  // leaves the z and y transform of s in pool_
     {
       auto sc = timer_.scope("lpt_mu2", 7.0 * P_ * sizeT());
       fk::k_mu2<T><<<grid_for(P_, kThreads), kThreads, 0, st_>>>(phi_, mu_, P_);
       IC_LAUNCHED();
     }
-    MulSpec sp2[3] = {spec(MUL_GRAD, 0, 0, -inv), spec(MUL_GRAD, 1, 0, -inv),
-                      spec(MUL_GRAD, 2, 0, -inv)};
-    T* outs2[3] = {p0, p0 + P_, p0 + 2 * P_};
-    chain_scatter(0, mu_, T(1), nullptr, T(0), outs2, sp2, 3);
+    auto f = fa(0);
+    const double U = (double)P_ * sizeT(), Hb = half_spectrum_bytes(np_);
+    const GIn in{mu_, T(1), nullptr, T(0), nullptr};
+    cx<T>* const S1[1] = {pool_ + Hp_};
+    r2c_zy(f, &in, S1, 1, U, Hb);
     const double a2E = prob_.a_init * prob_.a_init * co_.E_init;
-    auto sc = timer_.scope("lpt_assemble", 12.0 * P_ * sizeT());
-    fk::k_lpt_assemble<T><<<grid_for(3 * P_, kThreads), kThreads, 0, st_>>>(
-        d0, p0, static_cast<T>(co_.D1_init), static_cast<T>(co_.D2_init),
-        static_cast<T>(a2E * co_.f1_init * co_.D1_init),
-        static_cast<T>(a2E * co_.f2_init * co_.D2_init), 3 * P_);
-    IC_LAUNCHED();
+    const double c1[2] = {co_.D1_init, a2E * co_.f1_init * co_.D1_init};
+    const double c2[2] = {co_.D2_init, a2E * co_.f2_init * co_.D2_init};
+    XOut<T> xo[4];
+    YOut yo[6];
+    for (int k = 0; k < 2; ++k) {  // displacement, momentum
+      const Mul u = grad(0, inv);
+      for (int px = 0; px < 2; ++px)
+        xo[2 * k + px] = XOut<T>{pool_ + (2 + 2 * k + px) * Hp_, c1[k] * u.scale,
+                                 -c2[k] * u.scale, px};
+      for (int a = 0; a < 3; ++a)
+        yo[3 * k + a] = YOut{xo[2 * k + (a == 0)].S, yz_mul<T>(1.0, a == 1, a == 2, 1),
+                             (k ? p0 : d0) + a * P_};
+    }
+    {
+      auto sc = timer_.scope("fft_x_scatter", 6 * Hb);
+      const cx<T>* Si[2] = {pool_, pool_ + Hp_};
+      const int white[2] = {1, 0};
+      fft_x_scatter<T>(f, Si, white, 2, 1, xo, 4);
+    }
+    c2r_yz(f, yo, 6, pool_ + 6 * Hp_, nullptr, T(0), U, Hb, false);
   }
 
   // g = -grad lap^-1 (rho / nbar - 1) on the mesh (the -1 only touches k = 0).
   void force_from_density(T* g) {
     const double nbar = (double)P_ / (double)M_;  // particles per mesh cell
     const double sc = 1.0 / (nbar * (double)M_);
-    MulSpec sp[3] = {spec(MUL_GRAD, 0, 0, sc), spec(MUL_GRAD, 1, 0, sc), spec(MUL_GRAD, 2, 0, sc)};
+    const Mul sp[3] = {grad(0, sc), grad(1, sc), grad(2, sc)};
     T* outs[3] = {g, g + M_, g + 2 * M_};
-    chain_scatter(1, rhom_, T(1), nullptr, T(0), outs, sp, 3, zh_);
+    chain_scatter(1, rhom_, outs, sp, 3, zh_);
   }
 
   // Force meshes of the state d_n (order n).  With gsrc the positions are
@@ -1266,8 +1337,7 @@ class Engine final : public EngineBase {
       GIn ins[3] = {{gbar_, T(1), nullptr, T(0), zh_},
                     {gbar_ + M_, T(1), nullptr, T(0), zh_ + zm},
                     {gbar_ + 2 * M_, T(1), nullptr, T(0), zh_ + 2 * zm}};
-      MulSpec sp[3] = {spec(MUL_GRAD, 0, 0, sc_rho), spec(MUL_GRAD, 1, 0, sc_rho),
-                       spec(MUL_GRAD, 2, 0, sc_rho)};
+      const Mul sp[3] = {grad(0, sc_rho), grad(1, sc_rho), grad(2, sc_rho)};
       chain_gather(1, ins, sp, 3, rhobar_, nullptr, T(0));
       const T drift = n >= 1 ? static_cast<T>(co_.Dr[n - 1]) : T(0);
       {
@@ -1291,10 +1361,10 @@ class Engine final : public EngineBase {
     const T c1d = static_cast<T>(co_.D1_init), c1p = static_cast<T>(a2E * co_.f1_init * co_.D1_init);
     const T c2d = static_cast<T>(co_.D2_init), c2p = static_cast<T>(a2E * co_.f2_init * co_.D2_init);
     GIn in2[3];
-    MulSpec sp2[3];
+    Mul sp2[3];
     for (int j = 0; j < 3; ++j) {
       in2[j] = {dbar_ + j * P_, c2d, pbar_ + j * P_, c2p};
-      sp2[j] = spec(MUL_GRAD, j, 0, inv);
+      sp2[j] = grad(j, inv);
     }
     chain_gather(0, in2, sp2, 3, mu_, nullptr, T(0));
     {
@@ -1303,15 +1373,15 @@ class Engine final : public EngineBase {
       IC_LAUNCHED();
     }
     GIn in9[9];
-    MulSpec sp9[9];
+    Mul sp9[9];
     const int ha[6] = {0, 1, 2, 0, 0, 1}, hb[6] = {0, 1, 2, 1, 2, 2};
     for (int j = 0; j < 3; ++j) {
       in9[j] = {dbar_ + j * P_, c1d, pbar_ + j * P_, c1p};
-      sp9[j] = spec(MUL_WHITE | MUL_GRAD, j, 0, -inv);
+      sp9[j] = grad(j, -inv, 1);
     }
     for (int k = 0; k < 6; ++k) {
       in9[3 + k] = {phi_ + k * P_, T(1), nullptr, T(0)};
-      sp9[3 + k] = spec(MUL_WHITE | MUL_HESS, ha[k], hb[k], inv);
+      sp9[3 + k] = hess(ha[k], hb[k], inv, 1);
     }
     chain_gather(0, in9, sp9, 9, out, aux, beta_aux);
   }

@@ -19,15 +19,19 @@
 
 namespace ic {
 
-enum MulKind : int { MUL_WHITE = 1, MUL_GRAD = 2, MUL_HESS = 4 };
-
-// One k-space multiplier: scale * [w(k)] * [i k~_ga / k^2] * [k~_ha k~_hb / k^2].
-// With no kind bits it is the plain scale (the k = 0 mode kept); otherwise it
-// vanishes at k = 0.
-struct MulSpec {
-  int kinds = 0;
-  int ga = 0, ha = 0, hb = 0;
+// One k-space multiplier, factored along the axes:
+//   scale w(k)^white |k|^(-2 div) k~x^px k~y^py k~z^pz i^imag,
+// wave numbers in units of the fundamental mode, k~ their derivative versions
+// (0 at the Nyquist index); it vanishes at k = 0 when white or div is set.  The
+// x passes apply w, |k|^-2 and the power of k~x, which need the transform along
+// x, and the inverse y pass the rest: outputs that differ only in k~y and k~z
+// share one spectrum (the three force components two, the nine fields of 2LPT
+// three).
+struct Mul {
   double scale = 1.0;
+  int white = 0, div = 0;  // 0 or 1; 0, 1 or 2
+  int px = 0, py = 0, pz = 0;  // 0..3
+  int imag = 0;
 };
 
 constexpr int kMaxMul = 9;
@@ -35,12 +39,33 @@ constexpr int kMaxMul = 9;
 // of the particle orders).
 constexpr int kZHalo = 8;
 
-struct MulSet {
-  int kinds[kMaxMul];
-  int ga[kMaxMul];
-  int ha[kMaxMul];
-  int hb[kMaxMul];
-  double scale[kMaxMul];
+// The y and z part of a multiplier with a real scale: c(k~y) d(k~z) i^imag, the
+// powers as polynomials with one term.
+template <typename T>
+struct YZMul {
+  T c[4], d[4];
+  int imag;
+};
+template <typename T>
+inline YZMul<T> yz_mul(double scale, int py, int pz, int imag) {
+  YZMul<T> m{};
+  m.c[py] = static_cast<T>(scale);
+  m.d[pz] = static_cast<T>(1);
+  m.imag = imag;
+  return m;
+}
+template <typename T>
+inline YZMul<T> yz_one() {
+  return yz_mul<T>(1.0, 0, 0, 0);
+}
+
+// One output of a scatter x pass: k~x^px (a V0 + b V1), V the inputs' spectra
+// times w^white |k|^(-2 div).
+template <typename T>
+struct XOut {
+  cx<T>* S;
+  double a, b;
+  int px;
 };
 
 // Row pitch of the stored half spectrum: n/2+1 rounded up to a multiple of
@@ -78,7 +103,7 @@ void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* a
 
 // One field of a fused z and y pass: forward, the half spectrum S of
 // alpha (a + zh) + beta b transformed along z and y; inverse, the real field
-// out = (inverse of S) + beta_aux aux.
+// out = (inverse of mul S) + beta_aux aux.
 template <typename T>
 struct PlaneFwd {
   const T* a;
@@ -91,6 +116,7 @@ struct PlaneFwd {
 template <typename T>
 struct PlaneInv {
   const cx<T>* S;
+  YZMul<T> mul;  // applied to S
   T* out;
   const T* aux;  // nullable
   T beta_aux;
@@ -115,6 +141,9 @@ void fft_c2r_yz(const FftArgs<T>& f, const PlaneInv<T>* fields, int m, bool slab
 // In-place complex FFT along y of the half spectrum (forward or inverse, unnormalised).
 template <typename T>
 void fft_y(const FftArgs<T>& f, cx<T>* data, bool forward);
+// out = inverse FFT along y of mul in.
+template <typename T>
+void fft_y_inv(const FftArgs<T>& f, const cx<T>* in, cx<T>* out, const YZMul<T>& mul);
 
 // Complex FFT along x, out = scale * FFT(in); in may equal out.
 template <typename T>
@@ -126,14 +155,19 @@ void spectrum_pack(const FftArgs<T>& f, const cx<T>* stored, cx<T>* dense);
 template <typename T>
 void spectrum_unpack(const FftArgs<T>& f, const cx<T>* dense, cx<T>* stored);
 
-// Forward x FFT of in, then for each j < m: outs[j] = inverse x FFT of (mult_j * .).
-template <typename T>
-void fft_x_scatter(const FftArgs<T>& f, const cx<T>* in, cx<T>* const* outs,
-                   const MulSpec* specs, int m);
+// The x passes' outputs at most, and inputs of a scatter.
+constexpr int kMaxXOut = 4;
 
-// out = inverse x FFT of sum_j mult_j * forward x FFT of ins[j]; out may equal ins[0].
+// Forward x FFT of the nin (1 or 2) inputs, then for each j < m the inverse x
+// FFT of outs[j]; white[q] per input, div for both.
 template <typename T>
-void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const MulSpec* specs, int m,
+void fft_x_scatter(const FftArgs<T>& f, const cx<T>* const* in, const int* white, int nin,
+                   int div, const XOut<T>* outs, int m);
+
+// out = inverse x FFT of sum_j mult_j * forward x FFT of ins[j]; out may equal
+// ins[0].  The multipliers share white and div.
+template <typename T>
+void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const Mul* muls, int m,
                   cx<T>* out);
 
 }  // namespace ic

@@ -495,6 +495,27 @@ __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_c2r_z(
   fft_line<T, n, false>(lane, buf, lidx, tw, 2, load0, storeL);
 }
 
+// Integer wavenumber of index i on a full axis of side N.
+__device__ __forceinline__ int wave_index(int i, int N) { return i < N / 2 ? i : i - N; }
+// Its derivative version (0 at the Nyquist index).
+template <typename T>
+__device__ __forceinline__ T wave_deriv(int i, int N) {
+  return static_cast<T>(i == N / 2 ? 0 : wave_index(i, N));
+}
+// The one-term polynomial c at k (exact where the power is: zero terms add
+// nothing).
+template <typename T>
+__device__ __forceinline__ T one_term(const T (&c)[4], T k) {
+  return fma(fma(fma(c[3], k, c[2]), k, c[1]), k, c[0]);
+}
+// v times the y and z part of a multiplier: ky index e of side N, dz = one_term
+// of the line's k~z.
+template <typename T>
+__device__ __forceinline__ cx<T> times_yz(cx<T> v, const YZMul<T>& m, int e, int N, T dz) {
+  const T s = one_term(m.c, wave_deriv<T>(e, N)) * dz;
+  return mkc<T>(s * (m.imag ? -v.y : v.x), s * (m.imag ? v.x : v.y));
+}
+
 // The fields of one fused launch, one per blockIdx.y.
 template <typename T>
 struct FwdSet {
@@ -695,12 +716,14 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
   auto cidx = [&](int e) { return e * C::LS + zl(c); };
   auto cstore = [&](int e, cx<T> v) { buf[cidx(e)] = v; };
   // inverse y transforms of the even and odd rows ky, the packed column
-  // read as X(ky, 0) + i X(ky, n/2)
+  // read as X(ky, 0) + i X(ky, n/2) (k~z is 0 for both)
+  const YZMul<T>& mul = fields.f[blockIdx.y].mul;
+  const T dz = one_term(mul.d, static_cast<T>(c));
   for (int par = 0; par < 2; ++par) {
     auto load0 = [&](int e) -> cx<T> {  // both loads for every column: no branch
       const cx<T>* row = in + (x * N + 2 * e + par) * kp;
       const cx<T> u = row[c], v = row[n];
-      return c != 0 ? u : mkc<T>(u.x - v.y, u.y + v.x);
+      return times_yz<T>(c != 0 ? u : mkc<T>(u.x - v.y, u.y + v.x), mul, 2 * e + par, N, dz);
     };
     fft_line<T, n, false>(r0, buf, cidx, tw, 2, load0, cstore);
     __syncthreads();
@@ -883,9 +906,10 @@ __global__ __launch_bounds__((PlCfg<T, N>::THREADS)) void k_plane_inv(
     const int c = t % C::COLS, r0 = t / C::COLS;
     const int ci = c < n ? c : n - 1, cj = c == 0 ? n : ci;
     const cx<T>* __restrict__ in = fl.S + x * N * kp;
+    const T dz = one_term(fl.mul.d, static_cast<T>(ci));
     auto load0 = [&](int e) -> cx<T> {  // both loads for every column: no branch
       const cx<T> u = in[e * kp + ci], v = in[e * kp + cj];
-      return c != 0 ? u : mkc<T>(u.x - v.y, u.y + v.x);
+      return times_yz<T>(c != 0 ? u : mkc<T>(u.x - v.y, u.y + v.x), fl.mul, e, N, dz);
     };
     auto cidx = [&](int e) { return e * C::LS + zl(c); };
     auto cstore = [&](int e, cx<T> v) { buf[cidx(e)] = v; };
@@ -940,10 +964,12 @@ __global__ __launch_bounds__((PlCfg<T, N>::THREADS)) void k_plane_inv(
 // Line L of the batch starts at (L / group) * gstride + L % group and its
 // elements are estride apart; lines with L mod vmod >= vcnt are row padding
 // and are skipped.
-template <typename T, int N, bool FWD>
+// MUL (the inverse y pass of a chain): elements are multiplied by mul on load, e
+// being their ky and L mod vmod their kz.
+template <typename T, int N, bool FWD, bool MUL>
 __global__ __launch_bounds__((SCfg<T, N>::THREADS)) void k_strided(
     const cx<T>* in, cx<T>* out, T scale, const cx<T>* __restrict__ twg, int nlines, int group,
-    long long gstride, long long estride, int vmod, int vcnt) {
+    long long gstride, long long estride, int vmod, int vcnt, YZMul<T> mul) {
   using C = SCfg<T, N>;
   __shared__ cx<T> buf[N * C::LP];
   __shared__ cx<T> tw[N];
@@ -953,7 +979,13 @@ __global__ __launch_bounds__((SCfg<T, N>::THREADS)) void k_strided(
   const int line = blockIdx.x * C::LINES + l;
   const bool valid = line < nlines && (line % vmod) < vcnt;
   const long long base = (long long)(line / group) * gstride + (line % group);
-  auto load0 = [&](int e) -> cx<T> { return valid ? in[base + e * estride] : mkc<T>(0, 0); };
+  const T dz = MUL ? one_term(mul.d, line % vmod == N / 2 ? T(0) : static_cast<T>(line % vmod))
+                   : T(1);
+  auto load0 = [&](int e) -> cx<T> {
+    const cx<T> v = valid ? in[base + e * estride] : mkc<T>(0, 0);
+    if constexpr (MUL) return times_yz<T>(v, mul, e, N, dz);
+    return v;
+  };
   auto storeL = [&](int e, cx<T> v) {
     if (valid) out[base + e * estride] = cscale<T>(v, scale);
   };
@@ -961,58 +993,53 @@ __global__ __launch_bounds__((SCfg<T, N>::THREADS)) void k_strided(
   fft_line<T, N, FWD>(lane, buf, lidx, tw, 1, load0, storeL);
 }
 
-// ------------------------------------------------- k-space multipliers
-// Integer wavenumber of index i on a full axis of side N and its derivative
-// version (0 at the Nyquist index).
-__device__ __forceinline__ int wave_index(int i, int N) { return i < N / 2 ? i : i - N; }
-
-// Component a (0, 1, 2) of an integer wave vector; a is the same for the
-// whole workgroup, so this is a select, not an indexed (private memory) load.
-__device__ __forceinline__ int pick(int a, int kx, int ky, int kz) {
-  return a == 0 ? kx : (a == 1 ? ky : kz);
-}
-
-// Multiplier j of ms applied to v at wave vector (kx, ky, kz) in units of the
-// fundamental mode (derivative versions), n2 = |k|^2 in the same units.
-template <typename T>
-__device__ __forceinline__ cx<T> apply_mult(cx<T> v, const MulSet& ms, int j, int n2, int kx,
-                                            int ky, int kz, const T* __restrict__ wtab,
-                                            T L_over_2pi) {
-  const int kinds = ms.kinds[j];
-  T f = static_cast<T>(ms.scale[j]);
-  if (kinds == 0) return cscale<T>(v, f);
-  if (n2 == 0) return mkc<T>(0, 0);
-  if (kinds & MUL_WHITE) f *= wtab[n2];
-  const T inv = static_cast<T>(1) / static_cast<T>(n2);
-  if (kinds & MUL_HESS)
-    f *= static_cast<T>(pick(ms.ha[j], kx, ky, kz) * pick(ms.hb[j], kx, ky, kz)) * inv;
-  if (kinds & MUL_GRAD) {
-    f *= L_over_2pi * static_cast<T>(pick(ms.ga[j], kx, ky, kz)) * inv;
-    return mkc<T>(-v.y * f, v.x * f);  // i f v
-  }
-  return cscale<T>(v, f);
-}
-
-template <typename T>
-struct OutPtrs {
-  cx<T>* p[kMaxMul];
-};
+// ------------------------------------------------- x passes
 template <typename T>
 struct InPtrs {
   const cx<T>* p[kMaxMul];
 };
 
-// Forward x FFT, then m inverse x FFTs of the multiplied spectrum; the
-// forward result stays in registers (XPlan layout) across the m inverses.  On
-// grids too small to fill the chip (fft_x_scatter) the outputs are dealt over
-// blockIdx.y and each workgroup repeats the forward transform.
-template <typename T, int N>
-__global__ __launch_bounds__((FCfg<T, N>::THREADS), (FCfg<T, N>::MINW)) void k_x_scatter(
-    const cx<T>* __restrict__ in, OutPtrs<T> outs, MulSet ms, int m,
-    const T* __restrict__ wtab, T L_over_2pi, const cx<T>* __restrict__ twg, int nlines,
-    int K, int kp) {
-  using C = FCfg<T, N>;
-  using X = XPlan<N>;
+// w(k)^white |k|^(-2 div) at the squared integer wave number n2 (0 at n2 = 0 when
+// either is set).
+template <typename T>
+__device__ __forceinline__ T k_factor(int n2, int white, int div, const T* __restrict__ wtab) {
+  const T inv = static_cast<T>(1) / static_cast<T>(n2);
+  T f = white ? wtab[n2] : static_cast<T>(1);
+  f *= div == 0 ? static_cast<T>(1) : (div == 1 ? inv : inv * inv);
+  return n2 == 0 && (white || div) ? static_cast<T>(0) : f;
+}
+
+// Outputs of a scatter: coefficients of the one-term polynomials in k~x.
+template <typename T>
+struct XOutSet {
+  cx<T>* p[kMaxXOut];
+  T a[kMaxXOut][4], b[kMaxXOut][4];
+};
+
+// The scatter with two inputs holds two spectra in registers.
+template <typename T, int N, int NIN> struct PlanS : PlanX<N> {};
+template <typename T> struct PlanS<T, 128, 2> {
+  static constexpr int R0 = 8, R1 = 4, R2 = 4, S = 3, RMAX = 8, TPL = 128 / RMAX;
+};
+template <typename T> struct PlanS<T, 256, 2> : PlanG<256> {};
+
+// Forward x FFT of the inputs, times w and |k|^-2 in place, then m inverse x FFTs
+// of their combinations with powers of k~x; the forward results stay in
+// registers (XPlan layout) across the m inverses.  On grids too small to
+// fill the chip (fft_x_scatter) the outputs are dealt over blockIdx.y and each
+// workgroup repeats the forward transform.
+//
+// With whole multipliers per output (a division, a table and index arithmetic
+// per element and output) the pass was bound by its arithmetic at two waves per
+// SIMD; factored, an output costs one multiplication per part.
+template <typename T, int N, int NIN>
+__global__ __launch_bounds__((FCfg<T, N, PlanS<T, N, NIN>>::THREADS),
+                             (FCfg<T, N, PlanS<T, N, NIN>>::MINW)) void k_x_scatter(
+    InPtrs<T> ins, int white0, int white1, int div, XOutSet<T> outs, int m,
+    const T* __restrict__ wtab, const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
+  using PL = PlanS<T, N, NIN>;
+  using C = FCfg<T, N, PL>;
+  using X = XPlan<N, PL>;
   __shared__ cx<T> B[N * C::LP];
   __shared__ cx<T> tw[N];
   load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
@@ -1023,38 +1050,68 @@ __global__ __launch_bounds__((FCfg<T, N>::THREADS), (FCfg<T, N>::MINW)) void k_x
   const bool valid = line < nlines && kz < K;
   const long long stride = (long long)nlines;  // = N * kp
   const int iy = wave_index(ky, N), iz = kz;
-  const int dy = (ky == N / 2) ? 0 : iy, dz = (kz == N / 2) ? 0 : iz;
   auto lidx = [&](int e) { return e * C::LP + l; };
-  auto load_in = [&](int e) -> cx<T> { return valid ? in[line + e * stride] : mkc<T>(0, 0); };
-  cx<T> V[X::BPT][X::RL];
-  fft_fwd_to_regs<T, N, PlanX<N>>(lane, B, lidx, tw, load_in, V);
+  cx<T> V[NIN][X::BPT][X::RL];
+#pragma unroll
+  for (int q = 0; q < NIN; ++q) {
+    const cx<T>* __restrict__ in = ins.p[q];
+    auto load_in = [&](int e) -> cx<T> { return valid ? in[line + e * stride] : mkc<T>(0, 0); };
+    fft_fwd_to_regs<T, N, PL>(lane, B, lidx, tw, load_in, V[q]);
+#pragma unroll
+    for (int b = 0; b < X::BPT; ++b) {
+#pragma unroll
+      for (int r = 0; r < X::RL; ++r) {
+        const int ix = wave_index(lane + b * X::TPL + r * X::NBL, N);
+        const int n2 = valid ? ix * ix + iy * iy + iz * iz : 0;
+        V[q][b][r] = cscale<T>(V[q][b][r], k_factor<T>(n2, q ? white1 : white0, div, wtab));
+      }
+    }
+  }
   for (int j = blockIdx.y; j < m; j += gridDim.y) {
     cx<T> W[X::BPT][X::RL];
 #pragma unroll
     for (int b = 0; b < X::BPT; ++b) {
 #pragma unroll
       for (int r = 0; r < X::RL; ++r) {
-        const int e = lane + b * X::TPL + r * X::NBL;
-        const int ix = wave_index(e, N);
-        const int n2 = ix * ix + iy * iy + iz * iz;
-        W[b][r] = apply_mult<T>(V[b][r], ms, j, n2, (e == N / 2) ? 0 : ix, dy, dz, wtab,
-                                L_over_2pi);
+        const T dx = wave_deriv<T>(lane + b * X::TPL + r * X::NBL, N);
+        const T sa = one_term(outs.a[j], dx);
+        cx<T> w = cscale<T>(V[0][b][r], sa);
+        if constexpr (NIN == 2) {
+          const T sb = one_term(outs.b[j], dx);
+          w.x = fma(sb, V[1][b][r].x, w.x);
+          w.y = fma(sb, V[1][b][r].y, w.y);
+        }
+        W[b][r] = w;
       }
     }
     cx<T>* dst = outs.p[j];
     auto store_o = [&](int e, cx<T> v) {
       if (valid) dst[line + e * stride] = v;
     };
-    fft_inv_from_regs<T, N, PlanX<N>>(lane, B, lidx, tw, W, store_o);
+    fft_inv_from_regs<T, N, PL>(lane, B, lidx, tw, W, store_o);
   }
+}
+
+// The polynomial parts of a gather's multipliers; white and div are common.
+template <typename T>
+struct GatherSet {
+  T cx[kMaxMul][4], cy[kMaxMul][4], cz[kMaxMul][4];
+  int imag[kMaxMul];
+};
+
+// s_j k~x^px k~y^py k~z^pz i^imag of input j applied to v (dyz: its y and z part).
+template <typename T>
+__device__ __forceinline__ cx<T> gather_term(cx<T> v, const T (&c)[4], int imag, T dx, T dyz) {
+  const T s = one_term(c, dx) * dyz;
+  return mkc<T>(s * (imag ? -v.y : v.x), s * (imag ? v.x : v.y));
 }
 
 // Sum over m inputs of multiplier * forward x FFT (accumulated in
 // registers), then one inverse x FFT.
 template <typename T, int N>
 __global__ __launch_bounds__((FCfg<T, N, PlanG<N>>::THREADS)) void k_x_gather(
-    InPtrs<T> ins, MulSet ms, int m, cx<T>* out, const T* __restrict__ wtab, T L_over_2pi,
-    const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
+    InPtrs<T> ins, GatherSet<T> gs, int white, int div, int m, cx<T>* out,
+    const T* __restrict__ wtab, const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
   using C = FCfg<T, N, PlanG<N>>;
   using X = XPlan<N, PlanG<N>>;
   __shared__ cx<T> B[N * C::LP];
@@ -1067,7 +1124,7 @@ __global__ __launch_bounds__((FCfg<T, N, PlanG<N>>::THREADS)) void k_x_gather(
   const bool valid = line < nlines && kz < K;
   const long long stride = (long long)nlines;  // = N * kp
   const int iy = wave_index(ky, N), iz = kz;
-  const int dy = (ky == N / 2) ? 0 : iy, dz = (kz == N / 2) ? 0 : iz;
+  const T dy = wave_deriv<T>(ky, N), dz = static_cast<T>(kz == N / 2 ? 0 : kz);
   auto lidx = [&](int e) { return e * C::LP + l; };
   cx<T> acc[X::BPT][X::RL];
   for (int j = 0; j < m; ++j) {
@@ -1077,17 +1134,24 @@ __global__ __launch_bounds__((FCfg<T, N, PlanG<N>>::THREADS)) void k_x_gather(
     };
     cx<T> V[X::BPT][X::RL];
     fft_fwd_to_regs<T, N, PlanG<N>>(lane, B, lidx, tw, load_in, V);
+    const T dyz = one_term(gs.cy[j], dy) * one_term(gs.cz[j], dz);
 #pragma unroll
     for (int b = 0; b < X::BPT; ++b) {
 #pragma unroll
       for (int r = 0; r < X::RL; ++r) {
-        const int e = lane + b * X::TPL + r * X::NBL;
-        const int ix = wave_index(e, N);
-        const int n2 = ix * ix + iy * iy + iz * iz;
-        const cx<T> t = apply_mult<T>(V[b][r], ms, j, n2, (e == N / 2) ? 0 : ix, dy, dz, wtab,
-                                      L_over_2pi);
+        const T dx = wave_deriv<T>(lane + b * X::TPL + r * X::NBL, N);
+        const cx<T> t = gather_term<T>(V[b][r], gs.cx[j], gs.imag[j], dx, dyz);
         acc[b][r] = j == 0 ? t : cadd<T>(acc[b][r], t);
       }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < X::BPT; ++b) {
+#pragma unroll
+    for (int r = 0; r < X::RL; ++r) {
+      const int ix = wave_index(lane + b * X::TPL + r * X::NBL, N);
+      const int n2 = valid ? ix * ix + iy * iy + iz * iz : 0;
+      acc[b][r] = cscale<T>(acc[b][r], k_factor<T>(n2, white, div, wtab));
     }
   }
   auto store_o = [&](int e, cx<T> v) {
@@ -1103,8 +1167,8 @@ __global__ __launch_bounds__((FCfg<T, N, PlanG<N>>::THREADS)) void k_x_gather(
 // instead of one after the other.
 template <typename T, int N>
 __global__ __launch_bounds__(1024) void k_x_gather_wide(
-    InPtrs<T> ins, MulSet ms, int m, cx<T>* out, const T* __restrict__ wtab, T L_over_2pi,
-    const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
+    InPtrs<T> ins, GatherSet<T> gs, int white, int div, int m, cx<T>* out,
+    const T* __restrict__ wtab, const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
   using C = FCfg<T, N, PlanG<N>>;
   using X = XPlan<N, PlanG<N>>;
   extern __shared__ char smem[];
@@ -1120,22 +1184,20 @@ __global__ __launch_bounds__(1024) void k_x_gather_wide(
   const bool valid = line < nlines && kz < K;
   const long long stride = (long long)nlines;  // = N * kp
   const int iy = wave_index(ky, N), iz = kz;
-  const int dy = (ky == N / 2) ? 0 : iy, dz = (kz == N / 2) ? 0 : iz;
+  const T dy = wave_deriv<T>(ky, N), dz = static_cast<T>(kz == N / 2 ? 0 : kz);
   auto lidx = [&](int e) { return e * C::LP + l; };
   const cx<T>* src = ins.p[j];
   auto load_in = [&](int e) -> cx<T> { return valid ? src[line + e * stride] : mkc<T>(0, 0); };
   cx<T> V[X::BPT][X::RL];
   fft_fwd_to_regs<T, N, PlanG<N>>(lane, B, lidx, tw, load_in, V);
   __syncthreads();
+  const T dyz = one_term(gs.cy[j], dy) * one_term(gs.cz[j], dz);
 #pragma unroll
   for (int b = 0; b < X::BPT; ++b) {
 #pragma unroll
     for (int r = 0; r < X::RL; ++r) {
       const int e = lane + b * X::TPL + r * X::NBL;
-      const int ix = wave_index(e, N);
-      const int n2 = ix * ix + iy * iy + iz * iz;
-      B[lidx(e)] = apply_mult<T>(V[b][r], ms, j, n2, (e == N / 2) ? 0 : ix, dy, dz, wtab,
-                                 L_over_2pi);
+      B[lidx(e)] = gather_term<T>(V[b][r], gs.cx[j], gs.imag[j], wave_deriv<T>(e, N), dyz);
     }
   }
   __syncthreads();
@@ -1143,10 +1205,12 @@ __global__ __launch_bounds__(1024) void k_x_gather_wide(
   for (int b = 0; b < X::BPT; ++b) {
 #pragma unroll
     for (int r = 0; r < X::RL; ++r) {
-      const int i = lidx(lane + b * X::TPL + r * X::NBL);
+      const int e = lane + b * X::TPL + r * X::NBL, i = lidx(e);
       cx<T> a = tiles[i];
       for (int q = 1; q < m; ++q) a = cadd<T>(a, tiles[q * N * C::LP + i]);
-      V[b][r] = a;
+      const int ix = wave_index(e, N);
+      const int n2 = valid ? ix * ix + iy * iy + iz * iz : 0;
+      V[b][r] = cscale<T>(a, k_factor<T>(n2, white, div, wtab));
     }
   }
   __syncthreads();
@@ -1204,19 +1268,6 @@ void dispatch_n(int n, F&& f) {
     case 1024: f(std::integral_constant<int, 1024>{}); break;
     default: throw ApiError(-2, "FFT size must be a power of two in [8, 1024]");
   }
-}
-
-inline MulSet make_set(const MulSpec* specs, int m) {
-  if (m < 1 || m > kMaxMul) throw ApiError(-1, "multiplier count out of range");
-  MulSet s{};
-  for (int j = 0; j < m; ++j) {
-    s.kinds[j] = specs[j].kinds;
-    s.ga[j] = specs[j].ga;
-    s.ha[j] = specs[j].ha;
-    s.hb[j] = specs[j].hb;
-    s.scale[j] = specs[j].scale;
-  }
-  return s;
 }
 
 }  // namespace fftk
@@ -1338,11 +1389,24 @@ void fft_y(const FftArgs<T>& f, cx<T>* data, bool forward) {
     const int nlines = N * kp;
     const unsigned grid = blocks_for(nlines, C::LINES);
     if (forward)
-      fftk::k_strided<T, N, true><<<grid, C::THREADS, 0, f.stream>>>(
-          data, data, T(1), f.tw, nlines, kp, (long long)N * kp, kp, kp, K);
+      fftk::k_strided<T, N, true, false><<<grid, C::THREADS, 0, f.stream>>>(
+          data, data, T(1), f.tw, nlines, kp, (long long)N * kp, kp, kp, K, yz_one<T>());
     else
-      fftk::k_strided<T, N, false><<<grid, C::THREADS, 0, f.stream>>>(
-          data, data, T(1), f.tw, nlines, kp, (long long)N * kp, kp, kp, K);
+      fftk::k_strided<T, N, false, false><<<grid, C::THREADS, 0, f.stream>>>(
+          data, data, T(1), f.tw, nlines, kp, (long long)N * kp, kp, kp, K, yz_one<T>());
+  });
+  IC_LAUNCHED();
+}
+
+template <typename T>
+void fft_y_inv(const FftArgs<T>& f, const cx<T>* in, cx<T>* out, const YZMul<T>& mul) {
+  fftk::dispatch_n<T>(f.n, [&](auto NC) {
+    constexpr int N = decltype(NC)::value;
+    using C = fftk::SCfg<T, N>;
+    const int K = N / 2 + 1, kp = f.kp;
+    const int nlines = N * kp;
+    fftk::k_strided<T, N, false, true><<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(
+        in, out, T(1), f.tw, nlines, kp, (long long)N * kp, kp, kp, K, mul);
   });
   IC_LAUNCHED();
 }
@@ -1356,11 +1420,11 @@ void fft_x(const FftArgs<T>& f, const cx<T>* in, cx<T>* out, bool forward, T sca
     const int nlines = N * kp;
     const unsigned grid = blocks_for(nlines, C::LINES);
     if (forward)
-      fftk::k_strided<T, N, true><<<grid, C::THREADS, 0, f.stream>>>(
-          in, out, scale, f.tw, nlines, nlines, 0, nlines, kp, K);
+      fftk::k_strided<T, N, true, false><<<grid, C::THREADS, 0, f.stream>>>(
+          in, out, scale, f.tw, nlines, nlines, 0, nlines, kp, K, yz_one<T>());
     else
-      fftk::k_strided<T, N, false><<<grid, C::THREADS, 0, f.stream>>>(
-          in, out, scale, f.tw, nlines, nlines, 0, nlines, kp, K);
+      fftk::k_strided<T, N, false, false><<<grid, C::THREADS, 0, f.stream>>>(
+          in, out, scale, f.tw, nlines, nlines, 0, nlines, kp, K, yz_one<T>());
   });
   IC_LAUNCHED();
 }
@@ -1385,34 +1449,56 @@ void spectrum_unpack(const FftArgs<T>& f, const cx<T>* dense, cx<T>* stored) {
 // and a pass over m fields then spreads them over more workgroups or threads.
 constexpr unsigned kSmallGrid = 512;
 
-template <typename T>
-void fft_x_scatter(const FftArgs<T>& f, const cx<T>* in, cx<T>* const* outs,
-                   const MulSpec* specs, int m) {
-  MulSet ms = fftk::make_set(specs, m);
-  fftk::OutPtrs<T> op{};
-  for (int j = 0; j < m; ++j) op.p[j] = outs[j];
-  const T l2p = static_cast<T>(f.box / (2.0 * 3.14159265358979323846));
+template <typename T, int NIN>
+void x_scatter(const FftArgs<T>& f, const fftk::InPtrs<T>& ip, const int* white, int div,
+               const fftk::XOutSet<T>& set, int m) {
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
-    using C = fftk::FCfg<T, N>;
+    using C = fftk::FCfg<T, N, fftk::PlanS<T, N, NIN>>;
     const int K = N / 2 + 1;
     const int nlines = N * f.kp;
     const unsigned blocks = blocks_for(nlines, C::LINES);
-    // fewer workgroups than CUs: one output per workgroup
     const dim3 grid(blocks, blocks <= kSmallGrid ? m : 1);
-    fftk::k_x_scatter<T, N><<<grid, C::THREADS, 0, f.stream>>>(in, op, ms, m, f.wtab, l2p, f.tw,
-                                                               nlines, K, f.kp);
+    fftk::k_x_scatter<T, N, NIN><<<grid, C::THREADS, 0, f.stream>>>(
+        ip, white[0], NIN == 2 ? white[1] : 0, div, set, m, f.wtab, f.tw, nlines, K, f.kp);
   });
   IC_LAUNCHED();
 }
 
 template <typename T>
-void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const MulSpec* specs, int m,
-                  cx<T>* out) {
-  MulSet ms = fftk::make_set(specs, m);
+void fft_x_scatter(const FftArgs<T>& f, const cx<T>* const* in, const int* white, int nin,
+                   int div, const XOut<T>* outs, int m) {
+  if (m < 1 || m > kMaxXOut || nin < 1 || nin > 2) throw ApiError(-1, "x pass out of range");
   fftk::InPtrs<T> ip{};
-  for (int j = 0; j < m; ++j) ip.p[j] = ins[j];
-  const T l2p = static_cast<T>(f.box / (2.0 * 3.14159265358979323846));
+  for (int q = 0; q < nin; ++q) ip.p[q] = in[q];
+  fftk::XOutSet<T> set{};
+  for (int j = 0; j < m; ++j) {
+    set.p[j] = outs[j].S;
+    set.a[j][outs[j].px] = static_cast<T>(outs[j].a);
+    set.b[j][outs[j].px] = static_cast<T>(outs[j].b);
+  }
+  if (nin == 1)
+    x_scatter<T, 1>(f, ip, white, div, set, m);
+  else
+    x_scatter<T, 2>(f, ip, white, div, set, m);
+}
+
+template <typename T>
+void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const Mul* muls, int m,
+                  cx<T>* out) {
+  if (m < 1 || m > kMaxMul) throw ApiError(-1, "multiplier count out of range");
+  fftk::InPtrs<T> ip{};
+  fftk::GatherSet<T> gs{};
+  const int white = muls[0].white, div = muls[0].div;
+  for (int j = 0; j < m; ++j) {
+    if (muls[j].white != white || muls[j].div != div)
+      throw ApiError(-1, "multipliers of a gather share w and |k|^-2");
+    ip.p[j] = ins[j];
+    gs.cx[j][muls[j].px] = static_cast<T>(muls[j].scale);
+    gs.cy[j][muls[j].py] = static_cast<T>(1);
+    gs.cz[j][muls[j].pz] = static_cast<T>(1);
+    gs.imag[j] = muls[j].imag;
+  }
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     using C = fftk::FCfg<T, N, fftk::PlanG<N>>;
@@ -1423,12 +1509,12 @@ void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const MulSpec* s
       if (m > 1 && blocks <= kSmallGrid && C::THREADS * m <= 1024) {
         const size_t lds = sizeof(cx<T>) * (N + (size_t)m * N * C::LP);
         fftk::k_x_gather_wide<T, N><<<blocks, C::THREADS * m, lds, f.stream>>>(
-            ip, ms, m, out, f.wtab, l2p, f.tw, nlines, K, f.kp);
+            ip, gs, white, div, m, out, f.wtab, f.tw, nlines, K, f.kp);
         return;
       }
     }
-    fftk::k_x_gather<T, N><<<blocks, C::THREADS, 0, f.stream>>>(ip, ms, m, out, f.wtab, l2p,
-                                                                f.tw, nlines, K, f.kp);
+    fftk::k_x_gather<T, N><<<blocks, C::THREADS, 0, f.stream>>>(
+        ip, gs, white, div, m, out, f.wtab, f.tw, nlines, K, f.kp);
   });
   IC_LAUNCHED();
 }

@@ -63,19 +63,6 @@ __global__ void k_phi_bar(T* __restrict__ phi, const T* __restrict__ mub, long l
   }
 }
 
-// In place: d <- D1 Psi1 + D2 Psi2, p <- a^2 E (f1 D1 Psi1 + f2 D2 Psi2), with
-// Psi1 held in d and Psi2 in p on entry ([3][P] each).
-template <typename T>
-__global__ void k_lpt_assemble(T* __restrict__ d, T* __restrict__ p, T cd1, T cd2, T cp1, T cp2,
-                               long long n3) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n3;
-       i += (long long)gridDim.x * blockDim.x) {
-    const T psi1 = d[i], psi2 = p[i];
-    d[i] = cd1 * psi1 + cd2 * psi2;
-    p[i] = cp1 * psi1 + cp2 * psi2;
-  }
-}
-
 // Observation model of the data grid (section 2.2.1, items 4-5).
 template <typename T>
 struct Obs {

@@ -47,7 +47,6 @@ SCOPES = {
     "k_x_scatter": "fft_x_scatter",
     "k_x_gather": "fft_x_gather",
     "k_mu2": "lpt_mu2",
-    "k_lpt_assemble": "lpt_assemble",
     "k_phi_bar": "lpt_phi_bar",
     "k_loss": "loss",
 }
