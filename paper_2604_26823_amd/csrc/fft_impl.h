@@ -42,17 +42,16 @@ IC_FFT_PLAN(1024, 16, 8, 8)
 #undef IC_FFT_PLAN
 
 // Radix plans of the fused x passes, which hold a line's spectrum in
-// registers across several transforms: PlanX for the scatter (one forward,
-// several inverses), PlanG for the gather (several forwards, one inverse);
-// both default to Plan<n>.  The gather at n = 256 takes radix 8 first, so a
-// thread holds 8 values instead of 16 and more waves fit per SIMD.
+// registers across several transforms.  At n = 128 and 256 they take radix 8
+// first, so a thread holds 8 values instead of 16 and twice the waves fit per
+// SIMD (x scatter of two outputs: 128^3 FP64 24.7 -> 15.6 us, 256^3 FP64 111 ->
+// 88; the gather 116 -> 100 and 235 -> 175 in FP32 and FP64 at 256^3).
 template <int n> struct PlanX : Plan<n> {};
-template <int n> struct PlanG : Plan<n> {};
-template <> struct PlanG<256> {
-  static constexpr int R0 = 8, R1 = 8, R2 = 4;
-  static constexpr int S = 3;
-  static constexpr int RMAX = 8;
-  static constexpr int TPL = 256 / RMAX;
+template <> struct PlanX<128> {
+  static constexpr int R0 = 8, R1 = 4, R2 = 4, S = 3, RMAX = 8, TPL = 128 / RMAX;
+};
+template <> struct PlanX<256> {
+  static constexpr int R0 = 8, R1 = 8, R2 = 4, S = 3, RMAX = 8, TPL = 256 / RMAX;
 };
 
 // cos and sin of 2 pi m / 16, m = 0..7.
@@ -145,7 +144,7 @@ __device__ __forceinline__ void stage(int lane, int Ns, const cx<T>* __restrict_
 #pragma unroll
   for (int b = 0; b < BPT; ++b) {
     const int jb = lane + b * TPL;
-    const int k = jb & (Ns - 1);
+    const int k = Ns == NB ? jb : jb & (Ns - 1);  // (last stage: jb < Ns)
     const int base = (jb - k) * R + k;
 #pragma unroll
     for (int r = 0; r < R; ++r) store(base + r * Ns, v[b][r]);
@@ -185,9 +184,9 @@ __device__ __forceinline__ void fft_line(int lane, cx<T>* buf, LIdx lidx,
 // start from them, with no LDS round trip in between: the fused x passes
 // hold a line's spectrum in registers while it is multiplied (and summed),
 // and need one LDS tile instead of two.
-template <int n, class PL = PlanX<n>>
+template <int n>
 struct XPlan {
-  using P = PL;
+  using P = PlanX<n>;
   static constexpr int S = P::S;
   static constexpr int RL = S == 1 ? P::R0 : (S == 2 ? P::R1 : P::R2);  // last forward radix
   static constexpr int Q1 = S == 1 ? 1 : (S == 2 ? P::R0 : P::R1);      // inverse radices
@@ -244,11 +243,11 @@ __device__ __forceinline__ void stage_from_regs(int lane, cx<T> (&v)[n / R / TPL
 
 // Forward length-n transform from load0 ending in registers (XPlan layout);
 // the first store into buf follows a barrier.
-template <typename T, int n, class PL, class Load, class LIdx>
+template <typename T, int n, class Load, class LIdx>
 __device__ __forceinline__ void fft_fwd_to_regs(int lane, cx<T>* buf, LIdx lidx,
                                                 const cx<T>* __restrict__ tw, Load&& load0,
-                                                cx<T> (&v)[XPlan<n, PL>::BPT][XPlan<n, PL>::RL]) {
-  using P = PL;
+                                                cx<T> (&v)[XPlan<n>::BPT][XPlan<n>::RL]) {
+  using P = PlanX<n>;
   constexpr int TPL = P::TPL;
   auto ld = [&](int e) { return buf[lidx(e)]; };
   auto st = [&](int e, cx<T> x) { buf[lidx(e)] = x; };
@@ -270,12 +269,12 @@ __device__ __forceinline__ void fft_fwd_to_regs(int lane, cx<T>* buf, LIdx lidx,
 // Inverse length-n transform starting from registers in the XPlan layout,
 // radices in the reversed order, last stage to storeL; the first store into
 // buf follows a barrier.  v is consumed.
-template <typename T, int n, class PL, class Store, class LIdx>
+template <typename T, int n, class Store, class LIdx>
 __device__ __forceinline__ void fft_inv_from_regs(int lane, cx<T>* buf, LIdx lidx,
                                                   const cx<T>* __restrict__ tw,
-                                                  cx<T> (&v)[XPlan<n, PL>::BPT][XPlan<n, PL>::RL],
+                                                  cx<T> (&v)[XPlan<n>::BPT][XPlan<n>::RL],
                                                   Store&& storeL) {
-  using X = XPlan<n, PL>;
+  using X = XPlan<n>;
   constexpr int TPL = X::TPL;
   auto ld = [&](int e) { return buf[lidx(e)]; };
   auto st = [&](int e, cx<T> x) { buf[lidx(e)] = x; };
@@ -317,16 +316,50 @@ template <typename T, int N> struct SCfg {  // strided C2C passes
   static constexpr int LP = LINES + 1;  // padded LDS element stride
 };
 
-template <typename T, int N, class PL = PlanX<N>> struct FCfg {  // fused x passes
-  static constexpr int TPL = PL::TPL;
-  // waves per SIMD the register allocation must allow: the FP32 scatter
-  // otherwise takes just over half the register file (one wave per SIMD)
+template <typename T, int N> struct FCfg {  // fused x passes
+  static constexpr int TPL = PlanX<N>::TPL;
+  // waves per SIMD the register allocation must allow
   static constexpr int MINW = (sizeof(T) == 4 && N <= 512) ? 2 : 1;
+  // Lines of a workgroup.  At n >= 256 in FP32 eight (64 bytes of a row): the
+  // workgroups get half as large and overlap their loads with the others'
+  // transforms, and their neighbours on the same XCD (x_line) use the other
+  // half of each cache line: 512^3 x scatter of two outputs 545 -> 486 us,
+  // 256^3 gather 77 -> 70.  (Without the neighbours sixteen lines were better.)
   static constexpr int LINES = (N <= 16) ? 64
-                               : (sizeof(T) == 4 ? (N <= 512 ? 16 : 8)
+                               : (sizeof(T) == 4 ? (N <= 128 ? 16 : 8)
                                                  : (N <= 512 ? 8 : 2));
   static constexpr int THREADS = LINES * TPL;
   static constexpr int LP = LINES + 1;
+};
+
+// First line of this workgroup in an x pass: consecutive groups of lines go to
+// workgroups of one XCD (workgroup w runs on XCD w mod 8), which share the cache
+// lines that the groups split (x gather at 256^3 in FP64 132 -> 122 us).
+template <typename T, int N>
+__device__ __forceinline__ int x_line() {
+  const int nb = gridDim.x, w = blockIdx.x;
+  return (nb % 8 == 0 ? w % 8 * (nb / 8) + w / 8 : w) * FCfg<T, N>::LINES;
+}
+
+// Elements e of one line of a strided pass, `stride` complex values apart.  A lane
+// touches e = lane + constants, so an element's address is a base common to the
+// workgroup, a constant multiple of the stride, and one 32-bit byte offset per
+// lane; 64-bit addresses per element took a third of the x passes' registers.
+template <typename T>
+struct StridedLine {
+  char* p;
+  uint32_t off;
+  int lane;
+  long long sb;
+  __device__ __forceinline__ StridedLine(const cx<T>* data, long long first, long long stride,
+                                         int lane_)
+      : p(const_cast<char*>(reinterpret_cast<const char*>(data))), lane(lane_),
+        sb(stride * static_cast<long long>(sizeof(cx<T>))) {
+    off = static_cast<uint32_t>((first + lane_ * stride) * static_cast<long long>(sizeof(cx<T>)));
+  }
+  __device__ __forceinline__ cx<T>& operator()(int e) const {
+    return *reinterpret_cast<cx<T>*>(p + (e - lane) * sb + off);
+  }
 };
 
 template <typename T>
@@ -977,17 +1010,20 @@ __global__ __launch_bounds__((SCfg<T, N>::THREADS)) void k_strided(
   const int l = threadIdx.x % C::LINES;
   const int lane = threadIdx.x / C::LINES;
   const int line = blockIdx.x * C::LINES + l;
-  const bool valid = line < nlines && (line % vmod) < vcnt;
-  const long long base = (long long)(line / group) * gstride + (line % group);
+  const bool valid = (line % vmod) < vcnt;  // row padding is transformed too, and not stored
+  const int g0 = blockIdx.x * C::LINES / group;
+  const long long first = (long long)(line / group - g0) * gstride + line % group;
+  const StridedLine<T> src(in + g0 * gstride, first, estride, lane);
+  const StridedLine<T> dst(out + g0 * gstride, first, estride, lane);
   const T dz = MUL ? one_term(mul.d, line % vmod == N / 2 ? T(0) : static_cast<T>(line % vmod))
                    : T(1);
   auto load0 = [&](int e) -> cx<T> {
-    const cx<T> v = valid ? in[base + e * estride] : mkc<T>(0, 0);
+    const cx<T> v = src(e);
     if constexpr (MUL) return times_yz<T>(v, mul, e, N, dz);
     return v;
   };
   auto storeL = [&](int e, cx<T> v) {
-    if (valid) out[base + e * estride] = cscale<T>(v, scale);
+    if (valid) dst(e) = cscale<T>(v, scale);
   };
   auto lidx = [&](int e) { return e * C::LP + l; };
   fft_line<T, N, FWD>(lane, buf, lidx, tw, 1, load0, storeL);
@@ -1016,13 +1052,6 @@ struct XOutSet {
   T a[kMaxXOut][4], b[kMaxXOut][4];
 };
 
-// The scatter with two inputs holds two spectra in registers.
-template <typename T, int N, int NIN> struct PlanS : PlanX<N> {};
-template <typename T> struct PlanS<T, 128, 2> {
-  static constexpr int R0 = 8, R1 = 4, R2 = 4, S = 3, RMAX = 8, TPL = 128 / RMAX;
-};
-template <typename T> struct PlanS<T, 256, 2> : PlanG<256> {};
-
 // Forward x FFT of the inputs, times w and |k|^-2 in place, then m inverse x FFTs
 // of their combinations with powers of k~x; the forward results stay in
 // registers (XPlan layout) across the m inverses.  On grids too small to
@@ -1033,30 +1062,29 @@ template <typename T> struct PlanS<T, 256, 2> : PlanG<256> {};
 // per element and output) the pass was bound by its arithmetic at two waves per
 // SIMD; factored, an output costs one multiplication per part.
 template <typename T, int N, int NIN>
-__global__ __launch_bounds__((FCfg<T, N, PlanS<T, N, NIN>>::THREADS),
-                             (FCfg<T, N, PlanS<T, N, NIN>>::MINW)) void k_x_scatter(
+__global__ __launch_bounds__((FCfg<T, N>::THREADS),
+                             (FCfg<T, N>::MINW)) void k_x_scatter(
     InPtrs<T> ins, int white0, int white1, int div, XOutSet<T> outs, int m,
     const T* __restrict__ wtab, const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
-  using PL = PlanS<T, N, NIN>;
-  using C = FCfg<T, N, PL>;
-  using X = XPlan<N, PL>;
+  using C = FCfg<T, N>;
+  using X = XPlan<N>;
   __shared__ cx<T> B[N * C::LP];
   __shared__ cx<T> tw[N];
   load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
   const int l = threadIdx.x % C::LINES;
   const int lane = threadIdx.x / C::LINES;
-  const int line = blockIdx.x * C::LINES + l;
+  const int line = x_line<T, N>() + l;
   const int ky = line / kp, kz = line % kp;
-  const bool valid = line < nlines && kz < K;
+  const bool valid = kz < K;  // row padding is transformed too, and not stored
   const long long stride = (long long)nlines;  // = N * kp
   const int iy = wave_index(ky, N), iz = kz;
   auto lidx = [&](int e) { return e * C::LP + l; };
   cx<T> V[NIN][X::BPT][X::RL];
 #pragma unroll
   for (int q = 0; q < NIN; ++q) {
-    const cx<T>* __restrict__ in = ins.p[q];
-    auto load_in = [&](int e) -> cx<T> { return valid ? in[line + e * stride] : mkc<T>(0, 0); };
-    fft_fwd_to_regs<T, N, PL>(lane, B, lidx, tw, load_in, V[q]);
+    const StridedLine<T> in(ins.p[q], line, stride, lane);
+    auto load_in = [&](int e) -> cx<T> { return in(e); };
+    fft_fwd_to_regs<T, N>(lane, B, lidx, tw, load_in, V[q]);
 #pragma unroll
     for (int b = 0; b < X::BPT; ++b) {
 #pragma unroll
@@ -1084,11 +1112,11 @@ __global__ __launch_bounds__((FCfg<T, N, PlanS<T, N, NIN>>::THREADS),
         W[b][r] = w;
       }
     }
-    cx<T>* dst = outs.p[j];
+    const StridedLine<T> dst(outs.p[j], line, stride, lane);
     auto store_o = [&](int e, cx<T> v) {
-      if (valid) dst[line + e * stride] = v;
+      if (valid) dst(e) = v;
     };
-    fft_inv_from_regs<T, N, PL>(lane, B, lidx, tw, W, store_o);
+    fft_inv_from_regs<T, N>(lane, B, lidx, tw, W, store_o);
   }
 }
 
@@ -1109,31 +1137,29 @@ __device__ __forceinline__ cx<T> gather_term(cx<T> v, const T (&c)[4], int imag,
 // Sum over m inputs of multiplier * forward x FFT (accumulated in
 // registers), then one inverse x FFT.
 template <typename T, int N>
-__global__ __launch_bounds__((FCfg<T, N, PlanG<N>>::THREADS)) void k_x_gather(
+__global__ __launch_bounds__((FCfg<T, N>::THREADS)) void k_x_gather(
     InPtrs<T> ins, GatherSet<T> gs, int white, int div, int m, cx<T>* out,
     const T* __restrict__ wtab, const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
-  using C = FCfg<T, N, PlanG<N>>;
-  using X = XPlan<N, PlanG<N>>;
+  using C = FCfg<T, N>;
+  using X = XPlan<N>;
   __shared__ cx<T> B[N * C::LP];
   __shared__ cx<T> tw[N];
   load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
   const int l = threadIdx.x % C::LINES;
   const int lane = threadIdx.x / C::LINES;
-  const int line = blockIdx.x * C::LINES + l;
+  const int line = x_line<T, N>() + l;
   const int ky = line / kp, kz = line % kp;
-  const bool valid = line < nlines && kz < K;
+  const bool valid = kz < K;  // row padding is transformed too, and not stored
   const long long stride = (long long)nlines;  // = N * kp
   const int iy = wave_index(ky, N), iz = kz;
   const T dy = wave_deriv<T>(ky, N), dz = static_cast<T>(kz == N / 2 ? 0 : kz);
   auto lidx = [&](int e) { return e * C::LP + l; };
   cx<T> acc[X::BPT][X::RL];
   for (int j = 0; j < m; ++j) {
-    const cx<T>* src = ins.p[j];
-    auto load_in = [&](int e) -> cx<T> {
-      return valid ? src[line + e * stride] : mkc<T>(0, 0);
-    };
+    const StridedLine<T> src(ins.p[j], line, stride, lane);
+    auto load_in = [&](int e) -> cx<T> { return src(e); };
     cx<T> V[X::BPT][X::RL];
-    fft_fwd_to_regs<T, N, PlanG<N>>(lane, B, lidx, tw, load_in, V);
+    fft_fwd_to_regs<T, N>(lane, B, lidx, tw, load_in, V);
     const T dyz = one_term(gs.cy[j], dy) * one_term(gs.cz[j], dz);
 #pragma unroll
     for (int b = 0; b < X::BPT; ++b) {
@@ -1154,10 +1180,11 @@ __global__ __launch_bounds__((FCfg<T, N, PlanG<N>>::THREADS)) void k_x_gather(
       acc[b][r] = cscale<T>(acc[b][r], k_factor<T>(n2, white, div, wtab));
     }
   }
+  const StridedLine<T> dst(out, line, stride, lane);
   auto store_o = [&](int e, cx<T> v) {
-    if (valid) out[line + e * stride] = v;
+    if (valid) dst(e) = v;
   };
-  fft_inv_from_regs<T, N, PlanG<N>>(lane, B, lidx, tw, acc, store_o);
+  fft_inv_from_regs<T, N>(lane, B, lidx, tw, acc, store_o);
 }
 
 // The gather of grids too small to fill the chip: thread group j of the
@@ -1169,8 +1196,8 @@ template <typename T, int N>
 __global__ __launch_bounds__(1024) void k_x_gather_wide(
     InPtrs<T> ins, GatherSet<T> gs, int white, int div, int m, cx<T>* out,
     const T* __restrict__ wtab, const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
-  using C = FCfg<T, N, PlanG<N>>;
-  using X = XPlan<N, PlanG<N>>;
+  using C = FCfg<T, N>;
+  using X = XPlan<N>;
   extern __shared__ char smem[];
   cx<T>* tw = reinterpret_cast<cx<T>*>(smem);
   cx<T>* tiles = tw + N;
@@ -1179,17 +1206,17 @@ __global__ __launch_bounds__(1024) void k_x_gather_wide(
   cx<T>* B = tiles + j * N * C::LP;
   const int l = t % C::LINES;
   const int lane = t / C::LINES;
-  const int line = blockIdx.x * C::LINES + l;
+  const int line = x_line<T, N>() + l;
   const int ky = line / kp, kz = line % kp;
-  const bool valid = line < nlines && kz < K;
+  const bool valid = kz < K;  // row padding is transformed too, and not stored
   const long long stride = (long long)nlines;  // = N * kp
   const int iy = wave_index(ky, N), iz = kz;
   const T dy = wave_deriv<T>(ky, N), dz = static_cast<T>(kz == N / 2 ? 0 : kz);
   auto lidx = [&](int e) { return e * C::LP + l; };
   const cx<T>* src = ins.p[j];
-  auto load_in = [&](int e) -> cx<T> { return valid ? src[line + e * stride] : mkc<T>(0, 0); };
+  auto load_in = [&](int e) -> cx<T> { return src[line + e * stride]; };
   cx<T> V[X::BPT][X::RL];
-  fft_fwd_to_regs<T, N, PlanG<N>>(lane, B, lidx, tw, load_in, V);
+  fft_fwd_to_regs<T, N>(lane, B, lidx, tw, load_in, V);
   __syncthreads();
   const T dyz = one_term(gs.cy[j], dy) * one_term(gs.cz[j], dz);
 #pragma unroll
@@ -1217,7 +1244,7 @@ __global__ __launch_bounds__(1024) void k_x_gather_wide(
   auto store_o = [&](int e, cx<T> v) {
     if (valid && j == 0) out[line + e * stride] = v;
   };
-  fft_inv_from_regs<T, N, PlanG<N>>(lane, B, lidx, tw, V, store_o);
+  fft_inv_from_regs<T, N>(lane, B, lidx, tw, V, store_o);
 }
 
 // ------------------------------------------------- layout conversion
@@ -1454,7 +1481,7 @@ void x_scatter(const FftArgs<T>& f, const fftk::InPtrs<T>& ip, const int* white,
                const fftk::XOutSet<T>& set, int m) {
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
-    using C = fftk::FCfg<T, N, fftk::PlanS<T, N, NIN>>;
+    using C = fftk::FCfg<T, N>;
     const int K = N / 2 + 1;
     const int nlines = N * f.kp;
     const unsigned blocks = blocks_for(nlines, C::LINES);
@@ -1501,7 +1528,7 @@ void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const Mul* muls,
   }
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
-    using C = fftk::FCfg<T, N, fftk::PlanG<N>>;
+    using C = fftk::FCfg<T, N>;
     const int K = N / 2 + 1;
     const int nlines = N * f.kp;
     const unsigned blocks = blocks_for(nlines, C::LINES);
