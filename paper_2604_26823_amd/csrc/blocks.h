@@ -396,30 +396,96 @@ constexpr int kXcds = 8;
 // two orders of nwg = item_grid() records, one per workgroup: by_index in
 // index order, by_xcd dealt so that each XCD gets a contiguous range (see
 // item_of).  A workgroup then starts with one 16-byte load; looking up the
-// item count, the item and the block's slots took three dependent ones.
-static __global__ __launch_bounds__(256) void k_fill_items(const unsigned* __restrict__ start,
-                                                    const unsigned* __restrict__ istart,
-                                                    unsigned nb, unsigned nwg,
-                                                    uint4* __restrict__ by_index,
-                                                    uint4* __restrict__ by_xcd) {
-  const unsigned n = istart[nb];
-  const unsigned per = (n + kXcds - 1) / kXcds;
-  const unsigned t0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
-  for (unsigned b = t0; b < nb; b += step) {
-    const unsigned s0 = start[b], s1 = start[b + 1];
-    unsigned i = istart[b];
-    const unsigned flag = s1 - s0 <= static_cast<unsigned>(kChunk) ? kSingle : 0u;
-    for (unsigned s = s0; s < s1; s += kChunk, ++i) {
-      const uint4 v = make_uint4(b, s, min(s + kChunk, s1), i | flag);
-      by_index[i] = v;
-      by_xcd[(i % per) * kXcds + i / per] = v;
-    }
+// item count, the item and the block's slots took three dependent ones.  The
+// counts are left zeroed for the next order.
+__device__ __forceinline__ void write_items(unsigned b, unsigned s0, unsigned s1, unsigned i,
+                                            unsigned per, uint4* __restrict__ by_index,
+                                            uint4* __restrict__ by_xcd) {
+  const unsigned flag = s1 - s0 <= static_cast<unsigned>(kChunk) ? kSingle : 0u;
+  for (unsigned s = s0; s < s1; s += kChunk, ++i) {
+    const uint4 v = make_uint4(b, s, min(s + kChunk, s1), i | flag);
+    by_index[i] = v;
+    by_xcd[(i % per) * kXcds + i / per] = v;
   }
+}
+// The records of the workgroups past the n items.
+__device__ __forceinline__ void write_ends(unsigned n, unsigned per, unsigned nwg, unsigned t0,
+                                           unsigned step, uint4* __restrict__ by_index,
+                                           uint4* __restrict__ by_xcd) {
   for (unsigned w = t0; w < nwg; w += step) {
     if (w >= n) by_index[w] = make_uint4(0u, 0u, 0u, 0u);
     if (w / kXcds >= per || (w % kXcds) * per + w / kXcds >= n)
       by_xcd[w] = make_uint4(0u, 0u, 0u, 0u);
   }
+}
+static __global__ __launch_bounds__(256) void k_fill_items(const unsigned* __restrict__ start,
+                                                    const unsigned* __restrict__ istart,
+                                                    unsigned nb, unsigned nwg,
+                                                    uint4* __restrict__ by_index,
+                                                    uint4* __restrict__ by_xcd,
+                                                    unsigned* __restrict__ count) {
+  const unsigned n = istart[nb];
+  const unsigned per = (n + kXcds - 1) / kXcds;
+  const unsigned t0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+  for (unsigned b = t0; b < nb; b += step) {
+    write_items(b, start[b], start[b + 1], istart[b], per, by_index, by_xcd);
+    count[b] = 0u;
+  }
+  write_ends(n, per, nwg, t0, step, by_index, by_xcd);
+}
+
+// The scan and the items of an order of at most kOneBlocks blocks (grids up to
+// 128^3) by one workgroup: the four launches of the general path, three of them
+// scans of a few thousand counts, took 12 us of every step at 32^3 and 64^3.
+constexpr unsigned kOneThreads = 1024;
+constexpr unsigned kOnePer = 4;
+constexpr unsigned kOneBlocks = kOneThreads * kOnePer;
+static __global__ __launch_bounds__(kOneThreads) void k_order_one(
+    unsigned* __restrict__ count, unsigned nb, unsigned nwg, unsigned* __restrict__ start,
+    unsigned* __restrict__ istart, uint4* __restrict__ by_index, uint4* __restrict__ by_xcd) {
+  __shared__ unsigned long long wsum[kOneThreads / 64];
+  const unsigned t = threadIdx.x, lane = t & 63, w = t >> 6;
+  unsigned c[kOnePer];
+  unsigned long long sum = 0;  // items << 32 | particles
+#pragma unroll
+  for (unsigned j = 0; j < kOnePer; ++j) {
+    const unsigned b = t * kOnePer + j;
+    c[j] = b < nb ? count[b] : 0u;
+    sum += static_cast<unsigned long long>((c[j] + kChunk - 1) / kChunk) << 32 | c[j];
+  }
+  unsigned long long s = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned long long o = __shfl_up(s, off, 64);
+    if (lane >= static_cast<unsigned>(off)) s += o;
+  }
+  if (lane == 63) wsum[w] = s;
+  __syncthreads();
+  unsigned long long before = 0, total = 0;
+  for (unsigned q = 0; q < kOneThreads / 64; ++q) {
+    before += q < w ? wsum[q] : 0ull;
+    total += wsum[q];
+  }
+  s += before - sum;
+  const unsigned n = static_cast<unsigned>(total >> 32);
+  const unsigned per = (n + kXcds - 1) / kXcds;
+  unsigned p = static_cast<unsigned>(s), i = static_cast<unsigned>(s >> 32);
+#pragma unroll
+  for (unsigned j = 0; j < kOnePer; ++j) {
+    const unsigned b = t * kOnePer + j;
+    if (b >= nb) break;
+    start[b] = p;
+    istart[b] = i;
+    count[b] = 0u;
+    write_items(b, p, p + c[j], i, per, by_index, by_xcd);
+    p += c[j];
+    i += (c[j] + kChunk - 1) / kChunk;
+  }
+  if (t == 0) {
+    start[nb] = static_cast<unsigned>(total);
+    istart[nb] = n;
+  }
+  write_ends(n, per, nwg, t, kOneThreads, by_index, by_xcd);
 }
 
 // Moves nf fields (and the ids) of slot a to slot start[key[a]] + rank[a] of
@@ -436,24 +502,6 @@ __global__ __launch_bounds__(kThreads) void k_scatter(
   const unsigned s = start[key[a]] + rank[a];
   for (int f = 0; f < nf; ++f) dst.p[f][s] = src.p[f][a];
   ids_dst[s] = ids_src ? ids_src[a] : static_cast<unsigned>(a);
-  dest[a] = s;
-}
-
-// The ids of slot a (a itself when ids_src is null) to slot
-// s = start[key[a]] + rank[a] of the new order, dest[a] = s, and inv[s] = a:
-// the new order's map back to this one, through which the next kernels read
-// the state left in this order.
-static __global__ __launch_bounds__(kThreads) void k_scatter_ids(
-    const unsigned* __restrict__ key, const unsigned* __restrict__ rank,
-    const unsigned* __restrict__ start, const unsigned* __restrict__ ids_src,
-    unsigned* __restrict__ ids_dst, unsigned* __restrict__ dest, unsigned* __restrict__ inv,
-    long long P) {
-  const long long a = blockIdx.x * (long long)kThreads + threadIdx.x;
-  if (a >= P) return;
-  const unsigned id = ids_src ? ids_src[a] : static_cast<unsigned>(a);
-  const unsigned s = start[key[a]] + rank[a];
-  ids_dst[s] = id;
-  inv[s] = static_cast<unsigned>(a);
   dest[a] = s;
 }
 
@@ -640,28 +688,6 @@ __global__ __launch_bounds__(kThreads) void k_scatter_b(Items it, Layout L, Layo
       if (!ok[k]) continue;
       for (int f = 0; f < nf; ++f) dst.p[f][s[k]] = src.p[f][a[k]];
       ids_dst[s[k]] = id[k];
-      dest[a[k]] = s[k];
-    }
-  });
-}
-
-// The ids alone to the next order's slots, dest[a] = the slot of slot a, and
-// inv[s] = a: the new order's map back to this one, through which the next
-// kernels read the state left in this order.
-static __global__ __launch_bounds__(kThreads) void k_scatter_ids_b(
-    Items it, Layout L, Layout Ld, int rs, Moves mv, unsigned* __restrict__ ids_dst,
-    unsigned* __restrict__ dest, unsigned* __restrict__ inv) {
-  __shared__ unsigned first[kNbr];
-  Item m;
-  if (!item_of<true>(it, L, m)) return;
-  for_moves(m, it.ids, mv, Ld, rs, first, [&](const auto& a, const auto& ok, const auto& id,
-                                              const auto& s) {
-    constexpr int R = sizeof(s) / sizeof(s[0]);
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-      if (!ok[k]) continue;
-      ids_dst[s[k]] = id[k];
-      inv[s[k]] = static_cast<unsigned>(a[k]);
       dest[a[k]] = s[k];
     }
   });
@@ -877,10 +903,10 @@ __device__ __forceinline__ void flush_owned(const Item& m, const Layout& L,
 // lane (kx, ky) clears the eight cells of its z row and its z-halo entry.
 // istart: the order's item starts per block (nb + 1).
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_zero_unowned(const unsigned* __restrict__ istart,
-                                                           Layout L, int nf, MPtrs<T> dst,
-                                                           T* __restrict__ zh) {
-  const long long t = blockIdx.x * (long long)kThreads + threadIdx.x;
+__device__ __forceinline__ void zero_unowned(long long wg, const unsigned* __restrict__ istart,
+                                             const Layout& L, int nf, const MPtrs<T>& dst,
+                                             T* __restrict__ zh) {
+  const long long t = wg * kThreads + threadIdx.x;
   const long long b = t >> 6;
   if (b >= (1ll << (3 * L.lnb))) return;
   if (istart[b + 1] - istart[b] == 1u) return;
@@ -898,6 +924,75 @@ __global__ __launch_bounds__(kThreads) void k_zero_unowned(const unsigned* __res
     for (int z = 0; z < kB; ++z) dst.p[f][row + z] = T(0);
     zh[f * zplane + zc] = T(0);
   }
+}
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_zero_unowned(const unsigned* __restrict__ istart,
+                                                           Layout L, int nf, MPtrs<T> dst,
+                                                           T* __restrict__ zh) {
+  zero_unowned(blockIdx.x, istart, L, nf, dst, zh);
+}
+inline unsigned zero_grid(const Layout& L) {
+  return static_cast<unsigned>(((1ll << (3 * L.lnb)) * 64 + kThreads - 1) / kThreads);
+}
+
+// What a density paint of the new order needs zeroed, done by extra workgroups of
+// the kernel that moves the ids there (wg0: the first of them).
+template <typename T>
+struct ZeroFirst {
+  unsigned wg0;
+  const unsigned* istart;
+  T* rho;
+  T* zh;
+};
+
+// The ids of slot a (a itself when ids_src is null) to slot
+// s = start[key[a]] + rank[a] of the new order, dest[a] = s, and inv[s] = a:
+// the new order's map back to this one, through which the next kernels read
+// the state left in this order.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_scatter_ids(
+    const unsigned* __restrict__ key, const unsigned* __restrict__ rank,
+    const unsigned* __restrict__ start, const unsigned* __restrict__ ids_src,
+    unsigned* __restrict__ ids_dst, unsigned* __restrict__ dest, unsigned* __restrict__ inv,
+    long long P, Layout L, ZeroFirst<T> zf) {
+  if (blockIdx.x >= zf.wg0) {
+    zero_unowned(blockIdx.x - zf.wg0, zf.istart, L, 1, MPtrs<T>{{zf.rho}}, zf.zh);
+    return;
+  }
+  const long long a = blockIdx.x * (long long)kThreads + threadIdx.x;
+  if (a >= P) return;
+  const unsigned id = ids_src ? ids_src[a] : static_cast<unsigned>(a);
+  const unsigned s = start[key[a]] + rank[a];
+  ids_dst[s] = id;
+  inv[s] = static_cast<unsigned>(a);
+  dest[a] = s;
+}
+
+// The ids alone to the next order's slots, dest[a] = the slot of slot a, and
+// inv[s] = a: the new order's map back to this one, through which the next
+// kernels read the state left in this order.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_scatter_ids_b(
+    Items it, Layout L, Layout Ld, int rs, Moves mv, unsigned* __restrict__ ids_dst,
+    unsigned* __restrict__ dest, unsigned* __restrict__ inv, ZeroFirst<T> zf) {
+  if (blockIdx.x >= zf.wg0) {
+    zero_unowned(blockIdx.x - zf.wg0, zf.istart, Ld, 1, MPtrs<T>{{zf.rho}}, zf.zh);
+    return;
+  }
+  __shared__ unsigned first[kNbr];
+  Item m;
+  if (!item_of<true>(it, L, m)) return;
+  for_moves(m, it.ids, mv, Ld, rs, first, [&](const auto& a, const auto& ok, const auto& id,
+                                              const auto& s) {
+    constexpr int R = sizeof(s) / sizeof(s[0]);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if (!ok[k]) continue;
+      ids_dst[s[k]] = id[k];
+      inv[s[k]] = static_cast<unsigned>(a[k]);
+      dest[a[k]] = s[k];
+    }
+  });
 }
 
 // Output of a paint in deterministic mode: the integer fields det (nf fields

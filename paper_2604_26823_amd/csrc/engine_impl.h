@@ -612,9 +612,16 @@ class Engine final : public EngineBase {
 
   void zero_counts(unsigned nb) { ek_fill_u32(bcount_, 0u, nb); }
 
-  // Scan of the block counts in bcount_ into o, and its work items.
+  // Scan of the block counts in bcount_ into o, and its work items; the counts
+  // are left zeroed.
   void build_order(const Order& o) {
     auto sc = timer_.scope("sort_scan", 16.0 * o.nb);
+    if (o.nb <= bk::kOneBlocks) {
+      bk::k_order_one<<<1, bk::kOneThreads, 0, st_>>>(bcount_, o.nb, o.nwg, o.start, o.istart,
+                                                      o.items, o.items + o.nwg);
+      IC_LAUNCHED();
+      return;
+    }
     const unsigned chunks = (o.nb + bk::kScanChunk - 1) / bk::kScanChunk;
     if (chunks > 1024) throw ApiError(IC_ERR_UNSUPPORTED, "too many particle blocks");
     bk::k_scan_sums<<<chunks, 256, 0, st_>>>(bcount_, o.nb, bsums_);
@@ -624,7 +631,7 @@ class Engine final : public EngineBase {
     bk::k_scan_out<<<chunks, 256, 0, st_>>>(bcount_, o.nb, bsums_, o.start, o.istart);
     IC_LAUNCHED();
     bk::k_fill_items<<<grid_for(o.nwg, 256), 256, 0, st_>>>(o.start, o.istart, o.nb, o.nwg,
-                                                            o.items, o.items + o.nwg);
+                                                            o.items, o.items + o.nwg, bcount_);
     IC_LAUNCHED();
   }
 
@@ -637,14 +644,22 @@ class Engine final : public EngineBase {
     IC_LAUNCHED();
   }
 
-  // The ids alone to the order o (keys and ranks in bkey_ / brank_; ids_src
+  // The moves of ids end in a density paint of the same order: they also zero
+  // what that paint needs (the deterministic paints zero their own fields).
+  unsigned zero_wgs() const { return det_ ? 0u : bk::zero_grid(Lm_); }
+  bk::ZeroFirst<T> zero_first(const Order& o, unsigned wg0) const {
+    return bk::ZeroFirst<T>{wg0, o.istart, rhom_, zh_};
+  }
+
+  // The ids alone to the mesh order o (keys and ranks in bkey_ / brank_; ids_src
   // null means the lattice order), the destinations to dst_slots, and pinv_
   // = o's slots to the source order's.
   void scatter_ids(const Order& o, const unsigned* ids_src, unsigned* ids_dst,
                    unsigned* dst_slots) {
     auto sc = timer_.scope("sort_scatter_ids", P_ * 24.0);
-    bk::k_scatter_ids<<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
-        bkey_, brank_, o.start, ids_src, ids_dst, dst_slots, pinv_, P_);
+    const unsigned g = grid_for(P_, bk::kThreads, 1u << 30);
+    bk::k_scatter_ids<T><<<g + zero_wgs(), bk::kThreads, 0, st_>>>(
+        bkey_, brank_, o.start, ids_src, ids_dst, dst_slots, pinv_, P_, Lm_, zero_first(o, g));
     IC_LAUNCHED();
   }
 
@@ -661,8 +676,10 @@ class Engine final : public EngineBase {
   }
   void move_ids(const bk::Items& src, const Order& o, unsigned* ids_dst, unsigned* dst_slots) {
     auto sc = timer_.scope("sort_scatter_ids", P_ * 20.0);
-    bk::k_scatter_ids_b<<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
-        src, Lm_, Lm_, 0, bk::Moves{bkey_, brank_, bnbr_, o.start}, ids_dst, dst_slots, pinv_);
+    const unsigned g = bk::item_grid(Lm_, P_);
+    bk::k_scatter_ids_b<T><<<g + zero_wgs(), bk::kThreads, 0, st_>>>(
+        src, Lm_, Lm_, 0, bk::Moves{bkey_, brank_, bnbr_, o.start}, ids_dst, dst_slots, pinv_,
+        zero_first(o, g));
     IC_LAUNCHED();
   }
 
@@ -747,7 +764,8 @@ class Engine final : public EngineBase {
   // rho = CIC density of the state in order o (positions d, ids id), its
   // z halo left in zh (ncells / 8 values) for the consumer; every cell of
   // rho and zh is written here.  With gsrc the positions are read as
-  // d[gsrc[a]] (left in the previous order) and stored in order o to dcopy.
+  // d[gsrc[a]] (left in the previous order) and stored in order o to dcopy, and
+  // the ids' move to o has zeroed what needs it.
   void paint(const T* d, const Order& o, const unsigned* id, const pk::Grid<T>& g,
              const bk::Layout& L, T* rho, T* zh, long long ncells,
              const unsigned* gsrc = nullptr, T* dcopy = nullptr) {
@@ -766,7 +784,7 @@ class Engine final : public EngineBase {
       fill(zh, T(0), ncells / kZHalo);  // the halo is in rho already
       return;
     }
-    zero_unowned(o, L, 1, bk::MPtrs<T>{{rho}}, zh);
+    if (!gsrc) zero_unowned(o, L, 1, bk::MPtrs<T>{{rho}}, zh);  // else zeroed by the ids' move
     {
       auto sc = timer_.scope("cic_paint", bytes);
       bk::k_paint_b<T, false><<<o.max_items + 8, bk::kThreads, 0, st_>>>(
@@ -1069,7 +1087,6 @@ class Engine final : public EngineBase {
       pinv = pinv_;
     }
     for (int n = 0; n < S_; ++n) {
-      zero_counts(nbm_);
       const bool complete = state_complete(n + 1);
       // the new momenta go to a buffer the step does not read, and that a
       // complete sort can move into pslot(n + 1) (never tmpp_ or pbar2_)
@@ -1099,7 +1116,6 @@ class Engine final : public EngineBase {
       }
     }
     seg_ = K_ ? S_ - S_ % K_ : 0;
-    zero_counts(nbd_);
     {
       auto sc = timer_.scope("final_kick", P_ * (9.0 * sizeT() + 12.0) + 3.0 * M_ * sizeT());
       // the final momenta go to pslot(S) in order S (in place when state S
