@@ -737,10 +737,14 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
   T* __restrict__ out = fields.f[blockIdx.y].out;
   __shared__ cx<T> buf[n * C::LS];
   __shared__ cx<T> tw[N];
-  load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
+  __shared__ cx<T> edge[N];  // the column kz = n/2
   const int t = threadIdx.x;
   const size_t x = blockIdx.x;
   const int c = t % n, r0 = t / n;
+  if (t < N) {
+    tw[t] = twg[t];
+    edge[t] = in[(x * N + t) * kp + n];
+  }
   // held values: PER - 1 in registers, the last in LDS (the register file
   // is full)
   __shared__ cx<T> spare[C::THREADS];
@@ -749,14 +753,27 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
   auto cidx = [&](int e) { return e * C::LS + zl(c); };
   auto cstore = [&](int e, cx<T> v) { buf[cidx(e)] = v; };
   // inverse y transforms of the even and odd rows ky, the packed column
-  // read as X(ky, 0) + i X(ky, n/2) (k~z is 0 for both)
+  // read as X(ky, 0) + i X(ky, n/2) (k~z is 0 for both).  The column kz = n/2
+  // comes through LDS: a second load per element, needed by column 0 only, took
+  // three fields from 116 to 140 us.
   const YZMul<T>& mul = fields.f[blockIdx.y].mul;
   const T dz = one_term(mul.d, static_cast<T>(c));
   for (int par = 0; par < 2; ++par) {
-    auto load0 = [&](int e) -> cx<T> {  // both loads for every column: no branch
-      const cx<T>* row = in + (x * N + 2 * e + par) * kp;
-      const cx<T> u = row[c], v = row[n];
-      return times_yz<T>(c != 0 ? u : mkc<T>(u.x - v.y, u.y + v.x), mul, 2 * e + par, N, dz);
+    constexpr int RAW = n / C::TPL;  // element r0 + r TPL
+    cx<T> raw[RAW];
+#pragma unroll
+    for (int r = 0; r < RAW; ++r)
+      raw[r] = in[(x * N + 2 * (r0 + r * C::TPL) + par) * kp + c];
+    if (par == 0) __syncthreads();  // edge
+    if (c == 0) {
+#pragma unroll
+      for (int r = 0; r < RAW; ++r) {
+        const cx<T> v = edge[2 * (r0 + r * C::TPL) + par];
+        raw[r] = mkc<T>(raw[r].x - v.y, raw[r].y + v.x);
+      }
+    }
+    auto load0 = [&](int e) -> cx<T> {
+      return times_yz<T>(raw[(e - r0) / C::TPL], mul, 2 * e + par, N, dz);
     };
     fft_line<T, n, false>(r0, buf, cidx, tw, 2, load0, cstore);
     __syncthreads();
@@ -822,7 +839,7 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_c2r_yz(
 // one kernel that crosses HBM once each way, and all fields of a chain go in
 // one launch.  At 32^3 and 64^3 every launch takes 3-4 us whatever it does:
 // there the launches saved count (nine per force chain become three); at
-// 128^3 the two passes saved do as well: three fields take 41 us instead of 55
+// 128^3 the two passes saved do as well: three fields take 37 us instead of 55
 // in FP64.  A 32^3 FP64 evaluation went from 1244 to 790 us, a 64^3 FP32 forward
 // run from 1245 to 832, a 128^3 FP64 forward run and gradient from 10.25 to
 // 9.47 ms.
@@ -931,18 +948,33 @@ __global__ __launch_bounds__((PlCfg<T, N>::THREADS)) void k_plane_inv(
   constexpr int n = C::n;
   __shared__ cx<T> buf[C::TROWS * C::LS];
   __shared__ cx<T> tw[N];
-  load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
+  __shared__ cx<T> edge[N];  // the column kz = n (see k_c2r_yz)
   const PlaneInv<T>& fl = fields.f[blockIdx.y];
   const int t = threadIdx.x;
   const size_t x = blockIdx.x;
   {
     const int c = t % C::COLS, r0 = t / C::COLS;
-    const int ci = c < n ? c : n - 1, cj = c == 0 ? n : ci;
+    const int ci = c < n ? c : n - 1;
     const cx<T>* __restrict__ in = fl.S + x * N * kp;
     const T dz = one_term(fl.mul.d, static_cast<T>(ci));
-    auto load0 = [&](int e) -> cx<T> {  // both loads for every column: no branch
-      const cx<T> u = in[e * kp + ci], v = in[e * kp + cj];
-      return times_yz<T>(c != 0 ? u : mkc<T>(u.x - v.y, u.y + v.x), fl.mul, e, N, dz);
+    for (int i = t; i < N; i += C::THREADS) {
+      tw[i] = twg[i];
+      edge[i] = in[i * kp + n];
+    }
+    constexpr int TPL = PlanY<T, N>::TPL, RAW = N / TPL;  // element r0 + r TPL
+    cx<T> raw[RAW];
+#pragma unroll
+    for (int r = 0; r < RAW; ++r) raw[r] = in[(r0 + r * TPL) * kp + ci];
+    __syncthreads();  // edge
+    if (c == 0) {
+#pragma unroll
+      for (int r = 0; r < RAW; ++r) {
+        const cx<T> v = edge[r0 + r * TPL];
+        raw[r] = mkc<T>(raw[r].x - v.y, raw[r].y + v.x);
+      }
+    }
+    auto load0 = [&](int e) -> cx<T> {
+      return times_yz<T>(raw[(e - r0) / TPL], fl.mul, e, N, dz);
     };
     auto cidx = [&](int e) { return e * C::LS + zl(c); };
     auto cstore = [&](int e, cx<T> v) { buf[cidx(e)] = v; };
