@@ -334,26 +334,22 @@ class Engine final : public EngineBase {
                                                                   out, P_);
     IC_LAUNCHED();
     auto f = fa(0);
-    fft_r2c_z<T>(f, out, T(1), nullptr, T(0), pool_);
-    fft_y<T>(f, pool_, true);
-    fft_x<T>(f, pool_, pool_, true, T(1));
-    const long long modes = (long long)nl * nl * (nl / 2);
-    fk::k_embed_coarse<T><<<grid_for(modes, kThreads), kThreads, 0, st_>>>(
-        zl, nl, pool_, np_, kpp_, static_cast<T>(std::pow((double)np_ / nl, 1.5)));
-    IC_LAUNCHED();
-    fft_x<T>(f, pool_, pool_, false, T(1.0 / (double)P_));
-    fft_y<T>(f, pool_, false);
-    fft_c2r_z<T>(f, pool_, out, T(1), nullptr, T(0));
+    const double U = (double)P_ * sizeT(), Hb = half_spectrum_bytes(f.n);
+    const GIn in{out, T(1), nullptr, T(0), nullptr};
+    cx<T>* const S[1] = {pool_};
+    r2c_zy(f, &in, S, 1, U, Hb);
+    fft_x_embed<T>(f, pool_, zl, nl, static_cast<T>(std::pow((double)np_ / nl, 1.5)),
+                   T(1.0 / (double)P_));
+    const YOut yo{pool_, yz_one<T>(), out};
+    c2r_yz(f, &yo, 1, pool_, nullptr, T(0), U, Hb, false);
   }
 
   // Spectra cross the ABI in the contiguous n x n x (n/2+1) layout.
   void op_rfft(int grid, const void* x, void* xk) override {
     auto f = fa(grid);
-    {
-      auto sc = timer_.scope("fft_r2c_z", 0);
-      fft_r2c_z<T>(f, static_cast<const T*>(x), T(1), nullptr, T(0), pool_);
-    }
-    fft_y<T>(f, pool_, true);
+    const GIn in{static_cast<const T*>(x), T(1), nullptr, T(0), nullptr};
+    cx<T>* const S[1] = {pool_};
+    r2c_zy(f, &in, S, 1, 0, 0);
     fft_x<T>(f, pool_, pool_, true, T(1));
     spectrum_pack<T>(f, pool_, static_cast<cx<T>*>(xk));
   }

@@ -164,6 +164,15 @@ template <typename T>
 void fft_x_scatter(const FftArgs<T>& f, const cx<T>* const* in, const int* white, int nin,
                    int div, const XOut<T>* outs, int m);
 
+// White-noise upsampling (section 3, the resolution schedule): forward x FFT of
+// S, whose modes with every wave index strictly inside (-nl/2, nl/2) are
+// replaced by scale times those of the coarse spectrum lo ([nl][nl][nl/2+1],
+// dense; its Nyquist rows are not used), then norm times the inverse x FFT, in
+// place.  scale = (n/nl)^{3/2}: the unnormalised DFT of unit white noise grows
+// as the root of the cell count.
+template <typename T>
+void fft_x_embed(const FftArgs<T>& f, cx<T>* S, const cx<T>* lo, int nl, T scale, T norm);
+
 // out = inverse x FFT of sum_j mult_j * forward x FFT of ins[j]; out may equal
 // ins[0].  The multipliers share white and div.
 template <typename T>

@@ -18,4 +18,5 @@ template void fft_x_scatter<float>(const FftArgs<float>&, const cx<float>* const
                                    int, const XOut<float>*, int);
 template void fft_x_gather<float>(const FftArgs<float>&, const cx<float>* const*, const Mul*, int,
                                   cx<float>*);
+template void fft_x_embed<float>(const FftArgs<float>&, cx<float>*, const cx<float>*, int, float, float);
 }  // namespace ic

@@ -1279,6 +1279,50 @@ __global__ __launch_bounds__(1024) void k_x_gather_wide(
   fft_inv_from_regs<T, N>(lane, B, lidx, tw, V, store_o);
 }
 
+// The x passes of the white-noise upsampling (fft_x_embed): one pass over the
+// spectrum, where two transforms and a kernel that wrote the coarse modes between
+// them took three (25 + 12 + 25 us at 256^3 in FP32).
+template <typename T, int N>
+__global__ __launch_bounds__((FCfg<T, N>::THREADS)) void k_x_embed(
+    cx<T>* S, const cx<T>* __restrict__ lo, int nl, T scale, T norm,
+    const cx<T>* __restrict__ twg, int nlines, int K, int kp) {
+  using C = FCfg<T, N>;
+  using X = XPlan<N>;
+  __shared__ cx<T> B[N * C::LP];
+  __shared__ cx<T> tw[N];
+  load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
+  const int l = threadIdx.x % C::LINES;
+  const int lane = threadIdx.x / C::LINES;
+  const int line = x_line<T, N>() + l;
+  const int ky = line / kp, kz = line % kp;
+  const long long stride = (long long)nlines;  // = N * kp
+  auto lidx = [&](int e) { return e * C::LP + l; };
+  const StridedLine<T> io(S, line, stride, lane);
+  auto load_in = [&](int e) -> cx<T> { return io(e); };
+  cx<T> V[X::BPT][X::RL];
+  fft_fwd_to_regs<T, N>(lane, B, lidx, tw, load_in, V);
+  // coarse index of fine index i, and whether the band holds it
+  const int h = nl / 2;
+  auto coarse = [&](int i) { return i < h ? i : i - (N - nl); };
+  auto inside = [&](int i) { return i < h || i > N - h; };
+  if (kz < h && inside(ky)) {
+    const cx<T>* row = lo + static_cast<long long>(coarse(ky)) * (h + 1) + kz;
+    const long long plane = static_cast<long long>(nl) * (h + 1);
+#pragma unroll
+    for (int b = 0; b < X::BPT; ++b) {
+#pragma unroll
+      for (int r = 0; r < X::RL; ++r) {
+        const int e = lane + b * X::TPL + r * X::NBL;
+        if (inside(e)) V[b][r] = cscale<T>(row[coarse(e) * plane], scale);
+      }
+    }
+  }
+  auto store_o = [&](int e, cx<T> v) {
+    if (kz < K) io(e) = cscale<T>(v, norm);  // row padding is transformed too, and not stored
+  };
+  fft_inv_from_regs<T, N>(lane, B, lidx, tw, V, store_o);
+}
+
 // ------------------------------------------------- layout conversion
 // Copies between the stored half spectrum (row pitch kp) and the contiguous
 // [n][n][n/2+1] layout; pack = stored -> contiguous.
@@ -1574,6 +1618,18 @@ void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const Mul* muls,
     }
     fftk::k_x_gather<T, N><<<blocks, C::THREADS, 0, f.stream>>>(
         ip, gs, white, div, m, out, f.wtab, f.tw, nlines, K, f.kp);
+  });
+  IC_LAUNCHED();
+}
+
+template <typename T>
+void fft_x_embed(const FftArgs<T>& f, cx<T>* S, const cx<T>* lo, int nl, T scale, T norm) {
+  const int nlines = f.n * f.kp;
+  fftk::dispatch_n<T>(f.n, [&](auto NC) {
+    constexpr int N = decltype(NC)::value;
+    using C = fftk::FCfg<T, N>;
+    fftk::k_x_embed<T, N><<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(
+        S, lo, nl, scale, norm, f.tw, nlines, f.n / 2 + 1, f.kp);
   });
   IC_LAUNCHED();
 }

@@ -344,6 +344,18 @@ struct U64x4 {
   uint64_t v[4];
 };
 
+// hi 2^64 + lo = a b from its four 32-bit products, each taken once (the high
+// word alone takes all four, and a separate low word three more).
+__device__ __forceinline__ void mul_wide(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo) {
+  const uint64_t a0 = static_cast<uint32_t>(a), a1 = a >> 32;
+  const uint64_t b0 = static_cast<uint32_t>(b), b1 = b >> 32;
+  const uint64_t p = a0 * b0;
+  const uint64_t q = a0 * b1 + (p >> 32);
+  const uint64_t r = a1 * b0 + static_cast<uint32_t>(q);
+  hi = a1 * b1 + ((q >> 32) + (r >> 32));
+  lo = r << 32 | static_cast<uint32_t>(p);
+}
+
 __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2,
                                                uint64_t c3, uint64_t k0) {
   const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
@@ -355,8 +367,9 @@ __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_
       k0 += W0;
       k1 += W1;
     }
-    const uint64_t hi0 = __umul64hi(M0, c0), lo0 = M0 * c0;
-    const uint64_t hi1 = __umul64hi(M1, c2), lo1 = M1 * c2;
+    uint64_t hi0, lo0, hi1, lo1;
+    mul_wide(M0, c0, hi0, lo0);
+    mul_wide(M1, c2, hi1, lo1);
     const uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0;
     c1 = lo1;
@@ -391,31 +404,6 @@ __global__ void k_philox(int kind, uint64_t sub, uint64_t stream, uint64_t event
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
     out[i] = static_cast<T>(philox_draw(kind, (uint64_t)i, sub, stream, event, seed));
-}
-
-// White-noise upsampling (section 3, the resolution schedule): the modes of
-// a coarse field with every wave index strictly inside (-nl/2, nl/2) replace
-// those of a fine spectrum, times scale = (nh/nl)^{3/2} (the unnormalised DFT
-// of unit white noise grows as the cell count).  lo: dense coarse half
-// spectrum [nl][nl][nl/2+1]; hi: stored fine half spectrum [nh][nh][kp].  One
-// thread per coarse (i, j, kz < nl/2); the coarse Nyquist rows are skipped.
-template <typename T>
-__global__ void k_embed_coarse(const cx<T>* __restrict__ lo, int nl, cx<T>* __restrict__ hi,
-                               int nh, int kp, T scale) {
-  const int h = nl / 2;
-  const long long total = (long long)nl * nl * h;
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-       t += (long long)gridDim.x * blockDim.x) {
-    const int kz = static_cast<int>(t % h);
-    const long long r = t / h;
-    const int j = static_cast<int>(r % nl);
-    const int i = static_cast<int>(r / nl);
-    if (i == h || j == h) continue;
-    const int fi = i < h ? i : i + (nh - nl);
-    const int fj = j < h ? j : j + (nh - nl);
-    const cx<T> v = lo[((long long)i * nl + j) * (h + 1) + kz];
-    hi[((long long)fi * nh + fj) * kp + kz] = cscale<T>(v, scale);
-  }
 }
 
 // One projection pass: out = (x - mean) / std with mean = sum[0]/n and
