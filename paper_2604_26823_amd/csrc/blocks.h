@@ -263,8 +263,23 @@ __device__ __forceinline__ void rank_reserve_wg(unsigned b0, const Layout& L,
 }
 
 // ---------------------------------------------------------------- sorting
+// Particle of thread a when a kernel goes over the lattice to or from a block order:
+// a wavefront takes 8 x 4 x 2 (z, y, x) neighbouring sites, and consecutive
+// wavefronts follow along z.  Its particles are then in one block or a few, so
+// they get their ranks with as many atomics and their slots are a few
+// contiguous runs.  Wavefronts along z (64 sites: 8 blocks, or 16 when the mesh is twice
+// the lattice) gave every block runs of eight or four.
+__device__ __forceinline__ long long tile_site(long long a, int lp) {
+  const unsigned lane = static_cast<unsigned>(a) & 63u, t = static_cast<unsigned>(a >> 6);
+  const unsigned z = (t & ((1u << (lp - 3)) - 1)) << 3 | (lane & 7u);
+  const unsigned y = ((t >> (lp - 3)) & ((1u << (lp - 2)) - 1)) << 2 | (lane >> 3 & 3u);
+  const unsigned x = t >> (2 * lp - 5) << 1 | lane >> 5;
+  return static_cast<long long>((x << lp | y) << lp | z);
+}
+
 // Key and rank of every slot: the block of the stencil of displacement d
-// (particle ids[a], or a when ids is null) on grid g.
+// (particle ids[a] in slot a; when ids is null, thread a's is tile_site(a) and d
+// is in lattice order) on grid g.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_keys(const T* __restrict__ d,
                                                    const unsigned* __restrict__ ids, long long P,
@@ -276,11 +291,11 @@ __global__ __launch_bounds__(kThreads) void k_keys(const T* __restrict__ d,
   const bool ok = a < P;
   unsigned b = 0;
   if (ok) {
-    const long long j = ids ? static_cast<long long>(ids[a]) : a;
+    const long long j = ids ? static_cast<long long>(ids[a]) : tile_site(a, lp);
     int idx[3];
     pk::lattice(j, lp, idx);
     T dsp[3];
-    pk::load3(d, P, a, dsp);
+    pk::load3(d, P, ids ? a : j, dsp);
     Stencil<T> s = pk::stencil(idx, g.ratio, dsp, g.inv_cell, g.cell);
     b = block_of(s, L);
   }
@@ -488,33 +503,36 @@ static __global__ __launch_bounds__(kOneThreads) void k_order_one(
   write_ends(n, per, nwg, t, kOneThreads, by_index, by_xcd);
 }
 
-// Moves nf fields (and the ids) of slot a to slot start[key[a]] + rank[a] of
-// the new order; dest[a] receives that slot.  ids_src null means identity.
+// Moves nf fields (and the ids) of slot q to slot start[key[a]] + rank[a] of
+// the new order; dest[q] receives that slot.  q is a, or tile_site(a) when ids_src
+// is null (the lattice order, id = slot).
 // (Keys and ranks of k_keys; the moves between block orders are k_scatter_b.)
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_scatter(
     const unsigned* __restrict__ key, const unsigned* __restrict__ rank,
     const unsigned* __restrict__ start, Ptrs<T> src, MPtrs<T> dst, int nf,
     const unsigned* __restrict__ ids_src, unsigned* __restrict__ ids_dst,
-    unsigned* __restrict__ dest, long long P) {
+    unsigned* __restrict__ dest, long long P, int lp) {
   const long long a = blockIdx.x * (long long)kThreads + threadIdx.x;
   if (a >= P) return;
+  const long long q = ids_src ? a : tile_site(a, lp);
   const unsigned s = start[key[a]] + rank[a];
-  for (int f = 0; f < nf; ++f) dst.p[f][s] = src.p[f][a];
-  ids_dst[s] = ids_src ? ids_src[a] : static_cast<unsigned>(a);
-  dest[a] = s;
+  for (int f = 0; f < nf; ++f) dst.p[f][s] = src.p[f][q];
+  ids_dst[s] = ids_src ? ids_src[a] : static_cast<unsigned>(q);
+  dest[q] = s;
 }
 
-// dst_f[a] = src_f[dest[a]] for nf fields: values of the next order brought
-// back to this one.
+// dst_f[q] = src_f[dest[q]] for nf fields, q = tile_site(a): values of order 0
+// brought back to the lattice order.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_gather_back(const unsigned* __restrict__ dest,
                                                           Ptrs<T> src, MPtrs<T> dst, int nf,
-                                                          long long P) {
+                                                          long long P, int lp) {
   const long long a = blockIdx.x * (long long)kThreads + threadIdx.x;
   if (a >= P) return;
-  const unsigned s = dest[a];
-  for (int f = 0; f < nf; ++f) dst.p[f][a] = src.p[f][s];
+  const long long q = tile_site(a, lp);
+  const unsigned s = dest[q];
+  for (int f = 0; f < nf; ++f) dst.p[f][q] = src.p[f][s];
 }
 
 // dst_f[ids[a]] = src_f[a]: a sorted state back to lattice order.
@@ -945,27 +963,25 @@ struct ZeroFirst {
   T* zh;
 };
 
-// The ids of slot a (a itself when ids_src is null) to slot
-// s = start[key[a]] + rank[a] of the new order, dest[a] = s, and inv[s] = a:
-// the new order's map back to this one, through which the next kernels read
-// the state left in this order.
+// The ids of the lattice order's slots q = tile_site(a) to slots
+// s = start[key[a]] + rank[a] of the new order, dest[q] = s.  The new order's map
+// back, through which the next kernels read the state left in the lattice order,
+// is its ids.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_scatter_ids(
     const unsigned* __restrict__ key, const unsigned* __restrict__ rank,
-    const unsigned* __restrict__ start, const unsigned* __restrict__ ids_src,
-    unsigned* __restrict__ ids_dst, unsigned* __restrict__ dest, unsigned* __restrict__ inv,
-    long long P, Layout L, ZeroFirst<T> zf) {
+    const unsigned* __restrict__ start, unsigned* __restrict__ ids_dst,
+    unsigned* __restrict__ dest, long long P, int lp, Layout L, ZeroFirst<T> zf) {
   if (blockIdx.x >= zf.wg0) {
     zero_unowned(blockIdx.x - zf.wg0, zf.istart, L, 1, MPtrs<T>{{zf.rho}}, zf.zh);
     return;
   }
   const long long a = blockIdx.x * (long long)kThreads + threadIdx.x;
   if (a >= P) return;
-  const unsigned id = ids_src ? ids_src[a] : static_cast<unsigned>(a);
+  const long long q = tile_site(a, lp);
   const unsigned s = start[key[a]] + rank[a];
-  ids_dst[s] = id;
-  inv[s] = static_cast<unsigned>(a);
-  dest[a] = s;
+  ids_dst[s] = static_cast<unsigned>(q);
+  dest[q] = s;
 }
 
 // The ids alone to the next order's slots, dest[a] = the slot of slot a, and

@@ -392,9 +392,9 @@ class Engine final : public EngineBase {
         items(mesh_order(0), dids_), dbar2_, pbar2_, nullptr, nullptr, nullptr, nullptr);
     IC_LAUNCHED();
     T* F = static_cast<T*>(force);
-    bk::k_to_lattice<T><<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
-        dids_, bk::Ptrs<T>{{pbar2_, pbar2_ + P_, pbar2_ + 2 * P_}},
-        bk::MPtrs<T>{{F, F + P_, F + 2 * P_}}, 3, P_);
+    bk::k_gather_back<T><<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
+        dest(-1), bk::Ptrs<T>{{pbar2_, pbar2_ + P_, pbar2_ + 2 * P_}},
+        bk::MPtrs<T>{{F, F + P_, F + 2 * P_}}, 3, P_, lp_);
     IC_LAUNCHED();
   }
 
@@ -636,7 +636,7 @@ class Engine final : public EngineBase {
                const unsigned* ids_src, unsigned* ids_dst, unsigned* dst_slots) {
     auto sc = timer_.scope("sort_scatter", P_ * (2.0 * nf * sizeT() + 20.0));
     bk::k_scatter<T><<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
-        bkey_, brank_, o.start, src, dst, nf, ids_src, ids_dst, dst_slots, P_);
+        bkey_, brank_, o.start, src, dst, nf, ids_src, ids_dst, dst_slots, P_, lp_);
     IC_LAUNCHED();
   }
 
@@ -647,15 +647,14 @@ class Engine final : public EngineBase {
     return bk::ZeroFirst<T>{wg0, o.istart, rhom_, zh_};
   }
 
-  // The ids alone to the mesh order o (keys and ranks in bkey_ / brank_; ids_src
-  // null means the lattice order), the destinations to dst_slots, and pinv_
-  // = o's slots to the source order's.
-  void scatter_ids(const Order& o, const unsigned* ids_src, unsigned* ids_dst,
-                   unsigned* dst_slots) {
-    auto sc = timer_.scope("sort_scatter_ids", P_ * 24.0);
+  // The ids alone from the lattice order to the mesh order o (keys and ranks in
+  // bkey_ / brank_), the destinations to dst_slots; the ids are also o's slots to
+  // the lattice order's.
+  void scatter_ids(const Order& o, unsigned* ids_dst, unsigned* dst_slots) {
+    auto sc = timer_.scope("sort_scatter_ids", P_ * 16.0);
     const unsigned g = grid_for(P_, bk::kThreads, 1u << 30);
     bk::k_scatter_ids<T><<<g + zero_wgs(), bk::kThreads, 0, st_>>>(
-        bkey_, brank_, o.start, ids_src, ids_dst, dst_slots, pinv_, P_, Lm_, zero_first(o, g));
+        bkey_, brank_, o.start, ids_dst, dst_slots, P_, lp_, Lm_, zero_first(o, g));
     IC_LAUNCHED();
   }
 
@@ -1077,10 +1076,10 @@ class Engine final : public EngineBase {
               nullptr, ids(0), dest(-1));
       force_mesh(0, gslot(0));
     } else {
-      scatter_ids(mesh_order(0), nullptr, ids(0), dest(-1));
-      force_mesh(0, gslot(0), pinv_);
+      scatter_ids(mesh_order(0), ids(0), dest(-1));
+      force_mesh(0, gslot(0), ids(0));
       pin = tmpp_;
-      pinv = pinv_;
+      pinv = ids(0);
     }
     for (int n = 0; n < S_; ++n) {
       const bool complete = state_complete(n + 1);
@@ -1251,7 +1250,7 @@ class Engine final : public EngineBase {
     {
       auto sc = timer_.scope("sort_gather_back", P_ * (12.0 * sizeT() + 4.0));
       bk::k_gather_back<T><<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
-          dest_slots, state_ptrs(dbar_, pbar_), state_mptrs(dbar2_, pbar2_), 6, P_);
+          dest_slots, state_ptrs(dbar_, pbar_), state_mptrs(dbar2_, pbar2_), 6, P_, lp_);
       IC_LAUNCHED();
     }
     std::swap(dbar_, dbar2_);
