@@ -15,9 +15,8 @@
 //   * paints accumulate in LDS windows (FP64 adds for FP64 grids, exact
 //     64-bit fixed-point adds for FP32 grids, see WinAcc); a block's only
 //     item stores its 8^3 own cells (the items of a block with several add
-//     them atomically), its z halo into a one-value-per-eight-cells field
-//     the consumer adds while reading, and its x/y halo into a staging
-//     slot that a second pass adds along whole grid rows: global float
+//     them atomically), its halo into fields of their own (halo.h) that
+//     the consumer adds while reading: global float
 //     atomics are served past the XCD's L2 and were the paints' largest
 //     cost;
 //   * gathers read their mesh fields from a window loaded with coalesced
@@ -40,6 +39,7 @@
 
 #include <type_traits>
 
+#include "halo.h"
 #include "particles.h"
 
 namespace ic {
@@ -851,103 +851,91 @@ __device__ __forceinline__ double wg_max_finish(const double* red) {
   return x;
 }
 
-// The window's halo, its 217 cells with a coordinate 8, belongs to the
-// blocks above.  The 64 cells above in z only (kx, ky < 8, kz = 8) land on
-// the lowest z layer of the block above in z; the 153 with kx = 8 or ky = 8
-// are numbered x face (81), then y face without it (72).
-constexpr int kHaloXY = kW * kW + kB * kW;
-
-__device__ __forceinline__ int halo_xy_index(int kx, int ky, int kz) {
-  return kx == kB ? ky * kW + kz : kW * kW + kx * kW + kz;
-}
-
-// Flush of nf FP64 windows; the fields and zh are zero before the paint.
-// * The block's own 8^3 cells: plain stores when this item is the block's
-//   only one (no other item of the launch writes them), else global atomic
-//   adds of the non-zero cells.
-// * The z halo: into zh, one value per lowest-z-layer cell of every block
-//   (zh[f][(bz << lm | x) << lm | y], a grid field of one value per eight
-//   cells along z, laid out so that a block's 8 x 8 values form runs of 8),
-//   stored or atomically added by the same rule; the consumer adds it to the
-//   cell (x, y, 8 bz).
-// * The x and y halos: into this item's slot of the halo staging
-//   (nf x kHaloXY values), added into the cells by k_halo_rows.
-// Single-item blocks thus flush without global atomics.
-template <typename T>
-__device__ __forceinline__ void flush_owned(const Item& m, const Layout& L,
-                                            const typename WinAcc<T>::Cell* acc,
-                                            const typename WinAcc<T>::Scale& sc, int nf,
-                                            const MPtrs<T>& dst, T* __restrict__ zh,
-                                            T* __restrict__ halo) {
+// Flush of nf windows, value(f, k) being cell k of window f: the block's own 8^3
+// cells into the fields dst, the 217 cells with a coordinate 8 into the halos hl
+// (HaloMap, one after the other).  When this item is the block's only one (no
+// other item of the launch writes its cells and entries) it stores them; else it
+// adds the non-zero ones atomically to what zero_unowned cleared.
+template <typename V, class Value, class Add>
+__device__ __forceinline__ void flush(const Item& m, const Layout& L, int nf,
+                                      const MPtrs<V>& dst, V* __restrict__ hl, Value&& value,
+                                      Add&& add) {
   constexpr int kIt = (kWin + kThreads - 1) / kThreads;
-  T* hs = halo + static_cast<size_t>(m.i) * nf * kHaloXY;
-  const long long zplane = 1ll << (2 * L.lm + L.lnb);  // zh values per field (n^3 / 8)
-  const unsigned bmask = (1u << L.lnb) - 1;
+  const HaloMap hm(L.lm);
+  const unsigned bx = static_cast<unsigned>(m.o[0]) >> kLB,
+                 by = static_cast<unsigned>(m.o[1]) >> kLB,
+                 bz = static_cast<unsigned>(m.o[2]) >> kLB;
 #pragma unroll
   for (int j = 0; j < kIt; ++j) {
     const int k = static_cast<int>(threadIdx.x) + j * kThreads;
     if (k >= kWin) continue;
-    const int kx = k / (kW * kW), r = k - kx * kW * kW;
-    const int ky = r / kW, kz = r - ky * kW;
-    if (kx < kB && ky < kB) {
-      T* out[4];
-      long long c;
-      if (kz < kB) {
-        c = win_cell(m.o, k, L);
-        for (int f = 0; f < nf; ++f) out[f] = dst.p[f];
-      } else {
-        const unsigned bz = ((static_cast<unsigned>(m.o[2]) >> kLB) + 1) & bmask;
-        c = ((static_cast<long long>(bz) << L.lm | (m.o[0] + kx)) << L.lm) | (m.o[1] + ky);
-        for (int f = 0; f < nf; ++f) out[f] = zh + f * zplane;
-      }
-      for (int f = 0; f < nf; ++f) {
-        const T v = static_cast<T>(WinAcc<T>::get(acc[f * kWin + k], sc));
-        if (m.single)
-          out[f][c] = v;
-        else if (v != T(0))
-          pk::atomic_add(out[f] + c, v);
-      }
-    } else {
-      const int h = halo_xy_index(kx, ky, kz);
-      for (int f = 0; f < nf; ++f) hs[f * kHaloXY + h] = static_cast<T>(WinAcc<T>::get(acc[f * kWin + k], sc));
+    const unsigned kx = k / (kW * kW), r = k - kx * kW * kW;
+    const unsigned ky = r / kW, kz = r - ky * kW;
+    const bool own = kx < kB && ky < kB && kz < kB;
+    const unsigned c = own ? win_cell(m.o, k, L) : hm.of_window(bx, by, bz, kx, ky, kz);
+    for (int f = 0; f < nf; ++f) {
+      V* out = (own ? dst.p[f] : hl + static_cast<size_t>(f) * hm.size()) + c;
+      const V v = value(f, k);
+      if (m.single)
+        *out = v;
+      else if (v != V(0))
+        add(out, v);
     }
   }
 }
 
+template <typename T>
+__device__ __forceinline__ void flush_owned(const Item& m, const Layout& L,
+                                            const typename WinAcc<T>::Cell* acc,
+                                            const typename WinAcc<T>::Scale& sc, int nf,
+                                            const MPtrs<T>& dst, T* __restrict__ hl) {
+  flush(m, L, nf, dst, hl,
+        [&](int f, int k) { return static_cast<T>(WinAcc<T>::get(acc[f * kWin + k], sc)); },
+        [](T* p, T v) { pk::atomic_add(p, v); });
+}
+
 // Before a paint of one order: zeroes the own cells (nf fields) and the
-// z-halo entries of every block that no single work item owns, i.e. blocks
+// halo entries of every block that no single work item owns, i.e. blocks
 // with no particles or with several items (whose items add atomically); a
 // block's only item stores all of them itself.  One wavefront per block:
-// lane (kx, ky) clears the eight cells of its z row and its z-halo entry.
+// lane (i, j) clears the eight cells of its z row and its entries of the faces.
 // istart: the order's item starts per block (nb + 1).
-template <typename T>
+template <typename V>
 __device__ __forceinline__ void zero_unowned(long long wg, const unsigned* __restrict__ istart,
-                                             const Layout& L, int nf, const MPtrs<T>& dst,
-                                             T* __restrict__ zh) {
+                                             const Layout& L, int nf, const MPtrs<V>& dst,
+                                             V* __restrict__ hl) {
   const long long t = wg * kThreads + threadIdx.x;
   const long long b = t >> 6;
   if (b >= (1ll << (3 * L.lnb))) return;
   if (istart[b + 1] - istart[b] == 1u) return;
-  const int lane = static_cast<int>(t & 63);
+  const unsigned lane = static_cast<unsigned>(t & 63), i = lane >> 3, j = lane & 7;
   int o[3];
   block_origin(static_cast<unsigned>(b), L, o);
-  const long long cx = o[0] + (lane >> 3), cy = o[1] + (lane & 7);
-  const unsigned row = cell_at(static_cast<unsigned>(cx), static_cast<unsigned>(cy),
-                               static_cast<unsigned>(o[2]), L);
-  const long long zplane = 1ll << (2 * L.lm + L.lnb);
-  const unsigned bz = ((static_cast<unsigned>(o[2]) >> kLB) + 1) & ((1u << L.lnb) - 1);
-  const long long zc = ((static_cast<long long>(bz) << L.lm | cx) << L.lm) | cy;
+  const unsigned ox = static_cast<unsigned>(o[0]), oy = static_cast<unsigned>(o[1]),
+                 oz = static_cast<unsigned>(o[2]);
+  const unsigned row = cell_at(ox + i, oy + j, oz, L);
+  const HaloMap hm(L.lm);
+  const unsigned bx = ox >> kLB, by = oy >> kLB, bz = oz >> kLB;
   for (int f = 0; f < nf; ++f) {
 #pragma unroll
-    for (int z = 0; z < kB; ++z) dst.p[f][row + z] = T(0);
-    zh[f * zplane + zc] = T(0);
+    for (int z = 0; z < kB; ++z) dst.p[f][row + z] = V(0);
+    V* h = hl + static_cast<size_t>(f) * hm.size();
+    h[hm.of_window(bx, by, bz, i, j, kB)] = V(0);
+    h[hm.of_window(bx, by, bz, i, kB, j)] = V(0);
+    h[hm.of_window(bx, by, bz, kB, i, j)] = V(0);
+    if (i == 0) {
+      h[hm.of_window(bx, by, bz, j, kB, kB)] = V(0);
+      h[hm.of_window(bx, by, bz, kB, j, kB)] = V(0);
+      h[hm.of_window(bx, by, bz, kB, kB, j)] = V(0);
+      if (j == 0) h[hm.of_window(bx, by, bz, kB, kB, kB)] = V(0);
+    }
   }
 }
-template <typename T>
+template <typename V>
 __global__ __launch_bounds__(kThreads) void k_zero_unowned(const unsigned* __restrict__ istart,
-                                                           Layout L, int nf, MPtrs<T> dst,
-                                                           T* __restrict__ zh) {
-  zero_unowned(blockIdx.x, istart, L, nf, dst, zh);
+                                                           Layout L, int nf, MPtrs<V> dst,
+                                                           V* __restrict__ hl) {
+  zero_unowned(blockIdx.x, istart, L, nf, dst, hl);
 }
 inline unsigned zero_grid(const Layout& L) {
   return static_cast<unsigned>(((1ll << (3 * L.lnb)) * 64 + kThreads - 1) / kThreads);
@@ -960,7 +948,7 @@ struct ZeroFirst {
   unsigned wg0;
   const unsigned* istart;
   T* rho;
-  T* zh;
+  T* hl;
 };
 
 // The ids of the lattice order's slots q = tile_site(a) to slots
@@ -973,7 +961,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter_ids(
     const unsigned* __restrict__ start, unsigned* __restrict__ ids_dst,
     unsigned* __restrict__ dest, long long P, int lp, Layout L, ZeroFirst<T> zf) {
   if (blockIdx.x >= zf.wg0) {
-    zero_unowned(blockIdx.x - zf.wg0, zf.istart, L, 1, MPtrs<T>{{zf.rho}}, zf.zh);
+    zero_unowned(blockIdx.x - zf.wg0, zf.istart, L, 1, MPtrs<T>{{zf.rho}}, zf.hl);
     return;
   }
   const long long a = blockIdx.x * (long long)kThreads + threadIdx.x;
@@ -992,7 +980,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter_ids_b(
     Items it, Layout L, Layout Ld, int rs, Moves mv, unsigned* __restrict__ ids_dst,
     unsigned* __restrict__ dest, unsigned* __restrict__ inv, ZeroFirst<T> zf) {
   if (blockIdx.x >= zf.wg0) {
-    zero_unowned(blockIdx.x - zf.wg0, zf.istart, Ld, 1, MPtrs<T>{{zf.rho}}, zf.zh);
+    zero_unowned(blockIdx.x - zf.wg0, zf.istart, Ld, 1, MPtrs<T>{{zf.rho}}, zf.hl);
     return;
   }
   __shared__ unsigned first[kNbr];
@@ -1012,198 +1000,107 @@ __global__ __launch_bounds__(kThreads) void k_scatter_ids_b(
 }
 
 // Output of a paint in deterministic mode: the integer fields det (nf fields
-// of ncells), their z halo zh (nf x ncells / 8, laid out as a paint's z
-// halo) and x/y halo staging halo (nf x kHaloXY per item), the device
-// maximum |v| the scale is chosen for (null for a density paint) and lpc =
-// log2 of the particle count.
+// of ncells) and their halos hl, the device maximum |v| the scale is chosen for
+// (null for a density paint) and lpc = log2 of the particle count.
 struct DetOut {
   unsigned long long* det;
-  unsigned long long* zh;
-  unsigned long long* halo;
+  unsigned long long* hl;
   const double* vmax;
   long long ncells;
   int lpc;
 };
 
-// Flush of a deterministic paint: flush_owned's scheme with the windows'
-// integer sums themselves (one scale for the whole paint): a single item
-// stores its block's own cells and z-halo entries, the items of blocks with
-// several add theirs with 64-bit integer atomics (det and zh zeroed there
-// before the paint), and every item leaves its x/y halo in its staging
-// slot for k_halo_rows.  Integer adds commute, so the result depends neither
-// on the order of the atomics nor on which particles share an item.
+// Flush of a deterministic paint: the windows' integer sums themselves (one scale
+// for the whole paint), with 64-bit integer atomics where a block has several
+// items.  Integer adds commute, so the result depends neither on the order of the
+// atomics nor on which particles share an item.
 __device__ __forceinline__ void flush_det(const Item& m, const Layout& L, const FixAcc::Cell* acc,
                                           int nf, const DetOut& dt) {
-  constexpr int kIt = (kWin + kThreads - 1) / kThreads;
-  unsigned long long* hs = dt.halo + static_cast<size_t>(m.i) * nf * kHaloXY;
-  const long long zplane = 1ll << (2 * L.lm + L.lnb);  // zh values per field (n^3 / 8)
-  const unsigned bmask = (1u << L.lnb) - 1;
-#pragma unroll
-  for (int j = 0; j < kIt; ++j) {
-    const int k = static_cast<int>(threadIdx.x) + j * kThreads;
-    if (k >= kWin) continue;
-    const int kx = k / (kW * kW), r = k - kx * kW * kW;
-    const int ky = r / kW, kz = r - ky * kW;
-    if (kx < kB && ky < kB) {
-      unsigned long long* out;
-      long long c, fstride;
-      if (kz < kB) {
-        c = win_cell(m.o, k, L);
-        out = dt.det;
-        fstride = dt.ncells;
-      } else {
-        const unsigned bz = ((static_cast<unsigned>(m.o[2]) >> kLB) + 1) & bmask;
-        c = ((static_cast<long long>(bz) << L.lm | (m.o[0] + kx)) << L.lm) | (m.o[1] + ky);
-        out = dt.zh;
-        fstride = zplane;
-      }
-      for (int f = 0; f < nf; ++f) {
-        const unsigned long long v = acc[f * kWin + k];
-        if (m.single)
-          out[f * fstride + c] = v;
-        else if (v)
-          atomicAdd(out + f * fstride + c, v);
-      }
-    } else {
-      const int h = halo_xy_index(kx, ky, kz);
-      for (int f = 0; f < nf; ++f) hs[f * kHaloXY + h] = acc[f * kWin + k];
-    }
+  using V = unsigned long long;
+  flush(m, L, nf, MPtrs<V>{{dt.det, dt.det + dt.ncells, dt.det + 2 * dt.ncells}}, dt.hl,
+        [&](int f, int k) { return static_cast<V>(acc[f * kWin + k]); },
+        [](V* p, V v) { atomicAdd(p, v); });
+}
+
+// Coordinates of cell i of a field.
+__device__ __forceinline__ void cell_of(unsigned i, const Layout& L, unsigned c[3]) {
+  const unsigned m = (1u << L.lm) - 1;
+  if (L.slabs) {
+    c[2] = i >> (2 * L.lm + kLB) << kLB | (i & (kB - 1));
+    c[1] = i >> kLB & m;
+    c[0] = i >> (L.lm + kLB) & m;
+  } else {
+    c[2] = i & m;
+    c[1] = i >> L.lm & m;
+    c[0] = i >> (2 * L.lm);
   }
 }
 
-// The fields of a deterministic paint: out_f[i] = (det_f[i] + the z-halo
-// entry of cell i when its z is a multiple of 8) 2^-e with the paint's scale
-// (vmax, coef, lpc as given to the paint).
+// The fields of a deterministic paint: out_f[i] = (det_f[i] + what the halo holds
+// for cell i) 2^-e with the paint's scale (vmax, coef, lpc as given to the paint).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_det_to_field(const unsigned long long* __restrict__ det,
-                                                           const unsigned long long* __restrict__ zh,
+                                                           const unsigned long long* __restrict__ hl,
                                                            int nf, long long ncells, Layout L,
                                                            const double* __restrict__ vmax,
                                                            T coef, int lpc, MPtrs<T> out) {
   const double inv = FixAcc::scale_det(det_amax<T>(vmax, coef), lpc).inv;
-  const long long zplane = ncells >> kLB;
+  const HaloMap hm(L.lm);
   for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < ncells;
        i += (long long)gridDim.x * kThreads) {
-    const unsigned c = static_cast<unsigned>(i), m = (1u << L.lm) - 1;
-    const unsigned zi = L.slabs ? c >> kLB : (c & m) >> kLB << (2 * L.lm) | c >> L.lm;
-    const bool zcell = (i & (kB - 1)) == 0;
+    unsigned c[3];
+    cell_of(static_cast<unsigned>(i), L, c);
     for (int f = 0; f < nf; ++f) {
-      const unsigned long long z = zh[f * zplane + zi];
-      const unsigned long long v = det[f * ncells + i] + (zcell ? z : 0ull);
+      const unsigned long long v =
+          det[f * ncells + i] + hm.sum(hl + static_cast<size_t>(f) * hm.size(), c[0], c[1], c[2]);
       out.p[f][i] = static_cast<T>(static_cast<double>(static_cast<long long>(v)) * inv);
     }
   }
 }
 
-// Cells that receive x/y halo values: those with x or y on a block's lowest
-// layer (x = 8 i: every y; y = 8 j: x not on such a layer).  They are
-// visited block face by block face, one wavefront per face: 2 nb^3 faces
-// (the x faces of all blocks, then their y faces), 64 cells (lanes) each.
-__host__ __device__ __forceinline__ long long face_waves(const Layout& L) {
-  return 2ll << (3 * L.lnb);
-}
-
-// After a paint of one order: every face cell gets the x and y halo values
-// that the items of the blocks below it in x or y (with or without z) wrote
-// for it.  A wavefront takes the face of one block: on an x face lane
-// (ly, lz) is cell (8 b0, 8 b1 + ly, 8 b2 + lz), on a y face lane (lx, lz)
-// is cell (8 b0 + lx, 8 b1, 8 b2 + lz) with lx = 0 idle (an x face cell).
-// The main halo value of the face's 64 cells then sits in one contiguous
-// run of the staging of one item, and with the field in slabs an x face's
-// cells are one run too.  istart: the order's item starts per block (nb + 1).
-template <typename T, int NF>
-__global__ __launch_bounds__(kThreads) void k_halo_rows(const T* __restrict__ halo,
-                                                        const unsigned* __restrict__ istart,
-                                                        Layout L, MPtrs<T> dst) {
-  const long long t = blockIdx.x * (long long)kThreads + threadIdx.x;
-  const long long w = t >> 6;
-  if (w >= face_waves(L)) return;
-  const int lane = static_cast<int>(t & 63);
-  const long long nb3 = 1ll << (3 * L.lnb);
-  const bool yface = w >= nb3;
-  const long long q = yface ? w - nb3 : w;
-  const unsigned bm = (1u << L.lnb) - 1;
-  const unsigned bb[3] = {static_cast<unsigned>(q >> (2 * L.lnb)),
-                          static_cast<unsigned>(q >> L.lnb) & bm, static_cast<unsigned>(q) & bm};
-  const int l[3] = {yface ? lane >> 3 : 0, yface ? 0 : lane >> 3, lane & 7};
-  if (yface && l[0] == 0) return;
-  // The six neighbour classes a = 2..7 = (ax ay az) as bits 2 1 0 with ax or
-  // ay set: whether the lane's cell takes that class's halo, the
-  // neighbour's item range and the halo entry.  The item ranges of all
-  // classes, then the first items' values, are loaded in one branch-free
-  // run each (clamped to item 0 and selected where unused); further items
-  // (blocks with several) follow in a loop.
-  constexpr int kA = 6;
-  bool use[kA];
-  int h[kA];
-  unsigned i0[kA], i1[kA];
-#pragma unroll
-  for (int q = 0; q < kA; ++q) {
-    const int a = q + 2;
-    const int ax = (a >> 2) & 1, ay = (a >> 1) & 1, az = a & 1;
-    use[q] = !((ax && l[0]) || (ay && l[1]) || (az && l[2]));
-    const unsigned nbk = (((bb[0] - ax) & bm) << (2 * L.lnb)) | (((bb[1] - ay) & bm) << L.lnb) |
-                         ((bb[2] - az) & bm);
-    h[q] = halo_xy_index(ax ? kB : l[0], ay ? kB : l[1], az ? kB : l[2]);
-    i0[q] = istart[nbk];
-    i1[q] = istart[nbk + 1];
-  }
-  T v[kA][NF];
-#pragma unroll
-  for (int q = 0; q < kA; ++q) {
-    use[q] = use[q] && i0[q] < i1[q];
-    const T* hs = halo + static_cast<size_t>(use[q] ? i0[q] : 0u) * NF * kHaloXY + h[q];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) v[q][f] = hs[f * kHaloXY];
-  }
-  T sum[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    sum[f] = T(0);
-#pragma unroll
-    for (int q = 0; q < kA; ++q) sum[f] += use[q] ? v[q][f] : T(0);
-  }
-#pragma unroll
-  for (int q = 0; q < kA; ++q) {
-    if (!use[q]) continue;
-    for (unsigned i = i0[q] + 1; i < i1[q]; ++i) {
-      const T* hs = halo + static_cast<size_t>(i) * NF * kHaloXY + h[q];
-#pragma unroll
-      for (int f = 0; f < NF; ++f) sum[f] += hs[f * kHaloXY];
-    }
-  }
-  const long long cx = (static_cast<long long>(bb[0]) << kLB) | l[0];
-  const long long cy = (static_cast<long long>(bb[1]) << kLB) | l[1];
-  const long long cz = (static_cast<long long>(bb[2]) << kLB) | l[2];
-  const unsigned c = cell_at(static_cast<unsigned>(cx), static_cast<unsigned>(cy),
-                             static_cast<unsigned>(cz), L);
-#pragma unroll
-  for (int f = 0; f < NF; ++f) dst.p[f][c] += sum[f];
-}
-
-// cell (x, y, 8 bz) += zh[(bz, x, y)] for one [x][y][z] field of side 2^lm (the
-// callers that want the painted field itself).
+// The x part of the halos into the planes x = 0 mod 8 of the fields in slabs, one per
+// blockIdx.y (fft_halo_x_apart).  Thread i: cell i of the fields' planes in turn.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_add_zh(T* __restrict__ rho, const T* __restrict__ zh,
-                                                     int lm, long long nz) {
+__global__ __launch_bounds__(kThreads) void k_add_halo_x(MPtrs<T> dst, const T* __restrict__ hl,
+                                                         Layout L) {
+  const unsigned i = blockIdx.x * kThreads + threadIdx.x;
+  if (i >> (3 * L.lm - kLB)) return;
+  const HaloMap hm(L.lm);
+  // i = [x / 8][z / 8][y][z mod 8]
+  const unsigned m = (1u << L.lm) - 1;
+  const unsigned z = (i >> (L.lm + kLB) & ((1u << L.lnb) - 1)) << kLB | (i & (kB - 1));
+  const unsigned y = i >> kLB & m, x = i >> (2 * L.lm) << kLB;
+  T* p = dst.p[blockIdx.y] + cell_at(x, y, z, L);
+  const T v = *p;
+  *p = v + hm.sum_x(hl + static_cast<size_t>(blockIdx.y) * hm.size(), x, y, z);
+}
+
+// rho += its halo, for one field of side 2^lm (the data grid, and the callers that
+// want the painted field itself).
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_add_halo(T* __restrict__ rho,
+                                                       const T* __restrict__ hl, Layout L,
+                                                       long long ncells) {
   const long long i = blockIdx.x * (long long)kThreads + threadIdx.x;
-  if (i >= nz) return;
-  const long long xy = i & ((1ll << (2 * lm)) - 1), bz = i >> (2 * lm);
-  rho[(xy << lm) | (bz << kLB)] += zh[i];
+  if (i >= ncells) return;
+  unsigned c[3];
+  cell_of(static_cast<unsigned>(i), L, c);
+  if (((c[0] & 7u) == 0) | ((c[1] & 7u) == 0) | ((c[2] & 7u) == 0))
+    rho[i] += HaloMap(L.lm).sum(hl, c[0], c[1], c[2]);
 }
 
 // rho(c) += sum_n W(q_n + d_n - c) over the items of one order.  The
 // displacement of slot a is d[a], or d[gsrc[a]] when it was left in the
 // previous order (gsrc: this order's slots to that order's); then dcopy
 // receives it in this order.  DET: the deterministic mode's output (dt)
-// instead of rho, zh and halo.
+// instead of rho and hl.
 template <typename T, bool DET>
 __global__ __launch_bounds__(kThreads) void k_paint_b(const T* __restrict__ d,
                                                       const unsigned* __restrict__ gsrc,
                                                       T* __restrict__ dcopy, long long P,
                                                       int lp, Grid<T> g, Layout L, Items it,
-                                                      T* __restrict__ rho, T* __restrict__ zh,
-                                                      T* __restrict__ halo, DetOut dt) {
+                                                      T* __restrict__ rho, T* __restrict__ hl,
+                                                      DetOut dt) {
   using A = PaintAcc<T, DET>;
   __shared__ typename A::Cell acc[kWin];
   Item m;
@@ -1254,13 +1151,13 @@ __global__ __launch_bounds__(kThreads) void k_paint_b(const T* __restrict__ d,
   if constexpr (DET)
     flush_det(m, L, acc, 1, dt);
   else
-    flush_owned<T>(m, L, acc, sc, 1, MPtrs<T>{{rho}}, zh, halo);
+    flush_owned<T>(m, L, acc, sc, 1, MPtrs<T>{{rho}}, hl);
 }
 
 // g_bar_j(c) += coef * sum_n v_nj W(q_n + d_n - c), three meshes M apart; v
 // of slot a is read at slot src[a] (the order the cotangents were left in).
 // DET: the deterministic mode's output (dt, with dt.vmax = max |v|) instead
-// of out, zh and halo.
+// of out and hl.
 template <typename T, bool DET>
 __global__ __launch_bounds__(kThreads) void k_paint_vec_b(const T* __restrict__ d,
                                                           const T* __restrict__ v, T coef,
@@ -1268,8 +1165,7 @@ __global__ __launch_bounds__(kThreads) void k_paint_vec_b(const T* __restrict__ 
                                                           Layout L, Items it, T* __restrict__ out,
                                                           long long M,
                                                           const unsigned* __restrict__ src,
-                                                          T* __restrict__ zh,
-                                                          T* __restrict__ halo, DetOut dt) {
+                                                          T* __restrict__ hl, DetOut dt) {
   using A = PaintAcc<T, DET>;
   __shared__ typename A::Cell acc[3 * kWin];
   __shared__ double red[kThreads / 64];
@@ -1325,7 +1221,7 @@ __global__ __launch_bounds__(kThreads) void k_paint_vec_b(const T* __restrict__ 
   if constexpr (DET)
     flush_det(m, L, acc, 3, dt);
   else
-    flush_owned<T>(m, L, acc, sc, 3, MPtrs<T>{{out, out + M, out + 2 * M}}, zh, halo);
+    flush_owned<T>(m, L, acc, sc, 3, MPtrs<T>{{out, out + M, out + 2 * M}}, hl);
 }
 
 // Readout of g at d_n, kick p += kick F, drift d' = d_n + drift p; the new
@@ -1593,15 +1489,14 @@ __global__ __launch_bounds__(kThreads) void k_final_b(
 }
 
 // Data-grid paint of the redshift-space positions (items of the data order).
-// DET: the deterministic mode's output (dt) instead of rho, zh and halo.
+// DET: the deterministic mode's output (dt) instead of rho and hl.
 template <typename T, bool DET>
 __global__ __launch_bounds__(kThreads) void k_data_paint_b(const T* __restrict__ d,
                                                            const T* __restrict__ p, long long P,
                                                            int lp, pk::Rsd<T> rsd, Grid<T> gd,
                                                            Layout Ld, Items it,
                                                            T* __restrict__ rho,
-                                                           T* __restrict__ zh,
-                                                           T* __restrict__ halo, DetOut dt) {
+                                                           T* __restrict__ hl, DetOut dt) {
   using A = PaintAcc<T, DET>;
   __shared__ typename A::Cell acc[kWin];
   Item m;
@@ -1641,7 +1536,7 @@ __global__ __launch_bounds__(kThreads) void k_data_paint_b(const T* __restrict__
   if constexpr (DET)
     flush_det(m, Ld, acc, 1, dt);
   else
-    flush_owned<T>(m, Ld, acc, sc, 1, MPtrs<T>{{rho}}, zh, halo);
+    flush_owned<T>(m, Ld, acc, sc, 1, MPtrs<T>{{rho}}, hl);
 }
 
 // Adjoint of the RSD + data paint (see pk::k_data_adjoint) over the data

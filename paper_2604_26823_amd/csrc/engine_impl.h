@@ -141,25 +141,17 @@ class Engine final : public EngineBase {
     bnbr_ = c.take<uint32_t>((size_t)bk::kNbrRow * mim_);
     pinv_ = c.take<uint32_t>(P_);
     bsums_ = c.take<uint2>(1024);
-    // halos of the paints (blocks.h): the x/y staging, one slot of
-    // nf x kHaloXY values per work item (three fields on the mesh orders, one
-    // on the data order); the z halos, one value per eight cells of each
-    // painted field (three mesh fields; the data grid's apart, since the
-    // loss reads it after the adjoint's paints began)
-    hstage_ = c.take<T>((size_t)std::max<long long>(3ll * mim_, mid_) * bk::kHaloXY);
     det_ = p.deterministic != 0;
     if (det_) {
       // deterministic mode: the paints' integer fields (three mesh fields, or
-      // the data grid), their z halo and x/y halo staging, and the device
-      // maximum the cotangent paint's scale is chosen for
+      // the data grid), their halos, and the device maximum the cotangent
+      // paint's scale is chosen for
       det64_ = c.take<unsigned long long>(3 * std::max(M_, P_));
-      detzh_ = c.take<unsigned long long>(3 * std::max(M_, P_) / kZHalo);
-      detstage_ =
-          c.take<unsigned long long>((size_t)std::max<long long>(3ll * mim_, mid_) * bk::kHaloXY);
+      dethl_ = c.take<unsigned long long>((size_t)3 * HaloMap(std::max(lm_, lp_)).size());
       detvmax_ = c.take<double>(8);
     }
-    zh_ = c.take<T>(3 * M_ / kZHalo);
-    zhd_ = c.take<T>(P_ / kZHalo);
+    hl_ = c.take<T>((size_t)3 * HaloMap(lm_).size());
+    hld_ = c.take<T>(HaloMap(lp_).size());
     tmpd_ = c.take<T>(3 * P_);
     tmpp_ = c.take<T>(3 * P_);
     dsd_ = c.take<T>(3 * P_);
@@ -187,7 +179,7 @@ class Engine final : public EngineBase {
     if (ws_bytes < need_) throw ApiError(IC_ERR_WORKSPACE, "workspace too small");
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
       throw ApiError(IC_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-    if (det_ && !(det64_ && detzh_ && detstage_ && detvmax_))
+    if (det_ && !(det64_ && dethl_ && detvmax_))
       throw ApiError(IC_ERR_STATE, "deterministic-mode buffers missing from the workspace");
     timer_.set_stream(st_);
     for (int i = 0; i <= m; ++i) free_slots_.push_back(i);
@@ -385,7 +377,7 @@ class Engine final : public EngineBase {
   void op_force(const void* disp, void* force) override {
     const T* d = static_cast<const T*>(disp);
     paint_lattice(d, 1, rhom_, false);  // positions of order 0 in tmpd_, ids in dids_
-    force_from_density(gtape_);         // adds the z halo left in zh_
+    force_from_density(gtape_);         // adds the halo left in hl_
     fill(tmpp_, T(0), 3 * P_);
     bk::k_step_b<T><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
         tmpd_, tmpp_, nullptr, gtape_, M_, T(1), T(0), P_, lp_, gmesh(), Lm_,
@@ -644,7 +636,7 @@ class Engine final : public EngineBase {
   // what that paint needs (the deterministic paints zero their own fields).
   unsigned zero_wgs() const { return det_ ? 0u : bk::zero_grid(Lm_); }
   bk::ZeroFirst<T> zero_first(const Order& o, unsigned wg0) const {
-    return bk::ZeroFirst<T>{wg0, o.istart, rhom_, zh_};
+    return bk::ZeroFirst<T>{wg0, o.istart, rhom_, hl_};
   }
 
   // The ids alone from the lattice order to the mesh order o (keys and ranks in
@@ -687,27 +679,10 @@ class Engine final : public EngineBase {
     IC_LAUNCHED();
   }
 
-  // First pass of a paint of order o into nf fields and their z halo: zero
-  // what no single work item stores (fields and zh need no fill of their own).
-  void zero_unowned(const Order& o, const bk::Layout& L, int nf, const bk::MPtrs<T>& dst, T* zh) {
-    const long long nb = 1ll << (3 * L.lnb);
-    bk::k_zero_unowned<T><<<grid_for(nb * 64, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
-        o.istart, L, nf, dst, zh);
-    IC_LAUNCHED();
-  }
-
-  // Second pass of a paint of order o: the x/y halo staging added along the
-  // grid rows through the blocks' lowest x or y layers, for nf fields.
-  void halo_rows(const Order& o, const bk::Layout& L, int nf, const bk::MPtrs<T>& dst) {
-    const long long waves = bk::face_waves(L);
-    const double cells = (double)(waves / 2) * (64 + 56);
-    auto sc = timer_.scope("halo_rows", (double)o.max_items * nf * bk::kHaloXY * sizeT() +
-                                            2.0 * nf * cells * sizeT());
-    const unsigned grid = grid_for(waves * 64, bk::kThreads, 1u << 30);
-    if (nf == 3)
-      bk::k_halo_rows<T, 3><<<grid, bk::kThreads, 0, st_>>>(hstage_, o.istart, L, dst);
-    else
-      bk::k_halo_rows<T, 1><<<grid, bk::kThreads, 0, st_>>>(hstage_, o.istart, L, dst);
+  // First pass of a paint of order o into nf fields and their halos: zero
+  // what no single work item stores (fields and hl need no fill of their own).
+  void zero_unowned(const Order& o, const bk::Layout& L, int nf, const bk::MPtrs<T>& dst, T* hl) {
+    bk::k_zero_unowned<T><<<bk::zero_grid(L), bk::kThreads, 0, st_>>>(o.istart, L, nf, dst, hl);
     IC_LAUNCHED();
   }
 
@@ -715,37 +690,28 @@ class Engine final : public EngineBase {
   // The paints accumulate in 64-bit fixed point with one scale per paint and
   // add their windows into det64_ with integer atomics, so a paint's result
   // depends neither on the atomics' order nor on which particles share a
-  // work item; the fields are then converted and left complete (their z
-  // halo buffers zeroed, no x/y halo pass).
+  // work item; the fields are then converted and left complete (their
+  // halos zeroed).
   bk::DetOut det_out(const double* vmax, long long ncells) const {
-    return bk::DetOut{det64_, detzh_, detstage_, vmax, ncells, 3 * lp_};
+    return bk::DetOut{det64_, dethl_, vmax, ncells, 3 * lp_};
   }
   bk::MPtrs<unsigned long long> det_fields(long long ncells) const {
     return bk::MPtrs<unsigned long long>{{det64_, det64_ + ncells, det64_ + 2 * ncells}};
   }
-  // Before a deterministic paint of order o: the integer cells and z-halo
+  // Before a deterministic paint of order o: the integer cells and halo
   // entries that no single work item stores.
   void det_zero_unowned(const Order& o, const bk::Layout& L, int nf, long long ncells) {
-    const long long nb = 1ll << (3 * L.lnb);
-    bk::k_zero_unowned<unsigned long long>
-        <<<grid_for(nb * 64, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
-            o.istart, L, nf, det_fields(ncells), detzh_);
+    bk::k_zero_unowned<unsigned long long><<<bk::zero_grid(L), bk::kThreads, 0, st_>>>(
+        o.istart, L, nf, det_fields(ncells), dethl_);
     IC_LAUNCHED();
   }
-  // After it: the x/y halo staging into the integer cells, then the fields.
-  void det_finish(const Order& o, const bk::Layout& L, const double* vmax, T coef, int nf,
-                  long long ncells, const bk::MPtrs<T>& out) {
-    const unsigned grid = grid_for(bk::face_waves(L) * 64, bk::kThreads, 1u << 30);
-    if (nf == 3)
-      bk::k_halo_rows<unsigned long long, 3>
-          <<<grid, bk::kThreads, 0, st_>>>(detstage_, o.istart, L, det_fields(ncells));
-    else
-      bk::k_halo_rows<unsigned long long, 1>
-          <<<grid, bk::kThreads, 0, st_>>>(detstage_, o.istart, L, det_fields(ncells));
-    IC_LAUNCHED();
+  // After it: the nf fields out, and their halos hl zeroed.
+  void det_finish(const bk::Layout& L, const double* vmax, T coef, int nf, long long ncells,
+                  const bk::MPtrs<T>& out, T* hl) {
     bk::k_det_to_field<T><<<grid_for(ncells, bk::kThreads), bk::kThreads, 0, st_>>>(
-        det64_, detzh_, nf, ncells, L, vmax, coef, 3 * lp_, out);
+        det64_, dethl_, nf, ncells, L, vmax, coef, 3 * lp_, out);
     IC_LAUNCHED();
+    fill(hl, T(0), (long long)nf * HaloMap(L.lm).size());
   }
   // *out = max |x_i| over n values.
   void absmax(const T* x, long long n, double* out) {
@@ -757,12 +723,12 @@ class Engine final : public EngineBase {
   }
 
   // rho = CIC density of the state in order o (positions d, ids id), its
-  // z halo left in zh (ncells / 8 values) for the consumer; every cell of
-  // rho and zh is written here.  With gsrc the positions are read as
+  // halo left in hl for the consumer; every cell of
+  // rho and every entry of hl is written here.  With gsrc the positions are read as
   // d[gsrc[a]] (left in the previous order) and stored in order o to dcopy, and
   // the ids' move to o has zeroed what needs it.
   void paint(const T* d, const Order& o, const unsigned* id, const pk::Grid<T>& g,
-             const bk::Layout& L, T* rho, T* zh, long long ncells,
+             const bk::Layout& L, T* rho, T* hl, long long ncells,
              const unsigned* gsrc = nullptr, T* dcopy = nullptr) {
     const double bytes = P_ * ((gsrc ? 6.0 : 3.0) * sizeT() + (gsrc ? 8.0 : 4.0)) +
                          2.0 * ncells * sizeT();
@@ -771,37 +737,44 @@ class Engine final : public EngineBase {
       {
         auto sc = timer_.scope("cic_paint", bytes);
         bk::k_paint_b<T, true><<<o.max_items + 8, bk::kThreads, 0, st_>>>(
-            d, gsrc, dcopy, P_, lp_, g, L, items(o, id), rho, zh, hstage_,
-            det_out(nullptr, ncells));
+            d, gsrc, dcopy, P_, lp_, g, L, items(o, id), rho, hl, det_out(nullptr, ncells));
         IC_LAUNCHED();
       }
-      det_finish(o, L, nullptr, T(1), 1, ncells, bk::MPtrs<T>{{rho}});
-      fill(zh, T(0), ncells / kZHalo);  // the halo is in rho already
+      det_finish(L, nullptr, T(1), 1, ncells, bk::MPtrs<T>{{rho}}, hl);
       return;
     }
-    if (!gsrc) zero_unowned(o, L, 1, bk::MPtrs<T>{{rho}}, zh);  // else zeroed by the ids' move
+    if (!gsrc) zero_unowned(o, L, 1, bk::MPtrs<T>{{rho}}, hl);  // else zeroed by the ids' move
     {
       auto sc = timer_.scope("cic_paint", bytes);
       bk::k_paint_b<T, false><<<o.max_items + 8, bk::kThreads, 0, st_>>>(
-          d, gsrc, dcopy, P_, lp_, g, L, items(o, id), rho, zh, hstage_, bk::DetOut{});
+          d, gsrc, dcopy, P_, lp_, g, L, items(o, id), rho, hl, bk::DetOut{});
       IC_LAUNCHED();
     }
-    halo_rows(o, L, 1, bk::MPtrs<T>{{rho}});
+    if (L.slabs) halo_x(1, bk::MPtrs<T>{{rho}}, hl);
   }
 
-  // cell (x, y, 8 k) of rho += zh[(x, y, k)]: a paint's z halo into the
-  // field, for the callers that read the field itself.
-  void add_zh(T* rho, const T* zh, long long ncells, int lg) {
-    const long long nz = ncells / kZHalo;
-    bk::k_add_zh<T><<<grid_for(nz, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(rho, zh, lg,
-                                                                                   nz);
+  // After a paint of nf mesh fields: the x part of their halos, where the FFT does
+  // not add it itself.
+  void halo_x(int nf, const bk::MPtrs<T>& dst, const T* hl) {
+    if (!fft_halo_x_apart<T>(nm_)) return;
+    auto sc = timer_.scope("halo_x", nf * 3.0 * M_ / 8 * sizeT());
+    bk::k_add_halo_x<T><<<dim3(blocks_for(M_ / 8, bk::kThreads), nf), bk::kThreads, 0, st_>>>(
+        dst, hl, Lm_);
+    IC_LAUNCHED();
+  }
+
+  // rho += the halo hl of its paint, for the callers that read the field itself.
+  void add_halo(T* rho, const T* hl, const bk::Layout& L, long long ncells) {
+    auto sc = timer_.scope("halo_add", 2.25 * ncells * sizeT());
+    bk::k_add_halo<T><<<grid_for(ncells, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
+        rho, hl, L, ncells);
     IC_LAUNCHED();
   }
 
   // rho = CIC density of displacements d given in lattice order (sorted into
   // the scratch order o first; tmpd_ receives the sorted positions).  The field
   // is the caller's, [x][y][z]; with complete = false it is the force chain's,
-  // in the grid's own layout, its z halo left in zh_.
+  // in the grid's own layout, its halo left in hl_.
   void paint_lattice(const T* d, int grid, T* rho, bool complete = true) {
     const pk::Grid<T> g = grid ? gmesh() : gdata();
     bk::Layout L = grid ? Lm_ : Ld_;
@@ -812,8 +785,8 @@ class Engine final : public EngineBase {
     build_order(o);
     scatter(o, bk::Ptrs<T>{{d, d + P_, d + 2 * P_}},
             bk::MPtrs<T>{{tmpd_, tmpd_ + P_, tmpd_ + 2 * P_}}, 3, nullptr, dids_, dest(-1));
-    paint(tmpd_, o, dids_, g, L, rho, zh_, ncells);
-    if (complete) add_zh(rho, zh_, ncells, L.lm);
+    paint(tmpd_, o, dids_, g, L, rho, hl_, ncells);
+    if (complete) add_halo(rho, hl_, L, ncells);
   }
 
   // ------------------------------------------------------ k-space chains
@@ -855,7 +828,7 @@ class Engine final : public EngineBase {
     T alpha;
     const T* b;
     T beta;
-    const T* zh;  // a paint's z halo added to a (nullable)
+    const T* hl;  // the halo of a paint into a, added to it (nullable)
   };
 
   // One real output of a chain: an x pass's spectrum, the rest of its multiplier.
@@ -888,16 +861,16 @@ class Engine final : public EngineBase {
     return nx;
   }
 
-  // outs[j] = Op_{mul_j}[a + zh] on the chosen grid.  Fields of the force mesh
-  // (grid 1) are painted ones with their z halo zh going in and particle
+  // outs[j] = Op_{mul_j}[a + hl] on the chosen grid.  Fields of the force mesh
+  // (grid 1) are painted ones with their halo hl going in and particle
   // windows' fields coming out, in slabs.
   void chain_scatter(int grid, const T* a, T* const* outs, const Mul* muls, int m,
-                     const T* zh = nullptr) {
+                     const T* hl = nullptr) {
     auto f = fa(grid);
     const long long H = grid ? Hm_ : Hp_;
     const double U = (double)(grid ? M_ : P_) * sizeT();
     const double Hb = half_spectrum_bytes(f.n);
-    const GIn in{a, T(1), nullptr, T(0), zh};
+    const GIn in{a, T(1), nullptr, T(0), hl};
     cx<T>* const S[1] = {pool_};
     r2c_zy(f, &in, S, 1, U, Hb);
     XOut<T> xo[kMaxXOut];
@@ -923,7 +896,7 @@ class Engine final : public EngineBase {
         int k = 0;
         for (; j0 + k < m && !in[j0 + k].b == !in[j0].b; ++k) {
           const GIn& g = in[j0 + k];
-          fl[k] = PlaneFwd<T>{g.a, g.alpha, g.b, g.beta, g.zh, S[j0 + k]};
+          fl[k] = PlaneFwd<T>{g.a, g.alpha, g.b, g.beta, g.hl, S[j0 + k]};
         }
         fft_r2c_zy<T>(f, fl, k);
         j0 += k;
@@ -933,7 +906,7 @@ class Engine final : public EngineBase {
     for (int j = 0; j < m; ++j) {
       {
         auto sc = timer_.scope("fft_r2c_z", (in[j].b ? 2 : 1) * U + Hb);
-        fft_r2c_z<T>(f, in[j].a, in[j].alpha, in[j].b, in[j].beta, S[j], in[j].zh);
+        fft_r2c_z<T>(f, in[j].a, in[j].alpha, in[j].b, in[j].beta, S[j], in[j].hl);
       }
       auto sc = timer_.scope("fft_y", 2 * Hb);
       fft_y<T>(f, S[j], true);
@@ -1034,7 +1007,7 @@ class Engine final : public EngineBase {
     const double sc = 1.0 / (nbar * (double)M_);
     const Mul sp[3] = {grad(0, sc), grad(1, sc), grad(2, sc)};
     T* outs[3] = {g, g + M_, g + 2 * M_};
-    chain_scatter(1, rhom_, outs, sp, 3, zh_);
+    chain_scatter(1, rhom_, outs, sp, 3, hl_);
   }
 
   // Force meshes of the state d_n (order n).  With gsrc the positions are
@@ -1042,9 +1015,9 @@ class Engine final : public EngineBase {
   // order's); the paint reads them through gsrc and stores d_n in its slot.
   void force_mesh(int n, T* g, const unsigned* gsrc = nullptr) {
     if (gsrc)
-      paint(tmpd_, mesh_order(n), ids(n), gmesh(), Lm_, rhom_, zh_, M_, gsrc, dslot(n));
+      paint(tmpd_, mesh_order(n), ids(n), gmesh(), Lm_, rhom_, hl_, M_, gsrc, dslot(n));
     else
-      paint(dslot(n), mesh_order(n), ids(n), gmesh(), Lm_, rhom_, zh_, M_);
+      paint(dslot(n), mesh_order(n), ids(n), gmesh(), Lm_, rhom_, hl_, M_);
     force_from_density(g);
   }
 
@@ -1163,23 +1136,22 @@ class Engine final : public EngineBase {
       {
         auto sc = timer_.scope("data_paint", P_ * (8.0 * sizeT() + 4.0) + 2.0 * P_ * sizeT());
         bk::k_data_paint_b<T, true><<<bk::item_grid(Ld_, P_), bk::kThreads, 0, st_>>>(
-            dsd_, psd_, P_, lp_, rsd(), gdata(), Ld_, items(data_order(), dids_), rhod_, zhd_,
-            hstage_, det_out(nullptr, P_));
+            dsd_, psd_, P_, lp_, rsd(), gdata(), Ld_, items(data_order(), dids_), rhod_, hld_,
+            det_out(nullptr, P_));
         IC_LAUNCHED();
       }
-      det_finish(data_order(), Ld_, nullptr, T(1), 1, P_, bk::MPtrs<T>{{rhod_}});
-      fill(zhd_, T(0), P_ / kZHalo);  // the halo is in rhod_ already
+      det_finish(Ld_, nullptr, T(1), 1, P_, bk::MPtrs<T>{{rhod_}}, hld_);
       return;
     }
-    zero_unowned(data_order(), Ld_, 1, bk::MPtrs<T>{{rhod_}}, zhd_);
+    zero_unowned(data_order(), Ld_, 1, bk::MPtrs<T>{{rhod_}}, hld_);
     {
       auto sc = timer_.scope("data_paint", P_ * (8.0 * sizeT() + 4.0) + 2.0 * P_ * sizeT());
       bk::k_data_paint_b<T, false><<<bk::item_grid(Ld_, P_), bk::kThreads, 0, st_>>>(
-          dsd_, psd_, P_, lp_, rsd(), gdata(), Ld_, items(data_order(), dids_), rhod_, zhd_,
-          hstage_, bk::DetOut{});
+          dsd_, psd_, P_, lp_, rsd(), gdata(), Ld_, items(data_order(), dids_), rhod_, hld_,
+          bk::DetOut{});
       IC_LAUNCHED();
     }
-    halo_rows(data_order(), Ld_, 1, bk::MPtrs<T>{{rhod_}});  // z halo: in zhd_, read by the loss
+    add_halo(rhod_, hld_, Ld_, P_);
   }
 
   // Step n: readout of the forces at d_n, kick, drift into (tmpd_, pout) in
@@ -1272,7 +1244,7 @@ class Engine final : public EngineBase {
       o.k = static_cast<T>(prob_.bias_k);
       fk::k_loss<T><<<g, fk::kRedThreads, 0, st_>>>(
           rhod_, want_loss ? counts_ : nullptr, resp_, s, o, want_loss ? seed_ : nullptr, delta,
-          lambda, part_, P_, zhd_, lp_);
+          lambda, part_, P_);
       IC_LAUNCHED();
     }
     if (!t) return;
@@ -1327,27 +1299,26 @@ class Engine final : public EngineBase {
         {
           auto sc = timer_.scope("cic_paint_vec", P_ * (6.0 * sizeT() + 8.0) + 6.0 * M_ * sizeT());
           bk::k_paint_vec_b<T, true><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
-              dslot(n), pbar_, coef, P_, lp_, gmesh(), Lm_, it, gbar_, M_, dest(n), zh_, hstage_,
+              dslot(n), pbar_, coef, P_, lp_, gmesh(), Lm_, it, gbar_, M_, dest(n), hl_,
               det_out(detvmax_, M_));
           IC_LAUNCHED();
         }
-        det_finish(mesh_order(n), Lm_, detvmax_, coef, 3, M_, gb);
-        fill(zh_, T(0), 3 * M_ / kZHalo);  // the halo is in the meshes already
+        det_finish(Lm_, detvmax_, coef, 3, M_, gb, hl_);
       } else {
-        zero_unowned(mesh_order(n), Lm_, 3, gb, zh_);
+        zero_unowned(mesh_order(n), Lm_, 3, gb, hl_);
         {
           auto sc = timer_.scope("cic_paint_vec", P_ * (6.0 * sizeT() + 8.0) + 6.0 * M_ * sizeT());
           bk::k_paint_vec_b<T, false><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
-              dslot(n), pbar_, coef, P_, lp_, gmesh(), Lm_, it, gbar_, M_, dest(n), zh_, hstage_,
+              dslot(n), pbar_, coef, P_, lp_, gmesh(), Lm_, it, gbar_, M_, dest(n), hl_,
               bk::DetOut{});
           IC_LAUNCHED();
         }
-        halo_rows(mesh_order(n), Lm_, 3, gb);
+        halo_x(3, gb, hl_);
       }
-      const long long zm = M_ / kZHalo;
-      GIn ins[3] = {{gbar_, T(1), nullptr, T(0), zh_},
-                    {gbar_ + M_, T(1), nullptr, T(0), zh_ + zm},
-                    {gbar_ + 2 * M_, T(1), nullptr, T(0), zh_ + 2 * zm}};
+      const size_t hs = HaloMap(lm_).size();
+      GIn ins[3] = {{gbar_, T(1), nullptr, T(0), hl_},
+                    {gbar_ + M_, T(1), nullptr, T(0), hl_ + hs},
+                    {gbar_ + 2 * M_, T(1), nullptr, T(0), hl_ + 2 * hs}};
       const Mul sp[3] = {grad(0, sc_rho), grad(1, sc_rho), grad(2, sc_rho)};
       chain_gather(1, ins, sp, 3, rhobar_, nullptr, T(0));
       const T drift = n >= 1 ? static_cast<T>(co_.Dr[n - 1]) : T(0);
@@ -1488,15 +1459,13 @@ class Engine final : public EngineBase {
   uint2* bsums_;
   uint32_t *bcount_, *bkey_, *brank_, *bnbr_;
   uint32_t* pinv_;  // the newest order's slots to the previous order's
-  T* hstage_ = nullptr;
-  T* zh_ = nullptr;
-  T* zhd_ = nullptr;
+  T* hl_ = nullptr;   // the mesh paints' halos
+  T* hld_ = nullptr;  // the data paint's
   bool det_ = false;                       // deterministic mode
   unsigned long long* det64_ = nullptr;    // its integer paint fields
-  unsigned long long* detzh_ = nullptr;    // their z halo
-  unsigned long long* detstage_ = nullptr; // their x/y halo staging
+  unsigned long long* dethl_ = nullptr;    // their halos
   double* detvmax_ = nullptr;              // its cotangent paint's max |p_bar|
-  static_assert(bk::kB == kZHalo, "the z halo spacing is the block side");
+  static_assert(bk::kB == kSlab, "slabs are as deep as the blocks");
   T *tmpd_, *tmpp_, *dsd_, *psd_, *dbar2_, *pbar2_;
   T* vbuf_;
   uint32_t* dbg_idx_[2];

@@ -16,6 +16,7 @@
 #pragma once
 
 #include "common.h"
+#include "halo.h"
 
 namespace ic {
 
@@ -35,9 +36,8 @@ struct Mul {
 };
 
 constexpr int kMaxMul = 9;
-// Spacing along z of the cells that receive a paint's z halo (the block side
-// of the particle orders).
-constexpr int kZHalo = 8;
+// Depth of a slab, the block side of the particle orders.
+constexpr int kSlab = 8;
 
 // The y and z part of a multiplier with a real scale: c(k~y) d(k~z) i^imag, the
 // powers as polynomials with one term.
@@ -88,13 +88,13 @@ struct FftArgs {
 };
 
 // Real fields are [x][y][z] or in the slab layout
-// [z / 8][x][y][z mod 8] of the fields that particles paint and read: inputs with a z halo zh are in slabs,
+// [z / 8][x][y][z mod 8] of the fields that particles paint and read: inputs with a halo hl (HaloMap) are in slabs,
 // outputs with slab set.
 
 // out = forward rfft along z of (alpha a + beta b); b may be null.
 template <typename T>
 void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* out,
-               const T* zh = nullptr);
+               const T* hl = nullptr);
 
 // out = alpha * (unnormalised inverse rfft along z of in) + beta * aux (aux may be null).
 template <typename T>
@@ -102,7 +102,7 @@ void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* a
                bool slab = false);
 
 // One field of a fused z and y pass: forward, the half spectrum S of
-// alpha (a + zh) + beta b transformed along z and y; inverse, the real field
+// alpha (a + hl) + beta b transformed along z and y; inverse, the real field
 // out = (inverse of mul S) + beta_aux aux.
 template <typename T>
 struct PlaneFwd {
@@ -110,7 +110,7 @@ struct PlaneFwd {
   T alpha;
   const T* b;    // nullable (all fields of one call alike)
   T beta;
-  const T* zh;   // a paint's z halo, a then in slabs (nullable, all alike)
+  const T* hl;   // the halo of a paint, a then in slabs (nullable, all alike)
   cx<T>* S;
 };
 template <typename T>
@@ -127,6 +127,13 @@ struct PlaneInv {
 // (n <= 128).
 template <typename T>
 bool fft_zy_fused(int n, bool with_aux = false);
+
+// Whether a field with a halo must have the x part of it added before its forward
+// passes (k_add_halo_x).  At n = 256 in FP32 the fused planes hold their field in all
+// registers of a CU, one plane each: the one plane in eight with an x halo took
+// 33 us longer and set the time of the launch, where adding it first takes 8.
+template <typename T>
+bool fft_halo_x_apart(int n);
 
 // fft_r2c_z then the forward fft_y of m fields in one launch (where fft_zy_fused).
 template <typename T>

@@ -19,4 +19,5 @@ template void fft_x_scatter<float>(const FftArgs<float>&, const cx<float>* const
 template void fft_x_gather<float>(const FftArgs<float>&, const cx<float>* const*, const Mul*, int,
                                   cx<float>*);
 template void fft_x_embed<float>(const FftArgs<float>&, cx<float>*, const cx<float>*, int, float, float);
+template bool fft_halo_x_apart<float>(int);
 }  // namespace ic

@@ -19,4 +19,5 @@ template void fft_x_scatter<double>(const FftArgs<double>&, const cx<double>* co
 template void fft_x_gather<double>(const FftArgs<double>&, const cx<double>* const*, const Mul*, int,
                                   cx<double>*);
 template void fft_x_embed<double>(const FftArgs<double>&, cx<double>*, const cx<double>*, int, double, double);
+template bool fft_halo_x_apart<double>(int);
 }  // namespace ic

@@ -381,7 +381,7 @@ __device__ __forceinline__ void load_table(cx<T>* dst, const cx<T>* __restrict__
 // fused passes, which hold a plane in all their registers, spills.
 template <typename T, int N, bool SLAB, int TPL>
 struct RowPairs {
-  static constexpr int kP = kZHalo / 2;
+  static constexpr int kP = kSlab / 2;
   static constexpr bool kShared = !SLAB || TPL % kP == 0;
   char* p;
   uint32_t off;
@@ -407,40 +407,104 @@ struct RowPairs {
   }
 };
 
-// ------------------------------------------------------------ z pass R2C
-// Element e of z row `line` (its complex pair 2e, 2e + 1) of
-// alpha (a + zh) + beta b, without a branch: ZH and B are compile-time, and
-// the z-halo value (added to the cells z = 0 mod 8) is loaded for every e and
-// selected, so the loads of a transform's first stage are all issued before
-// its first wait (a branch per element made each load wait for the previous).
-// A field with a z halo (a painted one) is in the slab layout (slab_pair).
-template <typename T, int N, bool ZH, bool B>
-__device__ __forceinline__ cx<T> r2c_elem(const RowPairs<T, N, ZH, Plan<N / 2>::TPL>& ra,
-                                          const RowPairs<T, N, false, Plan<N / 2>::TPL>& rb,
-                                          const T* __restrict__ zh, size_t line, int e,
-                                          T alpha, T beta) {
-  cx<T> u = ra(e);
-  if constexpr (ZH) {
-    const T z = zh[(size_t)(2 * e / kZHalo) * N * N + line];
-    u.x += (e & (kZHalo / 2 - 1)) == 0 ? z : static_cast<T>(0);
+// The halo of a paint (HaloMap) for ROWS rows y0.. of plane x, staged in LDS by a
+// workgroup of THREADS: what the cells z = 0 mod 8 of every row take along z and its
+// edges, then what the rows y = 0 mod 8 take along y.  Rows of a plane x = 0 mod
+// 8 also take the x halo, laid out as the rows themselves, from memory.  A load
+// per element and kind of halo, selected by the lanes that need it, would double
+// the loads of the pass.
+// XIN: the x halo is added here; else it is in the field already (fft_halo_x_apart).
+template <typename T, int N, int ROWS, int THREADS, bool XIN>
+struct HaloRows {
+  static constexpr int NB = N / 8;
+  static constexpr int RR = ROWS >= 8 ? ROWS / 8 : 1;
+  static constexpr int Z = NB * ROWS, R = RR * N;
+  static constexpr int kReals = Z + R;
+  static __device__ __forceinline__ HaloMap map() {
+    constexpr int lm = N == 8 ? 3 : N == 16 ? 4 : N == 32 ? 5 : N == 64 ? 6 : N == 128 ? 7
+                     : N == 256 ? 8 : N == 512 ? 9 : 10;
+    static_assert(1 << lm == N, "sides 8 to 1024");
+    return HaloMap(lm);
   }
-  cx<T> v = cscale<T>(u, alpha);
-  if constexpr (B) {
-    const cx<T> w = rb(e);
-    v.x += beta * w.x;
-    v.y += beta * w.y;
+  // row0: first row, x N + y0
+  static __device__ __forceinline__ void stage(const T* __restrict__ h, size_t row0, T* lds) {
+    const HaloMap m = map();
+    const unsigned x = static_cast<unsigned>(row0 / N), y0 = static_cast<unsigned>(row0 % N);
+    const unsigned bx = x >> 3;
+    const bool on_x = XIN && (x & 7u) == 0;
+    constexpr int QZ = (Z + THREADS - 1) / THREADS, QR = (R + THREADS - 1) / THREADS;
+    // all loads out before the first wait; indices past the end take the last entry
+    auto iz = [](int q) { return min(static_cast<int>(threadIdx.x) + q * THREADS, Z - 1); };
+    auto ir = [](int q) { return min(static_cast<int>(threadIdx.x) + q * THREADS, R - 1); };
+    auto zrow = [&](int i) { return y0 + i % ROWS; };
+    auto rby = [&](int i) { return (y0 >> 3) + i / N; };
+    T zv[QZ], yv[QR], ev[QR];
+#pragma unroll
+    for (int q = 0; q < QZ; ++q) zv[q] = h[m.z(iz(q) / ROWS, x, zrow(iz(q)))];
+#pragma unroll
+    for (int q = 0; q < QR; ++q) {
+      const unsigned i = ir(q), z = i % N;
+      yv[q] = h[m.y(rby(i), x, z)];
+      ev[q] = h[m.yz(rby(i), z >> 3, x)];
+    }
+    if (on_x) {
+#pragma unroll
+      for (int q = 0; q < QZ; ++q) zv[q] += h[m.xz(bx, iz(q) / ROWS, zrow(iz(q)))];
+#pragma unroll
+      for (int q = 0; q < QR; ++q) {
+        const unsigned i = ir(q), z = i % N;
+        yv[q] += h[m.xy(bx, rby(i), z)];
+        ev[q] += h[m.xyz(bx, rby(i), z >> 3)];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < QZ; ++q) lds[iz(q)] = zv[q];
+#pragma unroll
+    for (int q = 0; q < QR; ++q) {
+      const unsigned i = ir(q);
+      lds[Z + i] = yv[q] + ((i & 7u) == 0 ? ev[q] : T(0));
+    }
   }
-  return v;
-}
+  // raw[j], the pair of cells at element lane + j TPL of row `row` (rr after row0),
+  // plus its halo.
+  template <int TPL, int RAW>
+  static __device__ __forceinline__ void add(const T* __restrict__ h, const T* lds, size_t row,
+                                             int rr, int lane, cx<T> (&raw)[RAW]) {
+    const HaloMap m = map();
+    const unsigned x = static_cast<unsigned>(row / N), y = static_cast<unsigned>(row % N);
+    if (XIN && (x & 7u) == 0) {
+      cx<T> v[RAW];
+#pragma unroll
+      for (int j = 0; j < RAW; ++j)
+        v[j] = *reinterpret_cast<const cx<T>*>(
+            h + m.x(x >> 3, y, 2 * static_cast<unsigned>(lane + j * TPL)));
+#pragma unroll
+      for (int j = 0; j < RAW; ++j) raw[j] = cadd<T>(raw[j], v[j]);
+    }
+    if ((y & 7u) == 0) {
+      const T* p = lds + Z + (rr >> 3) * N;
+#pragma unroll
+      for (int j = 0; j < RAW; ++j) {
+        const int z = 2 * (lane + j * TPL);
+        raw[j] = mkc<T>(raw[j].x + p[z], raw[j].y + p[z + 1]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < RAW; ++j) {
+      const int e = lane + j * TPL;
+      const T z = lds[(e >> 2) * ROWS + rr];
+      raw[j].x += (e & 3) == 0 ? z : T(0);
+    }
+  }
+};
 
-// zh (nullable): a paint's z halo, one value per eight cells along z, added
-// to the cells z = 0 mod 8 of a (the value of cell z of line L = x N + y is
-// zh[(z / 8) N^2 + L]).
-template <typename T, int N, bool ZH, bool B>
+// ------------------------------------------------------------ z pass R2C
+// Loads out before the first wait: HL and B are compile-time.
+template <typename T, int N, bool HL, bool B>
 __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_r2c_z(
     const T* __restrict__ a, T alpha, const T* __restrict__ b, T beta,
     cx<T>* __restrict__ out, const cx<T>* __restrict__ twg, int kp,
-    const T* __restrict__ zh) {
+    const T* __restrict__ hl) {
   using C = ZCfg<T, N>;
   constexpr int n = C::n;
   static_assert(N * N % C::LINES == 0, "whole workgroups of rows");
@@ -450,10 +514,28 @@ __global__ __launch_bounds__((ZCfg<T, N>::THREADS)) void k_r2c_z(
   const int lane = threadIdx.x % C::TPL;
   const int l = threadIdx.x / C::TPL;
   const size_t line0 = static_cast<size_t>(blockIdx.x) * C::LINES, line = line0 + l;
-  const RowPairs<T, N, ZH, C::TPL> ra(a, line0, line, lane);
+  const RowPairs<T, N, HL, C::TPL> ra(a, line0, line, lane);
   const RowPairs<T, N, false, C::TPL> rb(b, line0, line, lane);
+  constexpr int RAW = n / C::TPL;
+  cx<T> raw[RAW];
+#pragma unroll
+  for (int r = 0; r < RAW; ++r) raw[r] = ra(lane + r * C::TPL);
+  if constexpr (HL) {
+    using H = HaloRows<T, N, C::LINES, C::THREADS, true>;
+    static_assert(N % C::LINES == 0 && H::kReals <= 2 * C::LINES * C::LS, "rows of one plane");
+    T* st = reinterpret_cast<T*>(buf);
+    H::stage(hl, line0, st);
+    __syncthreads();
+    H::template add<C::TPL>(hl, st, line, l, lane, raw);
+  }
   auto load0 = [&](int e) -> cx<T> {
-    return r2c_elem<T, N, ZH, B>(ra, rb, zh, line, e, alpha, beta);
+    cx<T> v = cscale<T>(raw[(e - lane) / C::TPL], alpha);
+    if constexpr (B) {
+      const cx<T> w = rb(e);
+      v.x += beta * w.x;
+      v.y += beta * w.y;
+    }
+    return v;
   };
   cx<T>* lb = buf + l * C::LS;
   auto lidx = [&](int e) { return l * C::LS + zl(e); };
@@ -594,14 +676,14 @@ struct ZYCfg<float, 256> {
   static constexpr int PER = n / OWN;            // 16 held values per thread
 };
 
-template <typename T, int N, bool ZH, bool B>
+template <typename T, int N, bool HL, bool B>
 __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_r2c_zy(
     FwdSet<T> fields, const cx<T>* __restrict__ twg, int kp) {
   using C = ZYCfg<T, N>;
   constexpr int n = C::n;
   const T* __restrict__ a = fields.f[blockIdx.y].a;
   const T* __restrict__ b = fields.f[blockIdx.y].b;
-  const T* __restrict__ zh = fields.f[blockIdx.y].zh;
+  const T* __restrict__ hl = fields.f[blockIdx.y].hl;
   const T alpha = fields.f[blockIdx.y].alpha, beta = fields.f[blockIdx.y].beta;
   cx<T>* __restrict__ out = fields.f[blockIdx.y].S;
   __shared__ cx<T> buf[n * C::LS];
@@ -622,36 +704,27 @@ __global__ __launch_bounds__((ZYCfg<T, N>::THREADS)) void k_r2c_zy(
     return j < C::PER - SPARE ? keep[j] : spare[(j - (C::PER - SPARE)) * C::THREADS + t];
   };
   cx<T>* lb = buf + l * C::LS;
-  // the half's z-halo values, staged in the tile as [z / 8][row] by coalesced
-  // loads (a row's 32 values lie a plane apart in zh)
-  constexpr int NZ = N / kZHalo;
-  static_assert(NZ * C::n % C::THREADS == 0, "z-halo staging: whole rounds");
-  const T* zt = reinterpret_cast<const T*>(buf);
+  T* st = reinterpret_cast<T*>(buf);  // the half's halo
+  using H = HaloRows<T, N, n, C::THREADS, false>;
+  static_assert(H::kReals <= 2 * n * C::LS, "the halo fits the tile");
   for (int h = 0; h < 2; ++h) {
     const size_t line = x * N + h * n + l;
-    if constexpr (ZH) {
-      if (h == 1) __syncthreads();  // the first half's held values are read
-      T* zw = reinterpret_cast<T*>(buf);
-      constexpr int QZ = NZ * n / C::THREADS;
-      T zv[QZ];
-#pragma unroll
-      for (int q = 0; q < QZ; ++q) {
-        const int i = t + q * C::THREADS;
-        zv[q] = zh[(size_t)(i / n) * N * N + x * N + h * n + i % n];
-      }
-#pragma unroll
-      for (int q = 0; q < QZ; ++q) zw[t + q * C::THREADS] = zv[q];
-      __syncthreads();
-    }
-    const RowPairs<T, N, ZH, C::TPL> ra(a, x * N, line, lane);
+    const RowPairs<T, N, HL, C::TPL> ra(a, x * N, line, lane);
     const RowPairs<T, N, false, C::TPL> rb(b, x * N, line, lane);
-    auto load0 = [&](int e) -> cx<T> {  // no branch: all loads out before the first wait
-      cx<T> u = ra(e);
-      if constexpr (ZH) {
-        const T z = zt[(2 * e / kZHalo) * n + l];
-        u.x += (e & (kZHalo / 2 - 1)) == 0 ? z : static_cast<T>(0);
-      }
-      cx<T> v = cscale<T>(u, alpha);
+    constexpr int RAW = n / C::TPL;
+    cx<T> raw[RAW];  // all loads out before the first wait
+    if constexpr (HL) {
+      if (h == 1) __syncthreads();  // the first half's held values are read
+      H::stage(hl, x * N + h * n, st);
+    }
+#pragma unroll
+    for (int r = 0; r < RAW; ++r) raw[r] = ra(lane + r * C::TPL);
+    if constexpr (HL) {
+      __syncthreads();
+      H::template add<C::TPL>(hl, st, line, l, lane, raw);
+    }
+    auto load0 = [&](int e) -> cx<T> {
+      cx<T> v = cscale<T>(raw[(e - lane) / C::TPL], alpha);
       if constexpr (B) {
         const cx<T> w = rb(e);
         v.x += beta * w.x;
@@ -869,7 +942,7 @@ struct PlCfg {
   static_assert(COLS >= n, "all columns in one round");
 };
 
-template <typename T, int N, bool ZH, bool B>
+template <typename T, int N, bool HL, bool B>
 __global__ __launch_bounds__((PlCfg<T, N>::THREADS)) void k_plane_fwd(
     FwdSet<T> fields, const cx<T>* __restrict__ twg, int kp) {
   using C = PlCfg<T, N>;
@@ -879,20 +952,41 @@ __global__ __launch_bounds__((PlCfg<T, N>::THREADS)) void k_plane_fwd(
   __shared__ cx<T> pk[N];  // the packed column's outputs
   load_table<T>(tw, twg, N);  // visible after the first stage's barrier, before any use
   const PlaneFwd<T>& fl = fields.f[blockIdx.y];
-  const T* __restrict__ zh = fl.zh;
+  const T* __restrict__ hl = fl.hl;
   const T alpha = fl.alpha, beta = fl.beta;
   cx<T>* __restrict__ out = fl.S;
   const int t = threadIdx.x;
   const size_t x = blockIdx.x;
   const int lane = t % C::TZ, l0 = t / C::TZ;
   const T half = static_cast<T>(0.5);
+  // the plane's halo, staged where the last round's rows go
+  T* st = reinterpret_cast<T*>(buf + (C::TROWS - C::ROWS) * C::LS);
+  using H = HaloRows<T, N, N, C::THREADS, true>;
+  static_assert(H::kReals <= 2 * C::ROWS * C::LS, "the halo fits the tile");
   for (int h = 0; h < C::ROUNDS; ++h) {
     const int l = h * C::ROWS + l0;                       // tile row
     const size_t line = x * N + (l < N ? l : 0);          // idle lanes transform row 0 again
-    const RowPairs<T, N, ZH, C::TZ> ra(fl.a, x * N, line, lane);
+    const RowPairs<T, N, HL, C::TZ> ra(fl.a, x * N, line, lane);
     const RowPairs<T, N, false, C::TZ> rb(fl.b, x * N, line, lane);
+    constexpr int RAW = n / C::TZ;
+    cx<T> raw[RAW];
+#pragma unroll
+    for (int r = 0; r < RAW; ++r) raw[r] = ra(lane + r * C::TZ);
+    if constexpr (HL) {
+      if (h == 0) {
+        H::stage(hl, x * N, st);
+        __syncthreads();
+      }
+      H::template add<C::TZ>(hl, st, line, static_cast<int>(line % N), lane, raw);
+    }
     auto load0 = [&](int e) -> cx<T> {
-      return r2c_elem<T, N, ZH, B>(ra, rb, zh, line, e, alpha, beta);
+      cx<T> v = cscale<T>(raw[(e - lane) / C::TZ], alpha);
+      if constexpr (B) {
+        const cx<T> w = rb(e);
+        v.x += beta * w.x;
+        v.y += beta * w.y;
+      }
+      return v;
     };
     cx<T>* lb = buf + l * C::LS;
     auto lidx = [&](int e) { return l * C::LS + zl(e); };
@@ -1340,12 +1434,12 @@ __global__ void k_spec_copy(const cx<T>* __restrict__ src, cx<T>* __restrict__ d
 }
 
 // ------------------------------------------------------------ dispatch
-// f(ZH, B) with the two flags as compile-time constants.
+// f(HL, B) with the two flags as compile-time constants.
 template <class F>
-void with_flags(bool zh, bool b, F&& f) {
+void with_flags(bool hl, bool b, F&& f) {
   using Y = std::true_type;
   using No = std::false_type;
-  if (zh) {
+  if (hl) {
     if (b)
       f(Y{}, Y{});
     else
@@ -1377,15 +1471,16 @@ void dispatch_n(int n, F&& f) {
 
 template <typename T>
 void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* out,
-               const T* zh) {
+               const T* hl) {
+  if (hl && f.n <= 128) throw ApiError(-2, "painted fields of n <= 128 go through the fused planes");
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     using C = fftk::ZCfg<T, N>;
     const int nlines = f.n * f.n;
-    fftk::with_flags(zh != nullptr, b != nullptr, [&](auto ZH, auto B) {
-      fftk::k_r2c_z<T, N, ZH.value, B.value>
+    fftk::with_flags(hl != nullptr, b != nullptr, [&](auto HL, auto B) {
+      fftk::k_r2c_z<T, N, HL.value && (N > 128), B.value>
           <<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(a, alpha, b, beta, out,
-                                                                      f.tw, f.kp, zh);
+                                                                      f.tw, f.kp, hl);
     });
   });
   IC_LAUNCHED();
@@ -1428,23 +1523,28 @@ void dispatch_plane(int n, F&& f) {
 }
 
 template <typename T>
+bool fft_halo_x_apart(int n) {
+  return fftk::ZYCfg<T, 256>::ok && n == 256;
+}
+
+template <typename T>
 void fft_r2c_zy(const FftArgs<T>& f, const PlaneFwd<T>* fields, int m) {
   if (m < 1 || m > kMaxMul) throw ApiError(-1, "field count out of range");
   fftk::FwdSet<T> set{};
   for (int j = 0; j < m; ++j) set.f[j] = fields[j];
   const dim3 grid(f.n, m);
-  fftk::with_flags(fields[0].zh != nullptr, fields[0].b != nullptr, [&](auto ZH, auto B) {
+  fftk::with_flags(fields[0].hl != nullptr, fields[0].b != nullptr, [&](auto HL, auto B) {
     if constexpr (fftk::ZYCfg<T, 256>::ok) {
       if (f.n == 256) {
         using C = fftk::ZYCfg<T, 256>;
-        fftk::k_r2c_zy<T, 256, ZH.value, B.value>
+        fftk::k_r2c_zy<T, 256, HL.value, B.value>
             <<<grid, C::THREADS, 0, f.stream>>>(set, f.tw, f.kp);
         return;
       }
     }
     dispatch_plane(f.n, [&](auto NC) {
       constexpr int N = decltype(NC)::value;
-      fftk::k_plane_fwd<T, N, ZH.value, B.value>
+      fftk::k_plane_fwd<T, N, HL.value, B.value>
           <<<grid, fftk::PlCfg<T, N>::THREADS, 0, f.stream>>>(set, f.tw, f.kp);
     });
   });

@@ -88,25 +88,21 @@ template <typename T>
 __global__ __launch_bounds__(kRedThreads) void k_loss(
     const T* __restrict__ rho, const int* __restrict__ counts, const T* __restrict__ R,
     const T* __restrict__ s, Obs<T> o, T* __restrict__ seed, T* __restrict__ delta_out,
-    T* __restrict__ lambda_out, double* __restrict__ part, long long n,
-    const T* __restrict__ zh, int lg) {
+    T* __restrict__ lambda_out, double* __restrict__ part, long long n) {
   __shared__ double sh[kRedThreads / 64];
   double chi = 0, ss = 0, cnt = 0;
   // kU cells per thread and round (grid stride apart), all their inputs
   // loaded before any is used and without a branch on the cell (indices
-  // clamped, the halo value and the count selected rather than guarded), so
+  // clamped, the count selected rather than guarded), so
   // the loads of a round go out together.
   constexpr int kU = 4;
   const long long st = (long long)gridDim.x * blockDim.x;
   for (long long i0 = blockIdx.x * (long long)blockDim.x + threadIdx.x; i0 < n; i0 += kU * st) {
-    T rv[kU], zv[kU], rr[kU], sv[kU];
+    T rv[kU], rr[kU], sv[kU];
     int nv[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const long long i = i0 + u * st < n ? i0 + u * st : n - 1;
-      // the data paint's z halo (layout [z / 8][x][y], grid side 2^lg)
-      // completes the cells z = 0 mod 8
-      zv[u] = zh ? zh[((i & ((1ll << lg) - 1)) >> 3 << (2 * lg)) | (i >> lg)] : T(0);
       rr[u] = R ? R[i] : T(0);
       nv[u] = counts ? counts[i] : 0;
       sv[u] = s ? s[i] : T(0);
@@ -116,7 +112,7 @@ __global__ __launch_bounds__(kRedThreads) void k_loss(
     for (int u = 0; u < kU; ++u) {
       const long long i = i0 + u * st;
       if (i >= n) continue;
-      const T rh = rv[u] + ((i & 7) == 0 ? zv[u] : T(0));
+      const T rh = rv[u];
       const T delta = rh - T(1);
       const T r = rr[u];
       T sd = T(0);

@@ -34,6 +34,9 @@ SCOPES = {
     "k_data_adjoint_b": "data_adjoint",
     "k_paint_b": "cic_paint",
     "k_scatter": "sort_scatter",
+    "k_scatter_b": "sort_scatter",
+    "k_add_halo": "halo_add",
+    "k_add_halo_x": "halo_x",
     "k_scatter_ids_b": "sort_scatter_ids",
     "k_gather_back": "sort_gather_back",
     "k_keys": "sort_keys",
