@@ -78,8 +78,13 @@ struct HaloMap {
   __device__ __forceinline__ V sum(const V* __restrict__ h, U cx, U cy, U cz) const {
     const bool on_y = (cy & 7u) == 0, on_z = (cz & 7u) == 0;
     const U by = cy >> 3, bz = cz >> 3;
-    const V a = h[z(bz, cx, cy)], b = h[y(by, cx, cz)], c = h[yz(by, bz, cx)];
-    V v = (on_z ? a : V(0)) + (on_y ? b : V(0)) + (on_y && on_z ? c : V(0));
+    V v = V(0);
+    if (on_z) v += h[z(bz, cx, cy)];
+    if (on_y) {
+      const V a = h[y(by, cx, cz)], b = h[yz(by, bz, cx)];
+      v += a;
+      v += on_z ? b : V(0);
+    }
     if ((cx & 7u) == 0) v += sum_x(h, cx, cy, cz);
     return v;
   }
