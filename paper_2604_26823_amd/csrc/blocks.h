@@ -39,6 +39,7 @@
 
 #include <type_traits>
 
+#include "fixed.h"
 #include "halo.h"
 #include "particles.h"
 
@@ -754,15 +755,12 @@ __device__ __forceinline__ void load_window(const int o[3], const Layout& L, con
 // (ds_add_u64 takes about half the time of ds_add_f64 on scattered cells
 // of gfx950, and integer adds are exact, so the window sums do not depend
 // on the order of the atomics).  e is chosen per work item so that nothing
-// overflows: every contribution is at most amax in magnitude (CIC weights
-// are at most 1), a window cell receives at most kChunk of them, and
-// amax 2^e < 2^51, so every partial sum stays below 2^61.  The rounding of
-// a contribution, at most 2^-52 amax, is far below the FP32 result's.
+// overflows (fx::scale_for; a window cell receives at most kChunk
+// contributions).  The rounding of a contribution, at most 2^-52 amax, is far
+// below the FP32 result's.
 //
-// A contribution w x becomes its integer with one fused multiply-add: x 2^e is
-// taken once per particle (exact), and fma(w, x 2^e, 1.5 2^52) leaves
-// the rounded integer (below 2^51 in magnitude) in the low 52 bits of the
-// result, above a constant whose low word is zero.  gfx950 has no conversion
+// A contribution w x becomes its integer with one fused multiply-add (fx::rounded):
+// x 2^e is taken once per particle (exact).  gfx950 has no conversion
 // from FP64 to 64-bit integers; the emulated one (a dozen FP64 and integer
 // instructions) for 24 contributions per particle cost the cotangent paint
 // 10 of 257 us at 256^3.
@@ -780,16 +778,8 @@ struct WinAcc {
 };
 struct FixAcc {
   using Cell = unsigned long long;
-  struct Scale {
-    double s, inv;
-  };
-  // 2^e with amax 2^e < 2^51 (amax < 2^k from frexp, e = 51 - k)
-  __device__ static Scale scale_for(double amax) {
-    if (!(amax > 0.0)) return Scale{1.0, 1.0};
-    int k;
-    frexp(amax, &k);
-    return Scale{ldexp(1.0, 51 - k), ldexp(1.0, k - 51)};
-  }
+  using Scale = fx::Scale;
+  __device__ static Scale scale_for(double amax) { return fx::scale_for(amax); }
   // The scale of a deterministic paint, one for the whole paint: amax 2^e
   // 2^lpc < 2^62, so that a cell may receive one contribution from each of
   // the 2^lpc particles (a particle adds to a cell at most once) without
@@ -802,8 +792,7 @@ struct FixAcc {
   }
   __device__ static double scaled(double x, const Scale& sc) { return x * sc.s; }
   __device__ static void add(Cell* c, double w, double x) {
-    const long long b = __double_as_longlong(fma(w, x, 0x1.8p52));
-    atomicAdd(c, static_cast<unsigned long long>(b - 0x4338000000000000ll));
+    atomicAdd(c, static_cast<unsigned long long>(fx::rounded(w, x)));
   }
   __device__ static double get(Cell c, const Scale& sc) {
     return static_cast<double>(static_cast<long long>(c)) * sc.inv;
@@ -811,7 +800,7 @@ struct FixAcc {
 };
 template <>
 struct WinAcc<float> : FixAcc {};
-// Deterministic paints: scale_det lets contributions grow past 2^51 on the
+// Deterministic paints: scale_det lets contributions grow past 2^52 on the
 // smallest grid (8^3 particles), so they convert with the general rounding.
 struct DetAcc : FixAcc {
   __device__ static void add(Cell* c, double w, double x) {

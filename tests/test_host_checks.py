@@ -1,0 +1,55 @@
+"""Host-side checks of rules and arithmetic in the library's headers (CPU).
+
+The functions that the kernels and their launch code share with the host are
+compiled for the host alone (host_checks.hip) and called through ctypes."""
+import ctypes
+import os
+import subprocess
+from fractions import Fraction
+
+import numpy as np
+import pytest
+
+from paper_2604_26823_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("host") / "host_checks.so")
+    cmd = [build.hipcc(), "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17", "-fPIC",
+           "-ffp-contract=off", "-shared", os.path.join(HERE, "host_checks.hip"), "-o", so]
+    subprocess.run(cmd, check=True, capture_output=True, text=True)
+    lib = ctypes.CDLL(so)
+    d, q = ctypes.c_double, ctypes.c_longlong
+    lib.hc_unit.restype, lib.hc_unit.argtypes = d, [d]
+    lib.hc_rounded.restype, lib.hc_rounded.argtypes = q, [d, d, d]
+    return lib
+
+
+def contributions():
+    """(amax, w, v): weights in [0, 1], products of three FP32 factors, |v| <= amax."""
+    rng = np.random.default_rng(40)
+    t = rng.random((400, 3), dtype=np.float32)
+    w = (t[:, 0] * t[:, 1] * t[:, 2]).astype(np.float64)
+    v = rng.standard_normal(400).astype(np.float32).astype(np.float64)
+    out = []
+    for amax in (1.0, float(np.abs(v).max()), 2.0 ** -140, np.nextafter(2.0, 1.0)):
+        f = amax / np.abs(v).max()
+        out += [(amax, a, float(b)) for a, b in zip(w, np.clip(v * f, -amax, amax))]
+        out += [(amax, a, b) for a in (0.0, 0.5, 2.0 ** -51, 1.0 - 2.0 ** -24, 1.0)
+                for b in (-amax, amax, 0.0, -amax * 2.0 ** -30)]
+    return out
+
+
+def test_fixed_point_contributions_round_to_2_52_of_the_largest(host):
+    """A contribution w v of a work item whose largest |v| is amax: the integer is
+    w v in units of the scale rounded to nearest, so off by at most half a unit,
+    and the unit is at most 2^-51 amax (amax 2^e in [2^51, 2^52))."""
+    for amax, w, v in contributions():
+        unit = Fraction(host.hc_unit(amax))
+        assert Fraction(amax) / unit < 2 ** 52
+        assert unit <= Fraction(amax) / 2 ** 51
+        got = host.hc_rounded(amax, w, v) * unit
+        assert abs(got - Fraction(w) * Fraction(v)) <= unit / 2, (amax, w, v)
