@@ -771,6 +771,8 @@ struct WinAcc {
     double s, inv;
   };
   __device__ static Scale scale_for(double) { return Scale{1.0, 1.0}; }
+  // whether the particle contributes (one without a position makes its cells NaN)
+  __device__ static bool takes(const Stencil<T>&) { return true; }
   // x ready for add: the contribution w x is added to the cell
   __device__ static double scaled(double x, const Scale&) { return x; }
   __device__ static void add(Cell* c, double w, double x) { atomicAdd(c, w * x); }
@@ -780,6 +782,13 @@ struct FixAcc {
   using Cell = unsigned long long;
   using Scale = fx::Scale;
   __device__ static Scale scale_for(double amax) { return fx::scale_for(amax); }
+  // Whether the particle has a position.  The weights of one at NaN or infinity
+  // are NaN, which has no integer: it adds nothing.
+  template <typename T>
+  __host__ __device__ static bool takes(const Stencil<T>& s) {
+    const T t = s.t[0] + s.t[1] + s.t[2];
+    return t == t;
+  }
   // The scale of a deterministic paint, one for the whole paint: amax 2^e
   // 2^lpc < 2^62, so that a cell may receive one contribution from each of
   // the 2^lpc particles (a particle adds to a cell at most once) without
@@ -790,7 +799,10 @@ struct FixAcc {
     frexp(amax, &k);
     return Scale{ldexp(1.0, 62 - lpc - k), ldexp(1.0, k + lpc - 62)};
   }
-  __device__ static double scaled(double x, const Scale& sc) { return x * sc.s; }
+  // (a value that is not finite adds nothing either)
+  __host__ __device__ static double scaled(double x, const Scale& sc) {
+    return fabs(x) < HUGE_VAL ? x * sc.s : 0.0;
+  }
   __device__ static void add(Cell* c, double w, double x) {
     atomicAdd(c, static_cast<unsigned long long>(fx::rounded(w, x)));
   }
@@ -1132,6 +1144,7 @@ __global__ __launch_bounds__(kThreads) void k_paint_b(const T* __restrict__ d,
   for (int k = 0; k < kPer; ++k) {
     if (!ok[k]) continue;
     const Stencil<T> s = wrapped_stencil(idx[k], dsp[k], g);
+    if (!A::takes(s)) continue;
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
       A::add(&acc[win_index(m.o, cx, cy, cz)], static_cast<double>(w), one);
     });
@@ -1198,6 +1211,7 @@ __global__ __launch_bounds__(kThreads) void k_paint_vec_b(const T* __restrict__ 
                  v1 = A::scaled(static_cast<double>(coef * vv[k][1]), sc),
                  v2 = A::scaled(static_cast<double>(coef * vv[k][2]), sc);
     const Stencil<T> s = wrapped_stencil(idx[k], dsp[k], g);
+    if (!A::takes(s)) continue;
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
       const int c = win_index(m.o, cx, cy, cz);
       const double wd = static_cast<double>(w);
@@ -1517,6 +1531,7 @@ __global__ __launch_bounds__(kThreads) void k_data_paint_b(const T* __restrict__
     T ds[3];
     pk::rsd_shift(rsd, idx[k], dsp[k], mom[k], ds);
     const Stencil<T> s = wrapped_stencil(idx[k], ds, gd);
+    if (!A::takes(s)) continue;
     pk::for_corners_xyz(s, [&](int cx, int cy, int cz, T w, T, T, T) {
       A::add(&acc[win_index(m.o, cx, cy, cz)], static_cast<double>(w), one);
     });

@@ -24,7 +24,7 @@ struct Stencil {
 };
 
 // Lattice coordinates of particle index n on a side-np lattice (np = 2^lp).
-__device__ __forceinline__ void lattice(long long n, int lp, int idx[3]) {
+__host__ __device__ __forceinline__ void lattice(long long n, int lp, int idx[3]) {
   const int mask = (1 << lp) - 1;
   idx[2] = static_cast<int>(n & mask);
   idx[1] = static_cast<int>((n >> lp) & mask);
@@ -37,7 +37,7 @@ __device__ __forceinline__ void lattice(long long n, int lp, int idx[3]) {
 // fraction (L / N with N a power of two), so t carries the rounding of d only
 // and not the larger rounding of d / cell at |d| of many cells.
 template <typename T>
-__device__ __forceinline__ Stencil<T> stencil(const int idx[3], int ratio, const T dsp[3],
+__host__ __device__ __forceinline__ Stencil<T> stencil(const int idx[3], int ratio, const T dsp[3],
                                               T inv_cell, T cell) {
   Stencil<T> s;
 #pragma unroll
@@ -77,7 +77,7 @@ __device__ __forceinline__ void atomic_add(T* p, T v) {
 // cell coordinates, w the weight and dwa its derivative along axis a in
 // units of 1/cell.
 template <typename T, class F>
-__device__ __forceinline__ void for_corners_xyz(const Stencil<T>& s, F&& f) {
+__host__ __device__ __forceinline__ void for_corners_xyz(const Stencil<T>& s, F&& f) {
 #pragma unroll
   for (int ox = 0; ox < 2; ++ox) {
     const T wx = ox ? s.t[0] : T(1) - s.t[0];

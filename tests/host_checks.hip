@@ -1,6 +1,6 @@
 // Host-side functions of the library's headers behind a C interface, for
 // test_host_checks.py: compiled for the host alone, no device is touched.
-#include "../paper_2604_26823_amd/csrc/fixed.h"
+#include "../paper_2604_26823_amd/csrc/blocks.h"
 
 extern "C" {
 
@@ -9,6 +9,23 @@ double hc_unit(double amax) { return ic::fx::scale_for(amax).inv; }
 long long hc_rounded(double amax, double w, double v) {
   const ic::fx::Scale sc = ic::fx::scale_for(amax);
   return ic::fx::rounded(w, v * sc.s);
+}
+
+// the eight integers that an FP32 paint adds for a particle displaced by d
+// (cells of side 1) with value v, in a work item whose largest |v| is amax
+void hc_particle(float d, double v, double amax, long long* out) {
+  using A = ic::bk::FixAcc;
+  const A::Scale sc = ic::fx::scale_for(amax);
+  const double x = A::scaled(v, sc);
+  const int idx[3] = {0, 0, 0};
+  const float dsp[3] = {0.25f, d, 0.25f};
+  const ic::pk::Stencil<float> s = ic::pk::stencil(idx, 1, dsp, 1.0f, 1.0f);
+  for (int k = 0; k < 8; ++k) out[k] = 0;
+  if (!A::takes(s)) return;
+  int k = 0;
+  ic::pk::for_corners_xyz(s, [&](int, int, int, float w, float, float, float) {
+    out[k++] = ic::fx::rounded(static_cast<double>(w), x);
+  });
 }
 
 }

@@ -20,11 +20,14 @@ def host(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("host") / "host_checks.so")
     cmd = [build.hipcc(), "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17", "-fPIC",
            "-ffp-contract=off", "-shared", os.path.join(HERE, "host_checks.hip"), "-o", so]
-    subprocess.run(cmd, check=True, capture_output=True, text=True)
+    done = subprocess.run(cmd, capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
     lib = ctypes.CDLL(so)
     d, q = ctypes.c_double, ctypes.c_longlong
     lib.hc_unit.restype, lib.hc_unit.argtypes = d, [d]
     lib.hc_rounded.restype, lib.hc_rounded.argtypes = q, [d, d, d]
+    lib.hc_particle.restype = None
+    lib.hc_particle.argtypes = [ctypes.c_float, d, d, ctypes.POINTER(q)]
     return lib
 
 
@@ -53,3 +56,21 @@ def test_fixed_point_contributions_round_to_2_52_of_the_largest(host):
         assert unit <= Fraction(amax) / 2 ** 51
         got = host.hc_rounded(amax, w, v) * unit
         assert abs(got - Fraction(w) * Fraction(v)) <= unit / 2, (amax, w, v)
+
+
+def particle(host, d, v, amax=1.0):
+    out = (ctypes.c_longlong * 8)()
+    host.hc_particle(d, v, amax, out)
+    return list(out)
+
+
+def test_particles_without_a_position_or_value_add_nothing(host):
+    """A NaN or infinite displacement, and a NaN or infinite value, add nothing to the
+    FP32 windows: their bit patterns are no integers."""
+    whole = particle(host, 0.5, 1.0)
+    assert sum(whole) == 2 ** 51 and min(whole) > 0
+    nan, inf = float("nan"), float("inf")
+    for d in (nan, inf, -inf):
+        assert particle(host, d, 1.0) == [0] * 8, d
+    for v in (nan, inf, -inf):
+        assert particle(host, 0.5, v) == [0] * 8, v
