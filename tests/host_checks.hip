@@ -1,6 +1,7 @@
 // Host-side functions of the library's headers behind a C interface, for
 // test_host_checks.py: compiled for the host alone, no device is touched.
 #include "../paper_2604_26823_amd/csrc/blocks.h"
+#include "../paper_2604_26823_amd/csrc/sort.h"
 
 extern "C" {
 
@@ -26,6 +27,11 @@ void hc_particle(float d, double v, double amax, long long* out) {
   ic::pk::for_corners_xyz(s, [&](int, int, int, float w, float, float, float) {
     out[k++] = ic::fx::rounded(static_cast<double>(w), x);
   });
+}
+
+// passes that a sort of n values launches
+int hc_sort_passes(int bytes, long long n) {
+  return bytes == 4 ? ic::sort_passes<uint32_t>(n) : ic::sort_passes<uint64_t>(n);
 }
 
 }

@@ -28,6 +28,7 @@ def host(tmp_path_factory):
     lib.hc_rounded.restype, lib.hc_rounded.argtypes = q, [d, d, d]
     lib.hc_particle.restype = None
     lib.hc_particle.argtypes = [ctypes.c_float, d, d, ctypes.POINTER(q)]
+    lib.hc_sort_passes.argtypes = [ctypes.c_int, q]
     return lib
 
 
@@ -74,3 +75,10 @@ def test_particles_without_a_position_or_value_add_nothing(host):
         assert particle(host, d, 1.0) == [0] * 8, d
     for v in (nan, inf, -inf):
         assert particle(host, 0.5, v) == [0] * 8, v
+
+
+def test_a_sort_of_one_value_is_one_pass(host):
+    for size in (4, 8):
+        assert host.hc_sort_passes(size, 1) == 1
+        for n in (2, 1000, 1 << 20, 1 << 27):
+            assert host.hc_sort_passes(size, n) == size
