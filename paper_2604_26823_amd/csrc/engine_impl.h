@@ -709,13 +709,13 @@ class Engine final : public EngineBase {
         o.istart, L, nf, det_fields(ncells), dethl_);
     IC_LAUNCHED();
   }
-  // After it: the nf fields out, and their halos hl zeroed.
+  // After it: the nf fields out, complete; for a consumer that adds a halo, hl zeroed.
   void det_finish(const bk::Layout& L, const double* vmax, T coef, int nf, long long ncells,
                   const bk::MPtrs<T>& out, T* hl) {
     bk::k_det_to_field<T><<<grid_for(ncells, bk::kThreads), bk::kThreads, 0, st_>>>(
         det64_, dethl_, nf, ncells, L, vmax, coef, 3 * lp_, out);
     IC_LAUNCHED();
-    fill(hl, T(0), (long long)nf * HaloMap(L.lm).size());
+    if (hl) fill(hl, T(0), (long long)nf * HaloMap(L.lm).size());
   }
   // *out = max |x_i| over n values.
   void absmax(const T* x, long long n, double* out) {
@@ -728,7 +728,8 @@ class Engine final : public EngineBase {
 
   // rho = CIC density of the state in order o (positions d, ids id), its
   // halo left in hl for the consumer; every cell of
-  // rho and every entry of hl is written here.  With gsrc the positions are read as
+  // rho and every entry of hl is written here (a deterministic paint leaves rho
+  // complete and hl zero, or untouched when null).  With gsrc the positions are read as
   // d[gsrc[a]] (left in the previous order) and stored in order o to dcopy, and
   // the ids' move to o has zeroed what needs it.
   void paint(const T* d, const Order& o, const unsigned* id, const pk::Grid<T>& g,
@@ -789,8 +790,9 @@ class Engine final : public EngineBase {
     build_order(o);
     scatter(o, bk::Ptrs<T>{{d, d + P_, d + 2 * P_}},
             bk::MPtrs<T>{{tmpd_, tmpd_ + P_, tmpd_ + 2 * P_}}, 3, nullptr, dids_, dest(-1));
-    paint(tmpd_, o, dids_, g, L, rho, hl_, ncells);
-    if (complete) add_halo(rho, hl_, L, ncells);
+    const bool whole = complete && det_;  // the paint itself completes rho
+    paint(tmpd_, o, dids_, g, L, rho, whole ? nullptr : hl_, ncells);
+    if (complete && !whole) add_halo(rho, hl_, L, ncells);
   }
 
   // ------------------------------------------------------ k-space chains
@@ -1144,7 +1146,7 @@ class Engine final : public EngineBase {
             det_out(nullptr, P_));
         IC_LAUNCHED();
       }
-      det_finish(Ld_, nullptr, T(1), 1, P_, bk::MPtrs<T>{{rhod_}}, hld_);
+      det_finish(Ld_, nullptr, T(1), 1, P_, bk::MPtrs<T>{{rhod_}}, nullptr);
       return;
     }
     zero_unowned(data_order(), Ld_, 1, bk::MPtrs<T>{{rhod_}}, hld_);
