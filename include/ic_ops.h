@@ -105,7 +105,8 @@ int ic_host_coefficients(const ic_problem* p, double* out, size_t n);
  * starts recording (resetting the totals), 0 stops.  ic_timing_report
  * writes "name count total_ms bytes_per_launch" lines into buf (IC_ERR_
  * INVALID_ARG when len is too small), where bytes_per_launch is the
- * implementation's own count: each buffer a launch reads or writes, once.
+ * implementation's own count: each buffer a launch reads or writes, once
+ * (the mean over the recorded launches of that name).
  * ic_timing_only starts recording the launches of one kernel name only
  * (kernel: a name the report uses, not NULL), so timed code is otherwise
  * unchanged; ic_timing(ctx, 0) stops it. */

@@ -528,6 +528,10 @@ class Engine final : public EngineBase {
   }
 
   double sizeT() const { return (double)sizeof(T); }
+  // Bytes that a paint of one field writes (64-bit integers in deterministic mode).
+  double painted_bytes(const bk::Layout& L, long long ncells) const {
+    return ((double)ncells + HaloMap(L.lm).size()) * (det_ ? 8.0 : sizeT());
+  }
 
   // sum over blocks of part[stride * b + k] into scal_[k..k+stride), then to host.
   void reduce_parts(int nblocks, int stride, double* host) {
@@ -607,7 +611,7 @@ class Engine final : public EngineBase {
   // Scan of the block counts in bcount_ into o, and its work items; the counts
   // are left zeroed.
   void build_order(const Order& o) {
-    auto sc = timer_.scope("sort_scan", 16.0 * o.nb);
+    auto sc = timer_.scope("sort_scan", 16.0 * o.nb + 32.0 * o.nwg);
     if (o.nb <= bk::kOneBlocks) {
       bk::k_order_one<<<1, bk::kOneThreads, 0, st_>>>(bcount_, o.nb, o.nwg, o.start, o.istart,
                                                       o.items, o.items + o.nwg);
@@ -736,7 +740,7 @@ class Engine final : public EngineBase {
              const bk::Layout& L, T* rho, T* hl, long long ncells,
              const unsigned* gsrc = nullptr, T* dcopy = nullptr) {
     const double bytes = P_ * ((gsrc ? 6.0 : 3.0) * sizeT() + (gsrc ? 8.0 : 4.0)) +
-                         2.0 * ncells * sizeT();
+                         painted_bytes(L, ncells);
     if (det_) {
       det_zero_unowned(o, L, 1, ncells);
       {
@@ -770,7 +774,7 @@ class Engine final : public EngineBase {
 
   // rho += the halo hl of its paint, for the callers that read the field itself.
   void add_halo(T* rho, const T* hl, const bk::Layout& L, long long ncells) {
-    auto sc = timer_.scope("halo_add", 2.25 * ncells * sizeT());
+    auto sc = timer_.scope("halo_add", (2.0 * ncells + HaloMap(L.lm).size()) * sizeT());
     bk::k_add_halo<T><<<grid_for(ncells, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
         rho, hl, L, ncells);
     IC_LAUNCHED();
@@ -890,12 +894,18 @@ class Engine final : public EngineBase {
     c2r_yz(f, yo, m, pool_ + (1 + nx) * H, nullptr, T(0), U, Hb, grid == 1);
   }
 
+  // Bytes that the forward passes read of one field (of U bytes) and its halo.
+  double r2c_bytes(const FftArgs<T>& f, const GIn& in, double U) const {
+    return (in.b ? 2 : 1) * U + (in.hl ? HaloMap(ilog2(f.n)).size() * sizeT() : 0.0);
+  }
   // The z and y passes of a chain's m fields: fused into one launch where the
   // grid allows (the chains' spectra are those of real fields), else two passes
   // per field.
   void r2c_zy(const FftArgs<T>& f, const GIn* in, cx<T>* const* S, int m, double U, double Hb) {
     if (fft_zy_fused<T>(f.n)) {
-      auto sc = timer_.scope("fft_r2c_zy", m * ((in[0].b ? 2 : 1) * U + Hb));
+      double bytes = 0;
+      for (int j = 0; j < m; ++j) bytes += r2c_bytes(f, in[j], U) + Hb;
+      auto sc = timer_.scope("fft_r2c_zy", bytes);
       PlaneFwd<T> fl[kMaxMul];
       // the fields with a second input and those without go in launches of their own
       for (int j0 = 0; j0 < m;) {
@@ -911,7 +921,7 @@ class Engine final : public EngineBase {
     }
     for (int j = 0; j < m; ++j) {
       {
-        auto sc = timer_.scope("fft_r2c_z", (in[j].b ? 2 : 1) * U + Hb);
+        auto sc = timer_.scope("fft_r2c_z", r2c_bytes(f, in[j], U) + Hb);
         fft_r2c_z<T>(f, in[j].a, in[j].alpha, in[j].b, in[j].beta, S[j], in[j].hl);
       }
       auto sc = timer_.scope("fft_y", 2 * Hb);
@@ -1140,7 +1150,7 @@ class Engine final : public EngineBase {
     if (det_) {
       det_zero_unowned(data_order(), Ld_, 1, P_);
       {
-        auto sc = timer_.scope("data_paint", P_ * (8.0 * sizeT() + 4.0) + 2.0 * P_ * sizeT());
+        auto sc = timer_.scope("data_paint", P_ * (6.0 * sizeT() + 4.0) + painted_bytes(Ld_, P_));
         bk::k_data_paint_b<T, true><<<bk::item_grid(Ld_, P_), bk::kThreads, 0, st_>>>(
             dsd_, psd_, P_, lp_, rsd(), gdata(), Ld_, items(data_order(), dids_), rhod_, hld_,
             det_out(nullptr, P_));
@@ -1151,7 +1161,7 @@ class Engine final : public EngineBase {
     }
     zero_unowned(data_order(), Ld_, 1, bk::MPtrs<T>{{rhod_}}, hld_);
     {
-      auto sc = timer_.scope("data_paint", P_ * (8.0 * sizeT() + 4.0) + 2.0 * P_ * sizeT());
+      auto sc = timer_.scope("data_paint", P_ * (6.0 * sizeT() + 4.0) + painted_bytes(Ld_, P_));
       bk::k_data_paint_b<T, false><<<bk::item_grid(Ld_, P_), bk::kThreads, 0, st_>>>(
           dsd_, psd_, P_, lp_, rsd(), gdata(), Ld_, items(data_order(), dids_), rhod_, hld_,
           bk::DetOut{});
@@ -1303,7 +1313,8 @@ class Engine final : public EngineBase {
         absmax(pbar_, 3 * P_, detvmax_);  // the paint's scale: max |p_bar| over all slots
         det_zero_unowned(mesh_order(n), Lm_, 3, M_);
         {
-          auto sc = timer_.scope("cic_paint_vec", P_ * (6.0 * sizeT() + 8.0) + 6.0 * M_ * sizeT());
+          auto sc = timer_.scope("cic_paint_vec",
+                                 P_ * (6.0 * sizeT() + 8.0) + 3.0 * painted_bytes(Lm_, M_));
           bk::k_paint_vec_b<T, true><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
               dslot(n), pbar_, coef, P_, lp_, gmesh(), Lm_, it, gbar_, M_, dest(n), hl_,
               det_out(detvmax_, M_));
@@ -1313,7 +1324,8 @@ class Engine final : public EngineBase {
       } else {
         zero_unowned(mesh_order(n), Lm_, 3, gb, hl_);
         {
-          auto sc = timer_.scope("cic_paint_vec", P_ * (6.0 * sizeT() + 8.0) + 6.0 * M_ * sizeT());
+          auto sc = timer_.scope("cic_paint_vec",
+                                 P_ * (6.0 * sizeT() + 8.0) + 3.0 * painted_bytes(Lm_, M_));
           bk::k_paint_vec_b<T, false><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
               dslot(n), pbar_, coef, P_, lp_, gmesh(), Lm_, it, gbar_, M_, dest(n), hl_,
               bk::DetOut{});

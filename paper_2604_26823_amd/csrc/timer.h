@@ -53,7 +53,9 @@ class KernelTimer {
     return Scope(this, recs_used_++);
   }
 
-  // "name count total_ms bytes_per_launch" per kernel, in first-seen order.
+  // "name count total_ms bytes_per_launch" per kernel, in first-seen order; the
+  // bytes are the mean over its launches (one launch takes a chain's fields,
+  // one to nine of them).
   std::string report() {
     IC_HIP(hipStreamSynchronize(stream_));
     struct Agg {
@@ -69,7 +71,7 @@ class KernelTimer {
       if (it == agg.end()) it = agg.emplace(recs_[i].name, Agg{0, 0, 0, i}).first;
       it->second.count += 1;
       it->second.ms += ms;
-      it->second.bytes = recs_[i].bytes;
+      it->second.bytes += recs_[i].bytes;
     }
     std::vector<std::pair<std::string, Agg>> v(agg.begin(), agg.end());
     std::sort(v.begin(), v.end(),
@@ -77,8 +79,8 @@ class KernelTimer {
     std::ostringstream os;
     os.precision(9);
     for (auto& kv : v)
-      os << kv.first << " " << kv.second.count << " " << kv.second.ms << " " << kv.second.bytes
-         << "\n";
+      os << kv.first << " " << kv.second.count << " " << kv.second.ms << " "
+         << kv.second.bytes / kv.second.count << "\n";
     return os.str();
   }
 

@@ -40,3 +40,50 @@ def test_deterministic_paint_takes_no_halo_pass(prec, nm):
             assert np.max(np.abs(to_np(rho) - ref)) <= (2e-5 if prec == "f32" else 1e-11)
     finally:
         ctx.close()
+
+
+def spectrum_bytes(n, elem):
+    return n * n * (n // 2 + 1) * 2 * elem
+
+
+def halo_entries(n):
+    """Entries of a paint's halo: three faces, three edges and a corner per 8^3
+    block, rounded up to 32."""
+    b = n // 8
+    return (3 * n * n * b + 3 * n * b * b + b ** 3 + 31) // 32 * 32
+
+
+@pytest.mark.parametrize("prec", PRECS)
+def test_report_counts_the_fields_of_every_launch(prec):
+    """bytes_per_launch of the fused inverse passes over launches of one field (the
+    multiplier) and of six (2LPT, twice): the mean, each field read as a half
+    spectrum and written once."""
+    require_gpu()
+    n, elem = 16, 4 if prec == "f32" else 8
+    ctx = Context(cfg_small(1, n_part=n, n_mesh=n, n_steps=1, rsd="z", box=8.0 * n), prec, "cuda:0")
+    try:
+        x = to_dev(np.random.default_rng(36).standard_normal((n, n, n)), prec)
+        rows, _ = recorded(ctx, lambda: (ctx.lpt(x), ctx.multiplier(x, 2)))
+        row = rows["fft_c2r_yz"]
+        field = n ** 3 * elem + spectrum_bytes(n, elem)
+        assert row["count"] == 3
+        assert abs(row["bytes"] - (6 + 6 + 1) * field / 3) <= 1e-6 * field
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("det", [0, 1])
+def test_report_counts_what_a_paint_writes(prec, det):
+    """A paint reads positions and ids and writes its field and halo, once each."""
+    require_gpu()
+    n, elem = 16, 4 if prec == "f32" else 8
+    ctx = Context(cfg_small(1, n_part=n, n_mesh=n, n_steps=1, rsd="z", box=8.0 * n,
+                            deterministic=det), prec, "cuda:0")
+    try:
+        d = to_dev(np.random.default_rng(37).normal(0, 6.0, (3, n ** 3)), prec)
+        rows, _ = recorded(ctx, lambda: ctx.paint(d, 0))
+        out = (n ** 3 + halo_entries(n)) * (8 if det else elem)
+        assert rows["cic_paint"]["bytes"] == n ** 3 * (3 * elem + 4) + out
+    finally:
+        ctx.close()
