@@ -165,8 +165,22 @@ void spectrum_unpack(const FftArgs<T>& f, const cx<T>* dense, cx<T>* stored);
 // The x passes' outputs at most, and inputs of a scatter.
 constexpr int kMaxXOut = 4;
 
+// The outputs of a scatter must not share storage with its inputs or with each
+// other: on small grids every output is a row of workgroups of its own, which
+// reads the inputs again.
+template <typename T>
+inline void require_apart(const cx<T>* const* in, int nin, const XOut<T>* outs, int m) {
+  for (int j = 0; j < m; ++j) {
+    bool apart = true;
+    for (int q = 0; q < nin; ++q) apart = apart && outs[j].S != in[q];
+    for (int k = 0; k < j; ++k) apart = apart && outs[j].S != outs[k].S;
+    if (!apart) throw ApiError(-7, "outputs of an x scatter share storage");
+  }
+}
+
 // Forward x FFT of the nin (1 or 2) inputs, then for each j < m the inverse x
-// FFT of outs[j]; white[q] per input, div for both.
+// FFT of outs[j]; white[q] per input, div for both.  The outputs must be apart
+// (require_apart).
 template <typename T>
 void fft_x_scatter(const FftArgs<T>& f, const cx<T>* const* in, const int* white, int nin,
                    int div, const XOut<T>* outs, int m);

@@ -1672,6 +1672,7 @@ template <typename T>
 void fft_x_scatter(const FftArgs<T>& f, const cx<T>* const* in, const int* white, int nin,
                    int div, const XOut<T>* outs, int m) {
   if (m < 1 || m > kMaxXOut || nin < 1 || nin > 2) throw ApiError(-1, "x pass out of range");
+  require_apart<T>(in, nin, outs, m);
   fftk::InPtrs<T> ip{};
   for (int q = 0; q < nin; ++q) ip.p[q] = in[q];
   fftk::XOutSet<T> set{};

@@ -1,6 +1,7 @@
 // Host-side functions of the library's headers behind a C interface, for
 // test_host_checks.py: compiled for the host alone, no device is touched.
 #include "../paper_2604_26823_amd/csrc/blocks.h"
+#include "../paper_2604_26823_amd/csrc/fft.h"
 #include "../paper_2604_26823_amd/csrc/sort.h"
 
 extern "C" {
@@ -32,6 +33,20 @@ void hc_particle(float d, double v, double amax, long long* out) {
 // passes that a sort of n values launches
 int hc_sort_passes(int bytes, long long n) {
   return bytes == 4 ? ic::sort_passes<uint32_t>(n) : ic::sort_passes<uint64_t>(n);
+}
+
+// status of an x scatter from spectra 0 and 1 to outputs o0 and o1 (numbers of spectra):
+// 0 if it is launched, else the refusal's code
+int hc_x_scatter(int o0, int o1) {
+  ic::cx<float> spectra[4];
+  const ic::cx<float>* in[2] = {spectra, spectra + 1};
+  const ic::XOut<float> out[2] = {{spectra + o0, 1.0, 0.0, 0}, {spectra + o1, 1.0, 0.0, 1}};
+  try {
+    ic::require_apart<float>(in, 2, out, 2);
+  } catch (const ic::ApiError& e) {
+    return e.code;
+  }
+  return 0;
 }
 
 }

@@ -12,6 +12,7 @@ import pytest
 
 from paper_2604_26823_amd import build
 
+STATE = -7  # IC_ERR_STATE
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -82,3 +83,11 @@ def test_a_sort_of_one_value_is_one_pass(host):
         assert host.hc_sort_passes(size, 1) == 1
         for n in (2, 1000, 1 << 20, 1 << 27):
             assert host.hc_sort_passes(size, n) == size
+
+
+def test_scatter_outputs_must_not_share_storage(host):
+    """On small grids each output of an x scatter is a workgroup row of its own that reads
+    the inputs again: an output in an input's place, or in another output's, is refused."""
+    assert host.hc_x_scatter(2, 3) == 0
+    for o0, o1 in ((0, 3), (2, 1), (2, 2)):
+        assert host.hc_x_scatter(o0, o1) == STATE, (o0, o1)
