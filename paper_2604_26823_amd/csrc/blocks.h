@@ -1304,7 +1304,6 @@ __global__ __launch_bounds__(kThreads) void k_step_b(
     rank[a[k]] = static_cast<unsigned>(slot[k]) << kRankBits | r;
     if (slot[k] == kNbr) key[a[k]] = b[k];
   }
-  if (!count) return;
   __syncthreads();
   rank_reserve_wg(m.b, L, count, wcnt, nbr_base + static_cast<size_t>(m.i) * kNbrRow);
 }

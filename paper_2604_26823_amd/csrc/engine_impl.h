@@ -473,7 +473,6 @@ class Engine final : public EngineBase {
     f.kp = grid ? kpm_ : kpp_;
     f.tw = grid ? twm_ : twp_;
     f.wtab = wtab_;
-    f.box = prob_.box;
     f.stream = st_;
     return f;
   }

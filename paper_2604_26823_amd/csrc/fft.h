@@ -83,7 +83,6 @@ struct FftArgs {
   int kp = 0;                   // stored row pitch of the half spectrum (spectrum_pitch)
   const cx<T>* tw = nullptr;    // device table exp(-2 pi i m / n), m < n
   const T* wtab = nullptr;      // whitening multiplier indexed by |k|^2 / kf^2 (particle grid)
-  double box = 1.0;             // box side (for i k / k^2)
   hipStream_t stream = nullptr;
 };
 

@@ -1467,18 +1467,30 @@ void dispatch_n(int n, F&& f) {
   }
 }
 
+// Whether fields of side N always take the fused z and y passes (without aux), so
+// that their separate passes need no slab or halo form.
+template <typename T, int N>
+constexpr bool planes() {
+  return N <= 128 || ZYCfg<T, N>::ok;
+}
+
 }  // namespace fftk
+
+template <typename T>
+bool fft_zy_fused(int n, bool with_aux) {
+  return n <= 128 || (!with_aux && fftk::ZYCfg<T, 256>::ok && n == 256);
+}
 
 template <typename T>
 void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* out,
                const T* hl) {
-  if (hl && f.n <= 128) throw ApiError(-2, "painted fields of n <= 128 go through the fused planes");
+  if (hl && fft_zy_fused<T>(f.n)) throw ApiError(-2, "painted fields go through the fused planes");
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     using C = fftk::ZCfg<T, N>;
     const int nlines = f.n * f.n;
     fftk::with_flags(hl != nullptr, b != nullptr, [&](auto HL, auto B) {
-      fftk::k_r2c_z<T, N, HL.value && (N > 128), B.value>
+      fftk::k_r2c_z<T, N, HL.value && !fftk::planes<T, N>(), B.value>
           <<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(a, alpha, b, beta, out,
                                                                       f.tw, f.kp, hl);
     });
@@ -1489,24 +1501,20 @@ void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<
 template <typename T>
 void fft_c2r_z(const FftArgs<T>& f, const cx<T>* in, T* out, T alpha, const T* aux, T beta,
                bool slab) {
+  if (slab && fft_zy_fused<T>(f.n)) throw ApiError(-2, "slabs come out of the fused planes");
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     using C = fftk::ZCfg<T, N>;
     const int nlines = f.n * f.n;
     const unsigned grid = blocks_for(nlines, C::LINES);
     if (slab)
-      fftk::k_c2r_z<T, N, true><<<grid, C::THREADS, 0, f.stream>>>(in, out, alpha, aux, beta,
+      fftk::k_c2r_z<T, N, !fftk::planes<T, N>()><<<grid, C::THREADS, 0, f.stream>>>(in, out, alpha, aux, beta,
                                                                    f.tw, f.kp);
     else
       fftk::k_c2r_z<T, N, false><<<grid, C::THREADS, 0, f.stream>>>(in, out, alpha, aux, beta,
                                                                     f.tw, f.kp);
   });
   IC_LAUNCHED();
-}
-
-template <typename T>
-bool fft_zy_fused(int n, bool with_aux) {
-  return n <= 128 || (!with_aux && fftk::ZYCfg<T, 256>::ok && n == 256);
 }
 
 // f(integral_constant<N>) for the sides of the fused planes.
@@ -1603,12 +1611,13 @@ void fft_y(const FftArgs<T>& f, cx<T>* data, bool forward) {
 
 template <typename T>
 void fft_y_inv(const FftArgs<T>& f, const cx<T>* in, cx<T>* out, const YZMul<T>& mul) {
+  if (f.n <= 128) throw ApiError(-2, "multipliers of n <= 128 go through the fused planes");
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     using C = fftk::SCfg<T, N>;
     const int K = N / 2 + 1, kp = f.kp;
     const int nlines = N * kp;
-    fftk::k_strided<T, N, false, true><<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(
+    fftk::k_strided<T, N, false, (N > 128)><<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(
         in, out, T(1), f.tw, nlines, kp, (long long)N * kp, kp, kp, K, mul);
   });
   IC_LAUNCHED();
