@@ -57,7 +57,7 @@ void noalloc_sort_desc(int precision, const void* values, int64_t n, int32_t* or
 
 void validate_problem(const ic_problem& p) {
   auto bad = [](int code, const char* m) { throw ApiError(code, m); };
-  if (!pow2(p.n_part) || p.n_part < 8 || p.n_part > 512)
+  if (!pow2(p.n_part) || p.n_part < 8 || p.n_part > kMaxPart)
     bad(IC_ERR_UNSUPPORTED, "n_part must be a power of two in [8, 512]");
   if (!(p.n_mesh == p.n_part || p.n_mesh == 2 * p.n_part) || p.n_mesh > 1024)
     bad(IC_ERR_UNSUPPORTED, "n_mesh must be n_part or 2 n_part and at most 1024");

@@ -54,6 +54,9 @@ size_t workspace_bytes(const ic_problem& p, int precision);
 EngineBase* make_engine(const ic_problem& p, int precision, void* ws, size_t ws_bytes,
                         hipStream_t stream);
 
+// Largest particle grid side.
+constexpr int kMaxPart = 512;
+
 // Shape / parameter validation shared by ic_workspace_size and ic_create.
 void validate_problem(const ic_problem& p);
 

@@ -1483,6 +1483,8 @@ class Engine final : public EngineBase {
   unsigned long long* dethl_ = nullptr;    // their halos
   double* detvmax_ = nullptr;              // its cotangent paint's max |p_bar|
   static_assert(bk::kB == kSlab, "slabs are as deep as the blocks");
+  static_assert((1ll << bk::kRankBits) >= 1ll * kMaxPart * kMaxPart * kMaxPart,
+                "a particle's packed rank");
   T *tmpd_, *tmpp_, *dsd_, *psd_, *dbar2_, *pbar2_;
   T* vbuf_;
   uint32_t* dbg_idx_[2];

@@ -6,6 +6,9 @@
 
 namespace ic {
 
+static_assert(1ll * kMaxPart * kMaxPart * (kMaxPart / 2 + 1) < (1ll << rk::kModeBits),
+              "mode numbers");
+
 // Real space: the cells with R >= r_min, ranked by the white noise in
 // descending order (ties by cell index), receive the sorted N(0,1) targets.
 template <typename T>

@@ -90,9 +90,10 @@ static __global__ void k_bin_table(int len, double kf, double kmin, double dk, i
 }
 
 // Half-spectrum modes f = (kx n + ky) K + kz, K = n/2 + 1.
+constexpr int kModeBits = 28;  // f < 2^kModeBits
 struct Modes {
   int n, K;
-  uint64_t magic;      // ceil(2^40 / K): f / K = f magic >> 40 for f < 2^28
+  uint64_t magic;      // ceil(2^40 / K): f / K = f magic >> 40 for f < 2^kModeBits
   const uint8_t* tab;  // k_bin_table
   struct At {
     uint32_t r, kz;  // f = r K + kz
