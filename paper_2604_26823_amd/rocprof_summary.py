@@ -37,6 +37,7 @@ SCOPES = {
     "k_scatter_b": "sort_scatter",
     "k_add_halo": "halo_add",
     "k_add_halo_x": "halo_x",
+    "k_scatter_ids": "sort_scatter_ids",
     "k_scatter_ids_b": "sort_scatter_ids",
     "k_gather_back": "sort_gather_back",
     "k_keys": "sort_keys",
@@ -49,6 +50,7 @@ SCOPES = {
     "k_strided": "fft_y",
     "k_x_scatter": "fft_x_scatter",
     "k_x_gather": "fft_x_gather",
+    "k_x_gather_wide": "fft_x_gather",
     "k_mu2": "lpt_mu2",
     "k_phi_bar": "lpt_phi_bar",
     "k_loss": "loss",
