@@ -193,6 +193,27 @@ void fft_x_scatter(const FftArgs<T>& f, const cx<T>* const* in, const int* white
 template <typename T>
 void fft_x_embed(const FftArgs<T>& f, cx<T>* S, const cx<T>* lo, int nl, T scale, T norm);
 
+// Workgroups of an x pass up to which it counts as small: the chip has 256 CUs,
+// and a pass over m fields then spreads them over more workgroups or threads.
+// Grids up to 64^3 have at most 320, 128^3 at least 640.  Below the line the
+// spread is faster (64^3, scatters of two and three outputs 5.4 and 6.4 us against
+// 6.0 of one row of workgroups in FP32, of four from two inputs 8.6 against 9.9; 32^3
+// FP64 6.9 against 9.6), above it slower (128^3, three outputs 11.6 -> 16.3 us
+// in FP32 and 16.1 -> 24.3 in FP64, the three-input gather 13.4 -> 26.7 and 19.9 -> 33.1).
+constexpr unsigned kSmallGrid = 512;
+constexpr unsigned kCus = 256;
+constexpr size_t kCuLds = 160 * 1024;
+
+// Whether a gather of m inputs, `blocks` workgroups of `threads` each, takes its
+// inputs side by side (lds: bytes of the m tiles): on small grids, where the CUs
+// hold all its workgroups at once.  Three inputs take 8.2 us instead of 9.0 at
+// 64^3 in FP64 and 6.0 instead of 8.7 at 32^3, nine 7.9 instead of 18.0 at 32^3;
+// at 64^3 nine would fill a CU's LDS with each of 320 workgroups, a second round
+// for 64 of them: 20.6 us against 18.7 one after the other.
+inline bool gather_wide(unsigned blocks, int m, int threads, size_t lds) {
+  return m > 1 && threads * m <= 1024 && blocks <= kSmallGrid && blocks <= kCus * (kCuLds / lds);
+}
+
 // out = inverse x FFT of sum_j mult_j * forward x FFT of ins[j]; out may equal
 // ins[0].  The multipliers share white and div.
 template <typename T>

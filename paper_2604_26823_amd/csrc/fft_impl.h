@@ -1657,10 +1657,6 @@ void spectrum_unpack(const FftArgs<T>& f, const cx<T>* dense, cx<T>* stored) {
   IC_LAUNCHED();
 }
 
-// Workgroups of an x pass up to which it counts as small: the chip has 256 CUs,
-// and a pass over m fields then spreads them over more workgroups or threads.
-constexpr unsigned kSmallGrid = 512;
-
 template <typename T, int NIN>
 void x_scatter(const FftArgs<T>& f, const fftk::InPtrs<T>& ip, const int* white, int div,
                const fftk::XOutSet<T>& set, int m) {
@@ -1718,9 +1714,9 @@ void fft_x_gather(const FftArgs<T>& f, const cx<T>* const* ins, const Mul* muls,
     const int K = N / 2 + 1;
     const int nlines = N * f.kp;
     const unsigned blocks = blocks_for(nlines, C::LINES);
-    if constexpr (N <= 64) {
-      if (m > 1 && blocks <= kSmallGrid && C::THREADS * m <= 1024) {
-        const size_t lds = sizeof(cx<T>) * (N + (size_t)m * N * C::LP);
+    if constexpr (N <= 64) {  // (128 and above: too many workgroups)
+      const size_t lds = sizeof(cx<T>) * (N + (size_t)m * N * C::LP);
+      if (gather_wide(blocks, m, C::THREADS, lds)) {
         fftk::k_x_gather_wide<T, N><<<blocks, C::THREADS * m, lds, f.stream>>>(
             ip, gs, white, div, m, out, f.wtab, f.tw, nlines, K, f.kp);
         return;

@@ -49,4 +49,10 @@ int hc_x_scatter(int o0, int o1) {
   return 0;
 }
 
+// whether a gather of m inputs by `blocks` workgroups of `threads` per input takes its
+// inputs side by side, with `lds` bytes of tile per input
+int hc_gather_wide(unsigned blocks, int m, int threads, long long lds) {
+  return ic::gather_wide(blocks, m, threads, static_cast<size_t>(lds) * m);
+}
+
 }

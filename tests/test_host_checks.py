@@ -29,6 +29,7 @@ def host(tmp_path_factory):
     lib.hc_rounded.restype, lib.hc_rounded.argtypes = q, [d, d, d]
     lib.hc_particle.restype = None
     lib.hc_particle.argtypes = [ctypes.c_float, d, d, ctypes.POINTER(q)]
+    lib.hc_gather_wide.argtypes = [ctypes.c_uint, ctypes.c_int, ctypes.c_int, q]
     lib.hc_sort_passes.argtypes = [ctypes.c_int, q]
     return lib
 
@@ -91,3 +92,17 @@ def test_scatter_outputs_must_not_share_storage(host):
     assert host.hc_x_scatter(2, 3) == 0
     for o0, o1 in ((0, 3), (2, 1), (2, 2)):
         assert host.hc_x_scatter(o0, o1) == STATE, (o0, o1)
+
+
+@pytest.mark.parametrize("n,prec,blocks,threads,lds,m,wide", [
+    (8, "f32", 2, 64, 8 * 8 * 65, 9, 1), (16, "f64", 4, 64, 16 * 16 * 65, 9, 1),
+    (32, "f64", 96, 32, 16 * 32 * 9, 9, 1), (64, "f32", 192, 128, 8 * 64 * 17, 3, 1),
+    (64, "f64", 320, 64, 16 * 64 * 9, 3, 1), (64, "f32", 192, 128, 8 * 64 * 17, 9, 0),
+    (64, "f64", 320, 64, 16 * 64 * 9, 9, 0), (64, "f64", 320, 64, 16 * 64 * 9, 1, 0),
+    (128, "f32", 640, 256, 8 * 128 * 17, 3, 0), (128, "f64", 1152, 128, 16 * 128 * 9, 3, 0)])
+def test_gathers_go_wide_where_all_their_workgroups_run_at_once(host, n, prec, blocks, threads,
+                                                                lds, m, wide):
+    """Side by side the inputs of a gather take m times the LDS and threads: only while
+    the chip's 256 CUs hold every workgroup at once (nine inputs at 64^3 in FP64 fill
+    a CU's LDS with one workgroup each, 320 of them)."""
+    assert host.hc_gather_wide(blocks, m, threads, lds) == wide
