@@ -62,8 +62,8 @@ constexpr int kChunk = kThreads * kPer;  // particles per work item
 // slabs (its fields pass between the paints, the FFT's z passes and the
 // readouts only): a block's window is then nine runs of 72 cells and one of
 // nine cells 32 bytes apart per x, where [x][y][z] makes it 81 rows of nine
-// cells, each in a 128-byte line of its own, and the rows of a window lie
-// 64 n bytes apart instead of 4 n^2 (FP32).  Loading those rows cost 120 us of the 345 us step and
+// cells, each in a 128-byte line of its own, and the planes x of a window lie
+// 32 n bytes apart instead of 4 n^2 (FP32).  Loading those rows cost 120 us of the 345 us step and
 // 150 us of the 389 us force adjoint at 256^3 in FP32, several times what the
 // bytes take.
 struct Layout {
@@ -452,7 +452,9 @@ static __global__ __launch_bounds__(256) void k_fill_items(const unsigned* __res
 
 // The scan and the items of an order of at most kOneBlocks blocks (grids up to
 // 128^3) by one workgroup: the four launches of the general path, three of them
-// scans of a few thousand counts, took 12 us of every step at 32^3 and 64^3.
+// scans of a few thousand counts, took 12 us of every step at 32^3 and 64^3 (a
+// paint of 32^3 particles 26.9 us instead of 34.5, of 128^3 89 instead of 94).  The
+// 32768 blocks of a 256^3 grid are too many for one: that paint would go from 513 to 692 us.
 constexpr unsigned kOneThreads = 1024;
 constexpr unsigned kOnePer = 4;
 constexpr unsigned kOneBlocks = kOneThreads * kOnePer;

@@ -145,9 +145,10 @@ class Engine final : public EngineBase {
     if (det_) {
       // deterministic mode: the paints' integer fields (three mesh fields, or
       // the data grid), their halos, and the device maximum the cotangent
-      // paint's scale is chosen for.  The mode's addition to the workspace is
-      // part of the interface: three fields' entries along z and 153 per work
-      // item and field, of which the halos take 3.4 n^3 / 8 per field (74 to 96 %).
+      // paint's scale is chosen for.  Callers that know the mode's addition to the
+      // workspace (three fields' entries along z and 153 per work item and field)
+      // find it unchanged; the halos use 74 to 96 % of that part, 3.4 n^3 / 8 entries
+      // per field, and nothing uses the rest.
       det64_ = c.take<unsigned long long>(3 * std::max(M_, P_));
       dethl_ = c.take<unsigned long long>(std::max<size_t>(
           3 * std::max(M_, P_) / 8 + (size_t)std::max<long long>(3ll * mim_, mid_) * 153,

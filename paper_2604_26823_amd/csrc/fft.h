@@ -5,7 +5,8 @@
 // even/odd split), and complex passes along y and x over the half spectrum
 // [n][n][n/2+1], stored with each z row padded to kp >= n/2+1 entries so
 // that rows start on 128-byte boundaries and the strided passes move whole
-// cache lines (the pad entries are never read).  The x pass is the last forward axis
+// cache lines (the y and x passes load and transform the pad entries with the
+// others, and store none of them).  The x pass is the last forward axis
 // and the first inverse one, so k-space multipliers are applied inside it:
 // one kernel runs the forward x FFT, multiplies by m multipliers and runs m
 // inverse x FFTs (scatter), or the reverse for m inputs summed into one
