@@ -1115,8 +1115,9 @@ __global__ __launch_bounds__(kThreads) void k_paint_b(const T* __restrict__ d,
   int idx[kPer][3];
   T dsp[kPer][3];
   item_slots(m, a, ok);  // loads in flight while the window is cleared
-  // all rounds at once: by rounds the paint took 158 us instead of 148 (FP32,
-  // 256^3), its loads through gsrc starting later
+  // all rounds at once: by rounds, whose loads through gsrc start later, this kernel
+  // measured 158 us instead of 148 when it was split off, 164 instead of 168 with
+  // the present flush (FP32, 256^3)
   load_u32<kPer>(it.ids, a, id);
   if (gsrc) {
     unsigned sa[kPer];
