@@ -1434,22 +1434,19 @@ __global__ void k_spec_copy(const cx<T>* __restrict__ src, cx<T>* __restrict__ d
 }
 
 // ------------------------------------------------------------ dispatch
-// f(HL, B) with the two flags as compile-time constants.
+// f(HL, B) with the two flags as compile-time constants (a painted field, which
+// has a halo, has no second input).
 template <class F>
 void with_flags(bool hl, bool b, F&& f) {
   using Y = std::true_type;
   using No = std::false_type;
-  if (hl) {
-    if (b)
-      f(Y{}, Y{});
-    else
-      f(Y{}, No{});
-  } else {
-    if (b)
-      f(No{}, Y{});
-    else
-      f(No{}, No{});
-  }
+  if (hl && b) throw ApiError(-2, "a field with a halo has no second input");
+  if (hl)
+    f(Y{}, No{});
+  else if (b)
+    f(No{}, Y{});
+  else
+    f(No{}, No{});
 }
 
 template <typename T, class F>
@@ -1467,8 +1464,8 @@ void dispatch_n(int n, F&& f) {
   }
 }
 
-// Whether fields of side N always take the fused z and y passes (without aux), so
-// that their separate passes need no slab or halo form.
+// Whether the chains' fields of side N always take the fused z and y passes (without
+// aux), so that the separate passes need no slab, halo or second-input form.
 template <typename T, int N>
 constexpr bool planes() {
   return N <= 128 || ZYCfg<T, N>::ok;
@@ -1484,13 +1481,14 @@ bool fft_zy_fused(int n, bool with_aux) {
 template <typename T>
 void fft_r2c_z(const FftArgs<T>& f, const T* a, T alpha, const T* b, T beta, cx<T>* out,
                const T* hl) {
-  if (hl && fft_zy_fused<T>(f.n)) throw ApiError(-2, "painted fields go through the fused planes");
+  if ((hl || b) && fft_zy_fused<T>(f.n)) throw ApiError(-2, "chains go through the fused planes");
   fftk::dispatch_n<T>(f.n, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     using C = fftk::ZCfg<T, N>;
     const int nlines = f.n * f.n;
     fftk::with_flags(hl != nullptr, b != nullptr, [&](auto HL, auto B) {
-      fftk::k_r2c_z<T, N, HL.value && !fftk::planes<T, N>(), B.value>
+      fftk::k_r2c_z<T, N, HL.value && !fftk::planes<T, N>(),
+                    B.value && !fftk::planes<T, N>()>
           <<<blocks_for(nlines, C::LINES), C::THREADS, 0, f.stream>>>(a, alpha, b, beta, out,
                                                                       f.tw, f.kp, hl);
     });
