@@ -1545,7 +1545,7 @@ __global__ __launch_bounds__(kThreads) void k_data_paint_b(const T* __restrict__
     flush_owned<T>(m, Ld, acc, sc, 1, MPtrs<T>{{rho}}, hl);
 }
 
-// Adjoint of the RSD + data paint (see pk::k_data_adjoint) over the data
+// Adjoint of the redshift-space distortion and the data paint over the data
 // order: d_bar, p_bar in that order.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_data_adjoint_b(

@@ -30,7 +30,8 @@ __host__ __device__ inline Scale scale_for(double amax) {
 // bit patterns count up with them, so the integer is the difference of the bit
 // patterns.  o depends on x alone and the low words of its bits are zero: an
 // addition costs the fma and one 32-bit subtraction.  (One constant for both
-// signs, 1.5 2^52, leaves 51 bits.)
+// signs, 1.5 2^52, leaves 51 bits; the cotangent paint takes 257 us instead of 254 at
+// 256^3 for the bit, the density paint 168 either way.)
 __host__ __device__ inline long long rounded(double w, double x) {
   const double o = x < 0.0 ? 0x1p53 : 0x1p52;
   return __builtin_bit_cast(long long, fma(w, x, o)) - __builtin_bit_cast(long long, o);
