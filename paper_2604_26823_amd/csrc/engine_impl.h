@@ -634,7 +634,7 @@ class Engine final : public EngineBase {
   // Moves nf state fields to the order o (keys and ranks in bkey_ / brank_).
   void scatter(const Order& o, const bk::Ptrs<T>& src, const bk::MPtrs<T>& dst, int nf,
                const unsigned* ids_src, unsigned* ids_dst, unsigned* dst_slots) {
-    auto sc = timer_.scope("sort_scatter", P_ * (2.0 * nf * sizeT() + 20.0));
+    auto sc = timer_.scope("sort_scatter", P_ * (2.0 * nf * sizeT() + (ids_src ? 20.0 : 16.0)));
     bk::k_scatter<T><<<grid_for(P_, bk::kThreads, 1u << 30), bk::kThreads, 0, st_>>>(
         bkey_, brank_, o.start, src, dst, nf, ids_src, ids_dst, dst_slots, P_, lp_);
     IC_LAUNCHED();
@@ -1101,7 +1101,8 @@ class Engine final : public EngineBase {
     }
     seg_ = K_ ? S_ - S_ % K_ : 0;
     {
-      auto sc = timer_.scope("final_kick", P_ * (9.0 * sizeT() + 12.0) + 3.0 * M_ * sizeT());
+      auto sc = timer_.scope("final_kick",
+                             P_ * (9.0 * sizeT() + (pinv ? 12.0 : 8.0)) + 3.0 * M_ * sizeT());
       // the final momenta go to pslot(S) in order S (in place when state S
       // is complete; else pin, in tmpp_ or pbar2_, is read through pinv)
       bk::k_final_b<T><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
@@ -1176,7 +1177,8 @@ class Engine final : public EngineBase {
   // previous order.
   void step(int n, bool keyed, const T* pin, const unsigned* pinv, T* pout) {
     auto sc = timer_.scope(keyed ? "pm_step" : "pm_step_replay",
-                           P_ * (12.0 * sizeT() + (pinv ? 16.0 : 12.0)) + 3.0 * M_ * sizeT());
+                           P_ * (12.0 * sizeT() + 4.0 + (pinv ? 4.0 : 0.0) + (keyed ? 4.0 : 0.0)) +
+                               3.0 * M_ * sizeT());
     bk::k_step_b<T><<<bk::item_grid(Lm_, P_), bk::kThreads, 0, st_>>>(
         dslot(n), pin, pinv, gslot(n), M_, static_cast<T>(co_.kick[n]),
         static_cast<T>(co_.Dr[n]), P_, lp_, gmesh(), Lm_, items(mesh_order(n), ids(n)), tmpd_,

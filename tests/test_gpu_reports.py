@@ -87,3 +87,23 @@ def test_report_counts_what_a_paint_writes(prec, det):
         assert rows["cic_paint"]["bytes"] == n ** 3 * (3 * elem + 4) + out
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("prec", PRECS)
+def test_report_counts_what_a_step_moves(prec):
+    """The step of a one-step run reads positions, momenta (through the order's map) and
+    ids, the force meshes once, and writes both states and one packed rank; the
+    2LPT state is counted into its order by a key and a rank per particle."""
+    require_gpu()
+    n, elem = 16, 4 if prec == "f32" else 8
+    ctx = Context(cfg_small(1, n_part=n, n_mesh=n, n_steps=1, rsd="z", box=8.0 * n), prec, "cuda:0")
+    try:
+        s = to_dev(np.random.default_rng(38).standard_normal((n, n, n)), prec)
+        rows, _ = recorded(ctx, lambda: ctx.evolve(s))
+        assert rows["pm_step"]["bytes"] == n ** 3 * (12 * elem + 12) + 3 * n ** 3 * elem
+        assert rows["sort_keys"]["bytes"] == n ** 3 * (3 * elem + 8)
+        d = to_dev(np.random.default_rng(39).normal(0, 6.0, (3, n ** 3)), prec)
+        rows, _ = recorded(ctx, lambda: ctx.paint(d, 0))
+        assert rows["sort_scatter"]["bytes"] == n ** 3 * (6 * elem + 16)
+    finally:
+        ctx.close()
